@@ -312,11 +312,16 @@ sv_status_t sv_fused_block_is_diagonal(sv_fused_t f, int32_t i, int32_t* diagona
 
 sv_status_t sv_fused_free(sv_fused_t f);
 
-/* Applies all blocks of f in order (async).  Block matrices are uploaded in
- * batches of up to 1 MiB, one host-to-device copy per batch. */
+/* Applies all blocks of f (async), as if in order: consecutive blocks whose
+ * qubits fit one tile share a sweep of the state (Sec. II-B: a sweep is bound
+ * by the bandwidth), and on states of 22 qubits and more a block may pass
+ * blocks on other qubits on its way into a sweep.  With a forced tile variant
+ * (sv_handle_set_tile_mode) every block is swept on its own, in order.  Block
+ * matrices are uploaded in batches of up to 1 MiB, one host-to-device copy per
+ * batch. */
 sv_status_t sv_apply_fused(sv_state_t s, sv_fused_t f);
 
-/* Applies blocks [first, first + count) of f in order (async), so a caller
+/* Applies blocks [first, first + count) of f, as sv_apply_fused does (async), so a caller
  * can interleave its own work (timing events, measurements) between blocks.
  * Requires 0 <= first and first + count <= the block count. */
 sv_status_t sv_apply_fused_range(sv_state_t s, sv_fused_t f, int32_t first, int32_t count);

@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsv.so")
 
-SOURCES = ["sv_api.cpp", "sv_fuse.cpp", "sv_batch.cpp", "sv_apply.hip", "sv_reduce.hip", "sv_batch.hip"]
+SOURCES = ["sv_api.cpp", "sv_fuse.cpp", "sv_batch.cpp", "sv_apply.hip", "sv_sweep.hip", "sv_reduce.hip", "sv_batch.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

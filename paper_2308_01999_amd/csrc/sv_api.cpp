@@ -16,6 +16,7 @@
 
 #include "sv_batch.h"
 #include "sv_internal.h"
+#include "sv_sweep.h"
 #include "sv_tile.h"
 
 namespace sv {
@@ -751,31 +752,30 @@ bool pad_coupled_to_five(int n, const FusedBlock& b, FusedBlock& out, std::vecto
     return true;
 }
 
-// The blocks as launched: dense blocks on 2-4 qubits of a large state padded
-// to five qubits (pad_to_five; blocks of coupled fusion from 1 qubit up,
-// pad_coupled_to_five), all others as they are.
-void effective_blocks(int n, const sv_fused_s* f, int first, int end, std::vector<FusedBlock>& eff,
-                      std::vector<std::vector<double>>& padm, std::vector<std::vector<double>>& padc)
+// Block b as launched on its own: dense blocks on 2-4 qubits of a large state
+// padded to five qubits (pad_to_five; blocks of coupled fusion from 1 qubit
+// up, pad_coupled_to_five), all others as they are.
+struct LoneBlock {
+    FusedBlock b;
+    std::vector<double> m, c;  // storage of a padded block
+};
+
+void make_lone(int n, const FusedBlock& blk, LoneBlock& out)
 {
-    eff.assign(f->blocks, f->blocks + f->n_blocks);
-    padm.resize(f->n_blocks);
-    padc.resize(f->n_blocks);
-    for (int b = first; b < end; ++b) {
-        FusedBlock& blk = eff[b];
-        if (blk.diagonal) continue;
-        if (blk.n_couple > 0) {
-            FusedBlock out;
-            if (pad_coupled_to_five(n, blk, out, padm[b], padc[b])) blk = out;
-            continue;
-        }
-        int32_t pt[SV_MAX_TARGETS];
-        int32_t t[SV_MAX_TARGETS];
-        for (int a = 0; a < blk.k; ++a) t[a] = blk.targets[a];
-        if (pad_to_five(n, blk.k, 0, t, blk.m, pt, padm[b])) {
-            blk.k = 5;
-            for (int a = 0; a < 5; ++a) blk.targets[a] = pt[a];
-            blk.m = padm[b].data();
-        }
+    out.b = blk;
+    if (blk.diagonal) return;
+    if (blk.n_couple > 0) {
+        FusedBlock padded;
+        if (pad_coupled_to_five(n, blk, padded, out.m, out.c)) out.b = padded;
+        return;
+    }
+    int32_t pt[SV_MAX_TARGETS];
+    int32_t t[SV_MAX_TARGETS];
+    for (int a = 0; a < blk.k; ++a) t[a] = blk.targets[a];
+    if (pad_to_five(n, blk.k, 0, t, blk.m, pt, out.m)) {
+        out.b.k = 5;
+        for (int a = 0; a < 5; ++a) out.b.targets[a] = pt[a];
+        out.b.m = out.m.data();
     }
 }
 
@@ -824,51 +824,92 @@ void launch_block(sv_handle_s* h, const sv_state_s* s, const FusedBlock& b, cons
         launch_apply(h, s->dt, s->d, dm, d);
 }
 
+// The device work of a run of blocks: sweeps of several blocks, and blocks on
+// their own (a handle with a forced tile variant takes every block so).
+struct ProgramStep {
+    SweepStep sweep;
+    LoneBlock lone;
+    GateDesc desc;
+    size_t bytes = 0;  // of its device buffer, a multiple of 256
+};
+
+void make_steps(const sv_state_s* s, const sv_fused_s* f, int first, int end, std::vector<ProgramStep>& out)
+{
+    std::vector<SweepStep> plan;
+    if (s->h->tile_mode == SV_TILE_AUTO) {
+        plan = plan_sweeps(s->dt, s->n, s->h->cu_count, f->blocks, first, end);
+    } else {
+        for (int b = first; b < end; ++b) {
+            SweepStep one;
+            one.blocks = {b};
+            plan.push_back(one);
+        }
+    }
+    out.resize(plan.size());
+    for (size_t i = 0; i < plan.size(); ++i) {
+        ProgramStep& p = out[i];
+        p.sweep = std::move(plan[i]);
+        if (p.sweep.multi) {
+            for (int b : p.sweep.blocks)
+                (void)make_desc(s->n, f->blocks[b].targets, f->blocks[b].k, nullptr, nullptr, 0);
+            p.bytes = sweep_bytes(s->dt, p.sweep, f->blocks);
+        } else {
+            make_lone(s->n, f->blocks[p.sweep.blocks[0]], p.lone);
+            p.desc = make_desc(s->n, p.lone.b.targets, p.lone.b.k, nullptr, nullptr, 0);
+            p.bytes = block_bytes(s, p.lone.b);
+        }
+        p.bytes = (p.bytes + 255) & ~size_t(255);
+    }
+}
+
+void pack_step(const sv_state_s* s, const sv_fused_s* f, const ProgramStep& p, void* dst)
+{
+    if (p.sweep.multi)
+        pack_sweep(s->dt, p.sweep, f->blocks, dst);
+    else
+        pack_block(s, p.lone.b, dst);
+}
+
+void launch_step(sv_handle_s* h, const sv_state_s* s, const ProgramStep& p, const void* buffer)
+{
+    if (p.sweep.multi)
+        launch_sweep(h, s->dt, s->d, p.sweep, buffer);
+    else
+        launch_block(h, s, p.lone.b, buffer, p.desc);
+}
+
 void apply_fused_blocks(sv_state_s* s, sv_fused_s* f, int first, int count)
 {
     check_state(s);
     SV_CHECK(f != nullptr, "fused gates are NULL");
     SV_CHECK(first >= 0 && count >= 0 && first <= f->n_blocks && count <= f->n_blocks - first,
              "block range out of bounds");
-    const int end = first + count;
-    std::vector<GateDesc> descs(f->n_blocks);
-    std::vector<std::vector<double>> padm, padc;
-    std::vector<FusedBlock> eff;
-    effective_blocks(s->n, f, first, end, eff, padm, padc);
-    for (int b = first; b < end; ++b) {
-        const FusedBlock& blk = eff[b];
-        descs[b] = make_desc(s->n, blk.targets, blk.k, nullptr, nullptr, 0);
-    }
-    {
-        // stage in segment-sized batches: one copy per batch of blocks
-        const size_t seg = kMatRingBytes / kMatRingSegments;
-        int b = first;
-        while (b < end) {
-            std::vector<size_t> offs;
-            size_t bytes = 0;
-            int e = b;
-            while (e < end) {
-                const size_t mb = (block_bytes(s, eff[e]) + 255) & ~size_t(255);
-                if (bytes + mb > seg) break;
-                offs.push_back(bytes);
-                bytes += mb;
-                ++e;
-            }
-            if (e == b) {
-                // one block larger than a ring segment: stage it on its own
-                const size_t mb = block_bytes(s, eff[b]);
-                std::vector<char> one(mb);
-                pack_block(s, eff[b], one.data());
-                launch_block(s->h, s, eff[b], stage_matrix(s->h, one.data(), mb), descs[b]);
-                ++b;
-                continue;
-            }
-            std::vector<char> tmp(bytes);
-            for (int j = b; j < e; ++j) pack_block(s, eff[j], tmp.data() + offs[j - b]);
-            const char* dm = static_cast<const char*>(stage_matrix(s->h, tmp.data(), bytes));
-            for (int j = b; j < e; ++j) launch_block(s->h, s, eff[j], dm + offs[j - b], descs[j]);
-            b = e;
+    std::vector<ProgramStep> steps;
+    make_steps(s, f, first, first + count, steps);
+    // staged in segment-sized batches: one copy per batch of steps
+    const size_t seg = kMatRingBytes / kMatRingSegments;
+    size_t i = 0;
+    while (i < steps.size()) {
+        size_t bytes = 0, e = i;
+        while (e < steps.size() && bytes + steps[e].bytes <= seg) bytes += steps[e++].bytes;
+        if (e == i) {
+            // one step larger than a ring segment: staged on its own
+            bytes = steps[i].bytes;
+            ++e;
         }
+        std::vector<char> tmp(bytes);
+        size_t at = 0;
+        for (size_t j = i; j < e; ++j) {
+            pack_step(s, f, steps[j], tmp.data() + at);
+            at += steps[j].bytes;
+        }
+        const char* dm = static_cast<const char*>(stage_matrix(s->h, tmp.data(), bytes));
+        at = 0;
+        for (size_t j = i; j < e; ++j) {
+            launch_step(s->h, s, steps[j], dm + at);
+            at += steps[j].bytes;
+        }
+        i = e;
     }
 }
 
@@ -906,20 +947,16 @@ sv_status_t sv_graph_create(sv_state_t s, sv_fused_t f, sv_graph_t* out)
         check_state(s);
         SV_CHECK(f != nullptr, "fused gates are NULL");
         sv_handle_s* h = s->h;
-        std::vector<GateDesc> descs(f->n_blocks);
-        std::vector<size_t> offs(f->n_blocks);
-        std::vector<std::vector<double>> padm, padc;
-        std::vector<FusedBlock> eff;
-        effective_blocks(s->n, f, 0, f->n_blocks, eff, padm, padc);
+        std::vector<ProgramStep> steps;
+        make_steps(s, f, 0, f->n_blocks, steps);
+        std::vector<size_t> offs(steps.size());
         size_t bytes = 0;
-        for (int b = 0; b < f->n_blocks; ++b) {
-            const FusedBlock& blk = eff[b];
-            descs[b] = make_desc(s->n, blk.targets, blk.k, nullptr, nullptr, 0);
-            offs[b] = bytes;
-            bytes += (block_bytes(s, blk) + 255) & ~size_t(255);
+        for (size_t i = 0; i < steps.size(); ++i) {
+            offs[i] = bytes;
+            bytes += steps[i].bytes;
         }
         std::vector<char> host(bytes ? bytes : 1);
-        for (int b = 0; b < f->n_blocks; ++b) pack_block(s, eff[b], host.data() + offs[b]);
+        for (size_t i = 0; i < steps.size(); ++i) pack_step(s, f, steps[i], host.data() + offs[i]);
         auto* g = new sv_graph_s;
         g->s = s;
         hipStream_t cap = nullptr;
@@ -934,7 +971,7 @@ sv_status_t sv_graph_create(sv_state_t s, sv_fused_t f, sv_graph_t* out)
             h->stream = cap;
             SV_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeRelaxed));
             try {
-                for (int b = 0; b < f->n_blocks; ++b) launch_block(h, s, eff[b], g->mats + offs[b], descs[b]);
+                for (size_t i = 0; i < steps.size(); ++i) launch_step(h, s, steps[i], g->mats + offs[i]);
             } catch (...) {
                 hipGraph_t dropped = nullptr;
                 (void)hipStreamEndCapture(cap, &dropped);

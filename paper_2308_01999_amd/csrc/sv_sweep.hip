@@ -1,0 +1,632 @@
+// Sweeps of several fused blocks (Sec. II-B: fused gates; the state is read
+// and written once per sweep instead of once per block).
+//
+// A tile holds 2^T amplitudes: the low L index bits and T - L chosen higher
+// ones.  A run of blocks whose targets all lie among a tile's bits can be
+// applied to the tile while it sits in LDS, one after the other, so the state
+// crosses HBM once for the whole run.  A state of at most 2^T amplitudes is
+// one tile: its whole program runs in one launch of one workgroup.
+//
+// Per block, each wave gathers whole groups (the 2^k amplitudes a matrix
+// mixes) and multiplies them in the same order of operations as the
+// single-block sweeps (sv_tile.h, sv_apply.hip), so a state has the same bits
+// whichever sweep ran.
+//
+// What bounds it: a block alone is bound by HBM (the 30-qubit complex64 sweep:
+// 2.9 ms).  In a sweep of several, the matrix cores take about 1.7 ms a block
+// there, and they share their issue slots with the vector ALUs (a vector
+// instruction costs the matrix pipe 2.7 cycles with several waves on a SIMD), so the
+// kernel keeps the address work to one XOR per LDS access.  32 KiB tiles and
+// 256 threads: the runs of 128 bytes that they leave for eight free bits
+// stream at 4.6-5.4 TB/s, and three workgroups a CU overlap one's loads with
+// another's products; tiles of 64 and 128 KiB (fewer sweeps) measured slower,
+// 2.4 and 2.5 ms for two blocks on 29 qubits against 2.35.
+// Measured, before (a sweep per block) and after: 30-qubit brickwork circuit
+// of depth 20, complex64, 52 blocks in 20 sweeps, 156 -> 115 ms; 28-qubit
+// random CNOT/CP circuit, complex128, 71 -> 53 ms; 19-qubit circuit on random
+// pairs, complex128, 660 -> 392 us; 14 qubits complex64 as a recorded graph,
+// 155 -> 104 us.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstring>
+
+#include "sv_sweep.h"
+#include "sv_tile.h"
+
+namespace sv {
+namespace {
+
+using namespace tile;
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// LDS slot of tile-local amplitude a: bits 1-4 XORed with bits 6-9.  Bit 0
+// stays, so a pair (i, i + 1) keeps its order and stages as one 16-byte
+// slot without a swap.  The XOR is linear over bits, so the slot of a group's
+// amplitude r is slot(base) ^ slot(off(r)): one XOR per access with the
+// host's swizzled offset as the scalar operand.
+__host__ __device__ __forceinline__ uint32_t slot(uint32_t a) { return a ^ ((a >> 5) & 30u); }
+
+template <typename R>
+struct Amp;
+template <>
+struct Amp<float> {
+    using V = f32x2;       // one amplitude
+    using W = f32x4;       // one 16-byte access
+    static constexpr int kPerVec = 2;
+    static constexpr uint32_t kBytes = 8;
+};
+template <>
+struct Amp<double> {
+    using V = f64x2;
+    using W = f64x2;
+    static constexpr int kPerVec = 1;
+    static constexpr uint32_t kBytes = 16;
+};
+
+// Global index of tile t's first amplitude (tile order as tile_base).
+__device__ __forceinline__ uint64_t tile_origin(uint64_t t, const SweepArgs& a)
+{
+    if (a.trot > 0) t = ((t & ((uint64_t(1) << a.trot) - 1)) << (a.lg_tiles - a.trot)) | (t >> a.trot);
+    return insert_zero_bits(t << a.L, a.hi_pos, a.n_hi);
+}
+
+// Group index -> tile-local base: a zero inserted at each target position
+// (v + the bits at and above the position, which moves them up by one).
+__device__ __forceinline__ uint32_t spread(uint32_t v, const uint32_t* ins, int k)
+{
+    for (int j = 0; j < k; ++j) v += v & ins[j];
+    return v;
+}
+
+// complex64, five qubits, on v_mfma_f32_32x32x2_f32: one column tile of 32
+// groups per wave (the chain of tile_c64_k5_sweep).  in / out: LDS byte address of the
+// lane's inputs (matrix columns 2j + half) and outputs (rows 8(r/4) + 4 half +
+// r%4) before the XOR with the uniform part of the index.  SUM: Re M + Im M is
+// read too (states of fewer than 12 qubits take it as the host rounded it, as
+// k_apply_mfma_c64_k5 does), otherwise formed here.
+template <bool SUM>
+__device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f32x4* __restrict__ m, uint32_t g0, int lane)
+{
+    const int col = lane & 31, half = lane >> 5;
+    f32x4 vr[4], vi[4], vt[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        vr[q] = m[q * 64 + lane];
+        vi[q] = m[256 + q * 64 + lane];
+        if (SUM) vt[q] = m[512 + q * 64 + lane];
+    }
+    const uint32_t base = 8u * slot(spread(uint32_t(col), b.ins, 5)) ^ 8u * slot(spread(g0, b.ins, 5));
+    uint32_t in = base ^ (half ? b.off[1] : 0u), out = base ^ (half ? b.off[4] : 0u);
+    asm volatile("" : "+v"(in), "+v"(out));  // keep (base ^ half part) ^ uniform part: one XOR per access
+    f32x2 x[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x[j] = *reinterpret_cast<const f32x2*>(lds + (in ^ b.off[2 * j]));
+    f32x16 p1 = {0}, p2 = {0}, p3 = {0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const f32x4 vs = SUM ? vt[q] : vr[q] + vi[q];
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            const f32x2 xv = x[4 * q + jj];
+            p1 = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[q][jj], xv.x, p1, 0, 0, 0);
+            p2 = __builtin_amdgcn_mfma_f32_32x32x2f32(vi[q][jj], xv.y, p2, 0, 0, 0);
+            p3 = __builtin_amdgcn_mfma_f32_32x32x2f32(vs[jj], xv.x + xv.y, p3, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        *reinterpret_cast<f32x2*>(lds + (out ^ b.off[8 * (r / 4) + (r % 4)])) =
+            f32x2{p1[r] - p2[r], p3[r] - p1[r] - p2[r]};
+}
+
+// complex64, four qubits, on v_mfma_f32_16x16x4_f32 (the chain of
+// k_tile_c64_k4), `steps` column tiles of 16 groups per wave.
+__device__ __forceinline__ void block4(char* lds, const SweepBlock& b, const f32x4* __restrict__ m, uint32_t g0, int steps,
+                                       int lane)
+{
+    const int col = lane & 15, q = lane >> 4;
+    const f32x4 ar = m[lane], ai = m[64 + lane], as = m[128 + lane];
+    const uint32_t lin = ((q & 1) ? b.off[1] : 0u) ^ ((q & 2) ? b.off[2] : 0u);
+    const uint32_t lout = ((q & 1) ? b.off[4] : 0u) ^ ((q & 2) ? b.off[8] : 0u);
+    for (int c = 0; c < steps; ++c) {
+        const uint32_t base = 8u * slot(spread(g0 + uint32_t(c * 16 + col), b.ins, 4));
+        f32x2 x[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) x[s] = *reinterpret_cast<const f32x2*>(lds + (base ^ lin ^ b.off[4 * s]));
+        f32x4 p1 = {0}, p2 = {0}, p3 = {0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            p1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[s], x[s].x, p1, 0, 0, 0);
+            p2 = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[s], x[s].y, p2, 0, 0, 0);
+            p3 = __builtin_amdgcn_mfma_f32_16x16x4f32(as[s], x[s].x + x[s].y, p3, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<f32x2*>(lds + (base ^ lout ^ b.off[r])) = f32x2{p1[r] - p2[r], p3[r] - p1[r] - p2[r]};
+    }
+}
+
+// complex128, five qubits, on v_mfma_f64_16x16x4_f64: one column tile of 16
+// groups per wave, two row tiles (the chain of k_tile_c128_k5).  The lane's
+// inputs are matrix columns 4s + q, its outputs rows 16 rt + 4v + q.
+template <bool SUM>
+__device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f64x2* __restrict__ m, uint32_t g0, int lane)
+{
+    const int col = lane & 15, q = lane >> 4;
+    const uint32_t base = 16u * slot(spread(uint32_t(col), b.ins, 5)) ^ 16u * slot(spread(g0, b.ins, 5));
+    uint32_t at = base ^ ((q & 1) ? b.off[1] : 0u) ^ ((q & 2) ? b.off[2] : 0u);
+    asm volatile("" : "+v"(at));
+    f64x2 x[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) x[s] = *reinterpret_cast<const f64x2*>(lds + (at ^ b.off[4 * s]));
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+        f64x2 vr[4], vi[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            vr[h] = m[(rt * 4 + h) * 64 + lane];
+            vi[h] = m[(8 + rt * 4 + h) * 64 + lane];
+        }
+        f64x4 p1 = {0}, p2 = {0}, p3 = {0};
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const double a0 = vr[s >> 1][s & 1], a1 = vi[s >> 1][s & 1];
+            p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, x[s].x, p1, 0, 0, 0);
+            p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, x[s].y, p2, 0, 0, 0);
+            p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0 + a1, x[s].x + x[s].y, p3, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            *reinterpret_cast<f64x2*>(lds + (at ^ b.off[16 * rt + 4 * v])) =
+                f64x2{p1[v] - p2[v], p3[v] - p1[v] - p2[v]};
+    }
+}
+
+// k <= 3 (complex64) or k <= 4 (complex128) on the vector units, one group
+// per thread and step, in the order of k_apply_dense.
+template <typename R, int K>
+__device__ __forceinline__ void block_small(char* lds, const SweepBlock& b, const typename Amp<R>::V* __restrict__ m,
+                                            uint32_t groups, int nt)
+{
+    using V = typename Amp<R>::V;
+    constexpr int D = 1 << K;
+    for (uint32_t g = threadIdx.x; g < groups; g += uint32_t(nt)) {
+        asm volatile("" ::: "memory");  // the matrix stays out of the registers
+        const uint32_t base = Amp<R>::kBytes * slot(spread(g, b.ins, K));
+        V v[D];
+#pragma unroll
+        for (int c = 0; c < D; ++c) v[c] = *reinterpret_cast<const V*>(lds + (base ^ b.off[c]));
+#pragma unroll
+        for (int r = 0; r < D; ++r) {
+            R re = 0, im = 0;
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                const V e = m[r * D + c];
+                re = fma(e.x, v[c].x, re);
+                re = fma(-e.y, v[c].y, re);
+                im = fma(e.x, v[c].y, im);
+                im = fma(e.y, v[c].x, im);
+            }
+            *reinterpret_cast<V*>(lds + (base ^ b.off[r])) = V{re, im};
+        }
+    }
+}
+
+// complex128, five qubits, states of fewer than 11 qubits: on the vector units
+// in the order of k_apply_dense, one group per lane and 8 rows per wave (64
+// groups, four waves).  Every wave reads its groups' inputs before any writes.
+__device__ __forceinline__ void block5_rows(char* lds, const SweepBlock& b, const f64x2* __restrict__ m, int wave, int lane)
+{
+    const uint32_t base = 16u * slot(spread(uint32_t(lane), b.ins, 5));
+    f64x2 v[32], y[8];
+#pragma unroll
+    for (int c = 0; c < 32; ++c) v[c] = *reinterpret_cast<const f64x2*>(lds + (base ^ b.off[c]));
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const f64x2* row = m + (wave * 8 + r) * 32;
+        double re = 0, im = 0;
+#pragma unroll
+        for (int c = 0; c < 32; ++c) {
+            re = fma(row[c].x, v[c].x, re);
+            re = fma(-row[c].y, v[c].y, re);
+            im = fma(row[c].x, v[c].y, im);
+            im = fma(row[c].y, v[c].x, im);
+        }
+        y[r] = f64x2{re, im};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 8; ++r) *reinterpret_cast<f64x2*>(lds + (base ^ b.off[wave * 8 + r])) = y[r];
+}
+
+// NT threads on tiles of 2^T amplitudes; SMALL: the state is one tile (2^n <=
+// 2^T amplitudes, the rest of the tile zeros that no one stores), its blocks
+// of fewer than five qubits on the vector units.
+template <typename R, int T, int NT, bool SMALL>
+__global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
+                                               const char* __restrict__ mats, SweepArgs a)
+{
+    using A = Amp<R>;
+    using W = typename A::W;
+    constexpr int NV = (1 << T) / A::kPerVec / NT;     // 16-byte vectors per thread
+    constexpr int kCols = sizeof(R) == 4 ? 32 : 16;    // groups per wave
+    static_assert((1 << (T - 5)) == kCols * (NT / 64), "one column tile per wave");
+    __shared__ __align__(16) char lds[A::kBytes << T];
+    const uint64_t t0 = uint64_t(blockIdx.x) * a.tiles_per_wg;
+    if (t0 >= a.n_tiles) return;
+    const uint64_t t1 = (a.n_tiles - t0 < a.tiles_per_wg) ? a.n_tiles : t0 + a.tiles_per_wg;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // tile-local amplitude of the thread's vector u: (u NT + tid) amplitudes
+    // per vector; the lane's part of its address is a 32-bit offset (the
+    // lanes' index bits at or above L sit at the lowest of hi_pos), the rest
+    // is uniform
+    constexpr int kLaneBits = 6 + (A::kPerVec == 2 ? 1 : 0);
+    const uint32_t li = uint32_t(lane) * A::kPerVec;
+    uint32_t loff = li;
+    if (a.L < kLaneBits)
+        loff = (li & ((1u << a.L) - 1)) | uint32_t(deposit_bits(li >> a.L, a.hi_pos, kLaneBits - a.L));
+    loff *= A::kBytes;
+    uint64_t roff[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        const uint32_t i = uint32_t(u * NT + wave * 64) * A::kPerVec;
+        roff[u] = A::kBytes * (SMALL ? uint64_t(i)
+                                     : deposit_bits(i >> a.L, a.hi_pos, a.n_hi) + uint64_t(i & ((1u << a.L) - 1)));
+    }
+    char* base = psi + A::kBytes * tile_origin(t0, a);
+    W buf[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        if (SMALL && uint64_t(u * NT + tid) * A::kPerVec >= a.amps)
+            buf[u] = W{};
+        else
+            buf[u] = __builtin_nontemporal_load(reinterpret_cast<const W*>(base + roff[u] + loff));
+    }
+    for (uint64_t t = t0; t < t1; ++t) {
+#pragma unroll
+        for (int u = 0; u < NV; ++u)
+            *reinterpret_cast<W*>(lds + A::kBytes * slot(uint32_t(u * NT + tid) * A::kPerVec)) = buf[u];
+        __syncthreads();
+        char* nbase = base;
+        if (!SMALL && t + 1 < t1) {
+            nbase = psi + A::kBytes * tile_origin(t + 1, a);
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+                buf[u] = __builtin_nontemporal_load(reinterpret_cast<const W*>(nbase + roff[u] + loff));
+        }
+        for (int i = 0; i < a.n_blocks; ++i) {
+            const SweepBlock& b = blocks[i];
+            const char* m = mats + b.mat;
+            if (!SMALL || (b.k == 5 && !b.rows)) {
+                block5<SMALL>(lds, b, reinterpret_cast<const W*>(m), uint32_t(wave * kCols), lane);
+            } else if constexpr (SMALL) {
+                const auto* mv = reinterpret_cast<const typename A::V*>(m);
+                if constexpr (sizeof(R) == 8 && T == 11)
+                    if (b.k == 5) block5_rows(lds, b, mv, wave, lane);
+                if (b.k == 1) block_small<R, 1>(lds, b, mv, 1u << (T - 1), NT);
+                if (b.k == 2) block_small<R, 2>(lds, b, mv, 1u << (T - 2), NT);
+                if (b.k == 3) block_small<R, 3>(lds, b, mv, 1u << (T - 3), NT);
+                if (b.k == 4) {
+                    if constexpr (sizeof(R) == 8)
+                        block_small<R, 4>(lds, b, mv, 1u << (T - 4), NT);
+                    else
+                        block4(lds, b, reinterpret_cast<const W*>(m), uint32_t(wave * 64), 4, lane);
+                }
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            if (SMALL && uint64_t(u * NT + tid) * A::kPerVec >= a.amps) continue;
+            __builtin_nontemporal_store(
+                *reinterpret_cast<const W*>(lds + A::kBytes * slot(uint32_t(u * NT + tid) * A::kPerVec)),
+                reinterpret_cast<W*>(base + roff[u] + loff));
+        }
+        base = nbase;
+        __syncthreads();
+    }
+}
+
+constexpr int tile_bits(sv_dtype_t dt) { return dt == SV_C64 ? 12 : 11; }  // 32 KiB
+
+// Shortest runs of a tile: 128 bytes, the line of the L2.
+constexpr int min_run_bits(sv_dtype_t dt) { return dt == SV_C64 ? 4 : 3; }
+
+// Largest state that is swept as one tile, its whole program in one launch.
+constexpr int kOneTileQubitsC64 = 13, kOneTileQubitsC128 = 12;
+
+// Smallest state whose blocks may pass blocks on other qubits on their way
+// into a sweep (below, a program's blocks keep their order and its amplitudes
+// their bits).
+constexpr int kReorderQubits = 22;
+constexpr int kReorderWindow = 96;
+
+// Most blocks of one sweep: its descriptors and matrices fit a segment of the
+// handle's matrix ring (16 KiB a block at most, 1 MiB).
+constexpr size_t kMaxSweepBlocks = 48;
+
+// Largest state of multi-block sweeps: the lanes' part of an address (three
+// index bits below the fifth highest one) fits 32 bits.
+constexpr int kMaxSweepQubitsC64 = 34, kMaxSweepQubitsC128 = 33;
+
+uint64_t qubit_mask(const FusedBlock& b)
+{
+    uint64_t m = 0;
+    for (int a = 0; a < b.k; ++a) m |= uint64_t(1) << b.targets[a];
+    return m;
+}
+
+// Fills st's tile for the qubit set `on`: the runs as long as the set allows
+// (bits L.. join the low bits while the tile has room).
+void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, SweepStep& st)
+{
+    const int T = st.tile_bits;
+    SweepArgs& a = st.args;
+    a = SweepArgs{};
+    a.n_blocks = int(st.blocks.size());
+    a.amps = uint64_t(1) << n;
+    if (n <= T) {
+        a.n_tiles = a.tiles_per_wg = 1;
+        a.L = T;
+        return;
+    }
+    int L = min_run_bits(dt);
+    while (L < T && __builtin_popcountll(on >> L) + L < T) ++L;
+    a.L = L;
+    for (int q = L; q < n; ++q)
+        if ((on >> q) & 1) a.hi_pos[a.n_hi++] = q;
+    a.lg_tiles = n - T;
+    a.n_tiles = uint64_t(1) << a.lg_tiles;
+    uint64_t per = a.n_tiles / (uint64_t(cu_count) * SV_TILE_WGS_PER_CU);
+    per = std::max<uint64_t>(1, std::min<uint64_t>(per, SV_TILES_PER_WG_MAX_K5));
+    a.tiles_per_wg = per;
+    if ((per & (per - 1)) == 0)
+        while ((uint64_t(1) << a.trot) < per) ++a.trot;
+}
+
+}  // namespace
+
+std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const FusedBlock* blocks, int first, int end)
+{
+    std::vector<SweepStep> steps;
+    const bool one_tile = n <= (dt == SV_C64 ? kOneTileQubitsC64 : kOneTileQubitsC128);
+    const int T = one_tile ? std::max(n, tile_bits(dt)) : tile_bits(dt);
+    const int lo = min_run_bits(dt);
+    auto eligible = [&](const FusedBlock& b) {
+        if (b.diagonal || b.n_couple > 0 || b.k > 5) return false;
+        if (n > (dt == SV_C64 ? kMaxSweepQubitsC64 : kMaxSweepQubitsC128)) return false;
+        // larger states: blocks on 2-4 qubits are swept as five-qubit ones
+        // where their own sweep is (pad_to_five: from 14 qubits on, with
+        // enough qubits below or above theirs), single-qubit ones on their own
+        if (one_tile || b.k == 5) return true;
+        const uint64_t on = qubit_mask(b);
+        const int outside = __builtin_ctzll(on) + n - 1 - (63 - __builtin_clzll(on));
+        return b.k >= 2 && n >= 14 && outside >= 5 - b.k;
+    };
+    auto fits = [&](uint64_t on) { return one_tile || __builtin_popcountll(on >> lo) <= T - lo; };
+    auto add = [&](std::vector<int>&& take, uint64_t on) {
+        SweepStep st;
+        st.multi = take.size() > 1;
+        st.blocks = std::move(take);
+        if (st.multi) {
+            st.tile_bits = T;
+            fill_geometry(dt, n, cu_count, on, st);
+        }
+        steps.push_back(std::move(st));
+    };
+    std::vector<int> rest;
+    for (int i = first; i < end; ++i) rest.push_back(i);
+    size_t at = 0;
+    while (at < rest.size()) {
+        const int b0 = rest[at];
+        if (!eligible(blocks[b0])) {
+            add({b0}, 0);
+            ++at;
+            continue;
+        }
+        if (n < kReorderQubits) {
+            std::vector<int> take;
+            uint64_t on = 0;
+            while (at < rest.size() && take.size() < kMaxSweepBlocks && eligible(blocks[rest[at]]) && fits(on | qubit_mask(blocks[rest[at]]))) {
+                on |= qubit_mask(blocks[rest[at]]);
+                take.push_back(rest[at++]);
+            }
+            add(std::move(take), on);
+            continue;
+        }
+        // a block may join a sweep ahead of blocks left behind that share no
+        // qubit with it (they commute); of the first ready seeds, the one
+        // whose sweep takes most blocks
+        const size_t hi = std::min(rest.size(), at + kReorderWindow);
+        std::vector<int> best;
+        uint64_t best_on = 0;
+        int seeds = 0;
+        uint64_t before = 0;
+        for (size_t s = at; s < hi && seeds < 8; ++s) {
+            const uint64_t qs = qubit_mask(blocks[rest[s]]);
+            const bool ready = !(qs & before) && eligible(blocks[rest[s]]);
+            before |= qs;
+            if (!ready) continue;
+            ++seeds;
+            std::vector<int> take{rest[s]};
+            uint64_t on = qs;
+            std::vector<char> in(hi - at, 0);
+            in[s - at] = 1;
+            while (take.size() < kMaxSweepBlocks) {
+                int pick = -1, cost = 65;
+                uint64_t blocked = 0;
+                for (size_t j = at; j < hi; ++j) {
+                    if (in[j - at]) continue;
+                    const uint64_t q = qubit_mask(blocks[rest[j]]);
+                    if (!(q & blocked) && eligible(blocks[rest[j]]) && fits(on | q)) {
+                        const int c = __builtin_popcountll((on | q) >> lo);
+                        if (c < cost) {
+                            cost = c;
+                            pick = int(j);
+                        }
+                    }
+                    blocked |= q;
+                }
+                if (pick < 0) break;
+                in[pick - at] = 1;
+                on |= qubit_mask(blocks[rest[pick]]);
+                take.push_back(rest[pick]);
+            }
+            if (take.size() > best.size()) {
+                best = take;
+                best_on = on;
+            }
+        }
+        // program order inside the sweep
+        std::sort(best.begin(), best.end());
+        size_t w = hi;
+        for (size_t j = hi; j-- > at;)
+            if (!std::binary_search(best.begin(), best.end(), rest[j])) rest[--w] = rest[j];
+        at = w;
+        add(std::move(best), best_on);
+    }
+    return steps;
+}
+
+namespace {
+
+// Bytes of a block's packed matrix in a sweep.
+size_t sweep_matrix_bytes(sv_dtype_t dt, int k)
+{
+    if (k == 5) return dt == SV_C64 ? 3 * 1024 * sizeof(float) : 2 * 1024 * sizeof(double);
+    if (k == 4 && dt == SV_C64) return 3 * 256 * sizeof(float);
+    return (size_t(dt == SV_C64 ? 8 : 16)) << (2 * k);
+}
+
+int swept_qubits(const SweepStep& st, int n_state_tile, const FusedBlock& b)
+{
+    return st.args.n_tiles == 1 && st.args.L == n_state_tile ? b.k : 5;
+}
+
+// Packed A operands of the five-qubit sweep of M (x) I (M on the block's k
+// qubits, the padding qubits the high matrix bits).  complex64: float4
+// [part][q][lane] of A[i][2(4q + j) + half], lane = i + 32 half; complex128:
+// double2 [part][rt 4 + s/2][lane] of A[16 rt + i][4s + q], lane = i + 16 q.
+// Parts Re M, Im M and, for complex64, Re M + Im M (of the entries as given for
+// states of fewer than 12 qubits, else of the rounded ones, as their
+// single-block kernels take it).
+template <typename R>
+void pack5(const FusedBlock& b, int n, R* o)
+{
+    const int d = 1 << b.k;
+    for (int i = 0; i < 32; ++i)
+        for (int c = 0; c < 32; ++c) {
+            double re = 0.0, im = 0.0;
+            if ((i >> b.k) == (c >> b.k)) {
+                const double* e = b.m + 2 * (size_t(i & (d - 1)) * d + (c & (d - 1)));
+                re = e[0];
+                im = e[1];
+            }
+            size_t at;
+            if (sizeof(R) == 4)
+                at = size_t(((c >> 3) * 64 + i + 32 * (c & 1)) * 4 + ((c >> 1) & 3));
+            else
+                at = size_t((((i >> 4) * 4 + (c >> 3)) * 64 + (i & 15) + 16 * (c & 3)) * 2 + ((c >> 2) & 1));
+            o[at] = R(re);
+            o[1024 + at] = R(im);
+            if (sizeof(R) == 4) o[2048 + at] = n < 12 ? R(re + im) : R(re) + R(im);
+        }
+}
+
+}  // namespace
+
+size_t sweep_bytes(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks)
+{
+    size_t bytes = sizeof(SweepBlock) * st.blocks.size();
+    bytes = (bytes + 255) & ~size_t(255);
+    for (int i : st.blocks) bytes += (sweep_matrix_bytes(dt, swept_qubits(st, st.tile_bits, blocks[i])) + 255) & ~size_t(255);
+    return bytes;
+}
+
+void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, void* dst)
+{
+    char* out = static_cast<char*>(dst);
+    auto* desc = static_cast<SweepBlock*>(dst);
+    size_t mat = (sizeof(SweepBlock) * st.blocks.size() + 255) & ~size_t(255);
+    const int L = st.args.L, T = st.tile_bits;
+    for (size_t j = 0; j < st.blocks.size(); ++j) {
+        const FusedBlock& b = blocks[st.blocks[j]];
+        SweepBlock s{};
+        s.k = swept_qubits(st, T, b);
+        // tile-local positions of the targets, then of the padding qubits
+        // (the lowest positions that are free)
+        int pos[5] = {};
+        uint32_t used = 0;
+        for (int a = 0; a < b.k; ++a) {
+            int p = b.targets[a];
+            if (p >= L) {
+                int r = 0;
+                while (st.args.hi_pos[r] != p) ++r;
+                p = L + r;
+            }
+            pos[a] = p;
+            used |= 1u << p;
+        }
+        for (int a = b.k, p = 0; a < s.k; ++p)
+            if (!((used >> p) & 1)) {
+                pos[a++] = p;
+                used |= 1u << p;
+            }
+        int w = 0;
+        for (int p = 0; p < T; ++p)
+            if ((used >> p) & 1) s.ins[w++] = ~((1u << p) - 1u);
+        for (int r = 0; r < (1 << s.k); ++r) {
+            uint32_t o = 0;
+            for (int a = 0; a < s.k; ++a)
+                if ((r >> a) & 1) o |= 1u << pos[a];
+            s.off[r] = (dt == SV_C64 ? 8u : 16u) * slot(o);
+        }
+        s.mat = uint32_t(mat);
+        const int n = 63 - __builtin_clzll(st.args.amps);
+        s.rows = s.k == 5 && dt == SV_C128 && n < 11;
+        desc[j] = s;
+        if (s.k == 5 && dt == SV_C64) {
+            pack5(b, n, reinterpret_cast<float*>(out + mat));
+        } else if (s.k == 5 && !s.rows) {
+            pack5(b, n, reinterpret_cast<double*>(out + mat));
+        } else if (s.rows) {
+            std::memcpy(out + mat, b.m, 1024 * 2 * sizeof(double));
+        } else {
+            pack_matrix(dt, 12, s.k, 0, b.m, 0, out + mat);
+        }
+        mat += (sweep_matrix_bytes(dt, s.k) + 255) & ~size_t(255);
+    }
+}
+
+void launch_sweep(sv_handle_s* h, sv_dtype_t dt, void* psi_v, const SweepStep& st, const void* buffer)
+{
+    char* psi = static_cast<char*>(psi_v);
+    const auto* blocks = static_cast<const SweepBlock*>(buffer);
+    const auto* mats = static_cast<const char*>(buffer);
+    const SweepArgs& a = st.args;
+    const dim3 grid{unsigned((a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg)};
+    const bool one = a.n_tiles == 1;
+    if (dt == SV_C64) {
+        if (one && st.tile_bits == 13)
+            hipLaunchKernelGGL((k_sweep<float, 13, 512, true>), grid, dim3(512), 0, h->stream, psi, blocks, mats, a);
+        else if (one)
+            hipLaunchKernelGGL((k_sweep<float, 12, 256, true>), grid, dim3(256), 0, h->stream, psi, blocks, mats, a);
+        else
+            hipLaunchKernelGGL((k_sweep<float, 12, 256, false>), grid, dim3(256), 0, h->stream, psi, blocks, mats, a);
+    } else {
+        if (one && st.tile_bits == 12)
+            hipLaunchKernelGGL((k_sweep<double, 12, 512, true>), grid, dim3(512), 0, h->stream, psi, blocks, mats, a);
+        else if (one)
+            hipLaunchKernelGGL((k_sweep<double, 11, 256, true>), grid, dim3(256), 0, h->stream, psi, blocks, mats, a);
+        else
+            hipLaunchKernelGGL((k_sweep<double, 11, 256, false>), grid, dim3(256), 0, h->stream, psi, blocks, mats, a);
+    }
+    SV_HIP(hipGetLastError());
+}
+
+}  // namespace sv
