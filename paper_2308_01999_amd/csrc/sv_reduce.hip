@@ -5,12 +5,13 @@
 // scale, collapse and Pauli rotation.
 //
 // Every reduction accumulates in FP64 in an order that depends only on n
-// (never on the grid size or on other work on the device): a fixed partition
-// into blocks, a fixed per-thread order inside a block, a fixed LDS tree, and
+// (and, for Pauli strings with X or Y, on the strings of the call; never on
+// the grid size or on other work on the device): a fixed partition into blocks, a fixed per-thread order inside a block, a fixed LDS tree, and
 // a fixed final pass.  Results are therefore bitwise reproducible.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <functional>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -350,6 +351,146 @@ __global__ __launch_bounds__(kThreads) void k_expect_xy_group(const typename Cx<
     expect_xy_body<R>(psi, args[blockIdx.y], part + blockIdx.y * stride);
 }
 
+// Sweeps of D linearly independent X/Y masks x_0 .. x_{D-1} at once.  Their span
+// splits the indices into cosets of 2^D; a thread reads a coset's amplitudes
+// a[s] = psi[c ^ x(s)], x(s) the XOR of the x_b with bit b of s set, and has
+// both members of every pair of every mask, so the state is read once for D
+// masks instead of once for each.  c runs over the indices with zeros at the
+// masks' D pivots (their highest bits after elimination: lanes stay on
+// neighbouring amplitudes unless the masks have low bits only).
+// A pair of mask b is (s, s + 2^b), bit b of s clear, i = c ^ x(s): with w = conj(psi_j)
+// psi_i it adds 2 Re(w i^ny) (-1)^popcount(i & z) to a term, and
+// popcount(i & z) = popcount(c & z) + popcount(x(s) & z): the second part is a
+// bit of the term's `sig`, the same for all cosets.  FP64, per-thread order
+// fixed by n and the sweep's masks.
+// Bound by HBM: 16 random strings on 26 qubits complex64 take four sweeps of
+// four masks, 82 us each (6.5 TB/s), 0.33 ms, where 16 sweeps of one mask took 2.8
+// ms (175 us each: 32 predicated terms an item on the vector units).
+constexpr int kJointMax = 5;         // masks of one sweep
+constexpr int kJointTerms = 2;       // terms of one mask in it
+
+struct JointTerm {
+    uint64_t z;
+    uint32_t sig;   // bit s: parity of x(s) & z
+    int32_t ny;
+};
+
+struct JointArgs {
+    uint64_t per;                    // cosets per block
+    uint64_t x[kJointMax];
+    int32_t pivot[kJointMax];        // ascending
+    int32_t count[kJointMax];        // terms of mask b
+    int32_t row[kJointMax];          // result row of its first term
+    int32_t n_terms;
+    int32_t want_norm;
+    JointTerm term[kJointMax][kJointTerms];
+};
+
+template <typename R, int D>
+__global__ __launch_bounds__(kThreads, 2) void k_expect_joint(const typename Cx<R>::T* __restrict__ psi,
+                                                              const JointArgs* __restrict__ args,
+                                                              double* __restrict__ part, uint64_t stride)
+{
+    using T2 = typename Cx<R>::T;
+    constexpr int S = 1 << D;
+    __shared__ double wsum[kJointMax * kJointTerms + 1][kThreads / 64];
+    const JointArgs& a = args[blockIdx.y];
+    part += blockIdx.y * stride;
+    const uint64_t first = uint64_t(blockIdx.x) * a.per;
+    double acc[D][kJointTerms], norm = 0.0;
+#pragma unroll
+    for (int b = 0; b < D; ++b)
+#pragma unroll
+        for (int t = 0; t < kJointTerms; ++t) acc[b][t] = 0.0;
+    for (uint64_t it = threadIdx.x; it < a.per; it += kThreads) {
+        const uint64_t c = insert_bits0(first + it, a.pivot, D);
+        T2 v[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            uint64_t xs = 0;
+#pragma unroll
+            for (int b = 0; b < D; ++b)
+                if ((s >> b) & 1) xs ^= a.x[b];
+            v[s] = psi[c ^ xs];
+        }
+        if (a.want_norm) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) norm = __dadd_rn(norm, prob(v[s]));
+        }
+#pragma unroll
+        for (int b = 0; b < D; ++b) {
+#pragma unroll
+            for (int t = 0; t < kJointTerms; ++t) {
+                if (t >= a.count[b]) continue;
+                const JointTerm& tm = a.term[b][t];
+                const uint32_t sig = tm.sig;
+                double sum = 0.0;
+                // sign of a pair as a uniform +-1.0
+                auto sign = [&](int s) {
+                    return __longlong_as_double((long long)(0x3ff0000000000000ull | (uint64_t((sig >> s) & 1u) << 63)));
+                };
+                if (tm.ny & 1) {
+#pragma unroll
+                    for (int s = 0; s < S; ++s) {
+                        if ((s >> b) & 1) continue;
+                        const T2 i = v[s], j = v[s | (1 << b)];
+                        const double w = fma(double(j.x), double(i.y), -__dmul_rn(double(j.y), double(i.x)));
+                        sum = fma(w, sign(s), sum);
+                    }
+                } else {
+#pragma unroll
+                    for (int s = 0; s < S; ++s) {
+                        if ((s >> b) & 1) continue;
+                        const T2 i = v[s], j = v[s | (1 << b)];
+                        const double w = fma(double(j.x), double(i.x), __dmul_rn(double(j.y), double(i.y)));
+                        sum = fma(w, sign(s), sum);
+                    }
+                }
+                acc[b][t] = __dadd_rn(acc[b][t], (__popcll(c & tm.z) & 1) ? -sum : sum);
+            }
+        }
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int b = 0; b < D; ++b)
+#pragma unroll
+        for (int t = 0; t < kJointTerms; ++t) {
+            if (t >= a.count[b]) continue;
+            const int m = a.term[b][t].ny & 3;
+            const double w = wave_sum((m == 1 || m == 2) ? -2.0 * acc[b][t] : 2.0 * acc[b][t]);
+            if (lane == 0) wsum[a.row[b] + t][wave] = w;
+        }
+    if (a.want_norm) norm = wave_sum(norm);
+    if (lane == 0) wsum[a.n_terms][wave] = norm;
+    __syncthreads();
+    if (int(threadIdx.x) <= a.n_terms) {
+        double sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) sum = __dadd_rn(sum, wsum[threadIdx.x][w]);
+        part[uint64_t(threadIdx.x) * gridDim.x + blockIdx.x] = sum;
+    }
+}
+
+template <typename R>
+void launch_joint(hipStream_t stream, int d, dim3 grid, const void* psi_v, const JointArgs* args, double* part,
+                  uint64_t stride)
+{
+    const auto* psi = static_cast<const typename Cx<R>::T*>(psi_v);
+#define SV_JOINT(D)                                                                                                \
+    case D:                                                                                                        \
+        hipLaunchKernelGGL((k_expect_joint<R, D>), grid, dim3(kThreads), 0, stream, psi, args, part, stride); \
+        break;
+    switch (d) {
+        SV_JOINT(1)
+        SV_JOINT(2)
+        SV_JOINT(3)
+        SV_JOINT(4)
+        SV_JOINT(5)
+    }
+#undef SV_JOINT
+    SV_HIP(hipGetLastError());
+}
+
 // out[t] = sum over blocks of part[t * nb + b], fixed order.  One block per t.
 __global__ __launch_bounds__(kThreads) void k_finish_sums(const double* __restrict__ part, uint64_t nb,
                                                          double* __restrict__ out)
@@ -363,18 +504,21 @@ __global__ __launch_bounds__(kThreads) void k_finish_sums(const double* __restri
 }
 
 // k_finish_sums for a group of sweeps: block (t, y) finishes term t of
-// sweep y (its partials at part + y * stride, nb_z blocks for the first
-// n_z sweeps, nb_xy for the others) into out[y * slot + t], in the same
-// order as k_finish_sums.
+// sweep y (its partials at part + y * stride) into out[y * slot + t], in the
+// same order as k_finish_sums.
+struct FinishArgs {
+    uint64_t nb;      // blocks of the sweep
+    int32_t n_terms;  // the norm is term n_terms
+};
+
 __global__ __launch_bounds__(kThreads) void k_finish_group(const double* __restrict__ part, uint64_t stride,
-                                                          const ExpectArgs* __restrict__ args, uint32_t n_z,
-                                                          uint64_t nb_z, uint64_t nb_xy, double* __restrict__ out,
-                                                          uint32_t slot)
+                                                          const FinishArgs* __restrict__ args,
+                                                          double* __restrict__ out, uint32_t slot)
 {
     __shared__ double lds[kThreads];
     const uint32_t y = blockIdx.y;
     if (int(blockIdx.x) > args[y].n_terms) return;
-    const uint64_t nb = y < n_z ? nb_z : nb_xy;
+    const uint64_t nb = args[y].nb;
     const double* p = part + y * stride + uint64_t(blockIdx.x) * nb;
     double acc = 0.0;
     for (uint64_t b = threadIdx.x; b < nb; b += kThreads) acc = __dadd_rn(acc, p[b]);
@@ -987,7 +1131,7 @@ void run_expect_t(sv_handle_s* h, const void* psi_v, int n, const PauliMasks* te
     using T2 = typename Cx<R>::T;
     const T2* psi = static_cast<const T2*>(psi_v);
     const uint64_t dim = uint64_t(1) << n;
-    // Sweeps: one per distinct X/Y mask and per kMaxTermsPerSweep terms.
+    // Sweeps: Z-type terms, kMaxTermsPerSweep at a time, then X/Y masks.
     // Z-type terms (x == 0) whose mask meets the bits that vary inside a
     // thread need per-item work: at most kMaxActive of them per sweep, placed
     // first; the others only flip the sign of the plain sum.
@@ -999,11 +1143,18 @@ void run_expect_t(sv_handle_s* h, const void* psi_v, int n, const PauliMasks* te
     std::vector<double> sums(n_terms, 0.0);
     double norm = -1.0;
     struct Launch {
-        std::vector<int> idx;  // term indices, active ones first
-        int n_active;
+        std::vector<int> idx;        // term indices in result order (Z-type: active ones first)
+        int n_active = 0;
+        std::vector<uint64_t> masks;  // joint sweep: its X/Y masks
+        std::vector<int> count;       // and the number of terms of each
     };
     std::vector<Launch> launches;
     const uint64_t zvary = (partition(dim).per - 1) & ~uint64_t(kThreads - 1);
+    struct Mask {
+        uint64_t x;
+        std::vector<int> idx;
+    };
+    std::vector<Mask> joint;  // masks of up to kJointTerms terms
     for (int i = 0; i < n_terms;) {
         int j = i;
         while (j < n_terms && terms[order[j]].x == terms[order[i]].x) ++j;
@@ -1018,7 +1169,10 @@ void run_expect_t(sv_handle_s* h, const void* psi_v, int n, const PauliMasks* te
                 while (ip < pas.size() && L.idx.size() < size_t(kMaxTermsPerSweep)) L.idx.push_back(pas[ip++]);
                 launches.push_back(std::move(L));
             }
+        } else if (j - i <= kJointTerms) {
+            joint.push_back({terms[order[i]].x, std::vector<int>(order.begin() + i, order.begin() + j)});
         } else {
+            // many terms on one mask: a sweep of that mask takes 32 of them
             for (int k = i; k < j; k += kMaxTermsPerSweep) {
                 Launch L;
                 for (int m = k; m < std::min(j, k + kMaxTermsPerSweep); ++m) L.idx.push_back(order[m]);
@@ -1028,13 +1182,40 @@ void run_expect_t(sv_handle_s* h, const void* psi_v, int n, const PauliMasks* te
         }
         i = j;
     }
-    // Sweeps in groups of up to kGroup, read back once per group: each
-    // sweep's finished sums go to its own slot of the results area.  A large
-    // state's sweeps are launched one by one and reuse the partials after
-    // the results area (each finish consumes them before the next sweep
-    // writes them: one stream).  A small state's group takes one launch per
-    // kind (its Z-type sweeps, which come first, then its pair sweeps) and
-    // one finish, each sweep with partials of its own.
+    // The other masks share sweeps, as evenly as the number of sweeps allows
+    // (16 masks: four sweeps of four); a mask in the span of a sweep's masks
+    // waits for a later one.
+    const size_t n_alone = launches.size();
+    while (!joint.empty()) {
+        const size_t sweeps = (joint.size() + kJointMax - 1) / kJointMax;
+        const size_t want = (joint.size() + sweeps - 1) / sweeps;
+        Launch L;
+        std::vector<uint64_t> basis;  // reduced by their highest bits
+        std::vector<Mask> later;
+        for (Mask& m : joint) {
+            uint64_t v = m.x;
+            for (uint64_t e : basis) v = std::min(v, v ^ e);
+            if (L.masks.size() == want || v == 0) {
+                later.push_back(std::move(m));
+                continue;
+            }
+            basis.push_back(v);
+            std::sort(basis.begin(), basis.end(), std::greater<uint64_t>());
+            L.masks.push_back(m.x);
+            L.count.push_back(int(m.idx.size()));
+            L.idx.insert(L.idx.end(), m.idx.begin(), m.idx.end());
+        }
+        joint = std::move(later);
+        launches.push_back(std::move(L));
+    }
+    // largest joint sweeps first: those of one size share a launch
+    std::stable_sort(launches.begin() + n_alone, launches.end(),
+                     [](const Launch& a, const Launch& b) { return a.masks.size() > b.masks.size(); });
+    // Sweeps in groups of up to kGroup, read back once per group: each sweep
+    // has partials of its own and its finished sums go to its own slot of the
+    // results area.  The Z-type sweeps of a small state share a launch, and so
+    // do its sweeps of one mask and, at any size, the joint sweeps of one
+    // number of masks.
     constexpr size_t kGroup = 64, kSlot = kMaxTermsPerSweep + 1;
     constexpr int kGroupedQubits = 22;
     auto make_args = [&](const Launch& L) {
@@ -1051,63 +1232,121 @@ void run_expect_t(sv_handle_s* h, const void* psi_v, int n, const PauliMasks* te
         }
         return a;
     };
+    const Partition Pz = partition(dim);
+    auto joint_blocks = [&](size_t d) {
+        const uint64_t items = dim >> d;
+        return std::max<uint64_t>(1, std::min<uint64_t>(items / kThreads, Pz.nb));
+    };
+    auto make_joint = [&](const Launch& L, bool want_norm) {
+        JointArgs a{};
+        const int d = int(L.masks.size());
+        a.per = (dim >> d) / joint_blocks(size_t(d));
+        a.want_norm = want_norm;
+        a.n_terms = int(L.idx.size());
+        std::vector<uint64_t> basis;
+        int at = 0;
+        for (int b = 0; b < d; ++b) {
+            a.x[b] = L.masks[b];
+            a.count[b] = L.count[b];
+            a.row[b] = at;
+            for (int t = 0; t < L.count[b]; ++t, ++at) {
+                JointTerm& tm = a.term[b][t];
+                tm.z = terms[L.idx[at]].z;
+                tm.ny = terms[L.idx[at]].ny;
+                for (int s = 0; s < (1 << d); ++s) {
+                    uint64_t xs = 0;
+                    for (int q = 0; q < d; ++q)
+                        if ((s >> q) & 1) xs ^= L.masks[q];
+                    tm.sig |= uint32_t(__builtin_popcountll(xs & tm.z) & 1) << s;
+                }
+            }
+            uint64_t v = L.masks[b];
+            for (uint64_t e : basis) v = std::min(v, v ^ e);
+            basis.push_back(v);
+            std::sort(basis.begin(), basis.end(), std::greater<uint64_t>());
+        }
+        for (int b = 0; b < d; ++b) a.pivot[b] = highest_bit(basis[size_t(d - 1 - b)]);
+        return a;
+    };
     const bool grouped = n <= kGroupedQubits;
-    const Partition Pz = partition(dim), Pxy = partition(dim > 1 ? dim / 2 : 1);
     const uint64_t stride = kSlot * Pz.nb;  // one sweep's partials (pair sweeps have fewer blocks)
     double* res_dev = part;
     double* parts = part + kGroup * kSlot;
-    size_t group = kGroup;
-    if (grouped) {
-        const size_t room = (h->ws_bytes - kMatRingBytes) / sizeof(double) - kGroup * kSlot;
-        group = std::max<size_t>(1, std::min<size_t>(kGroup, room / stride));
-    }
+    const size_t room = (h->ws_bytes - kMatRingBytes) / sizeof(double) - kGroup * kSlot;
+    const size_t group = std::max<size_t>(1, std::min<size_t>(kGroup, room / stride));
     std::vector<double> host(kGroup * kSlot);
-    std::vector<ExpectArgs> ga;
+    std::vector<char> staged;
     for (size_t g0 = 0; g0 < launches.size(); g0 += group) {
         const size_t g1 = std::min(launches.size(), g0 + group);
-        if (grouped) {
-            ga.clear();
-            uint32_t n_z = 0;
-            for (size_t li = g0; li < g1; ++li) {
-                ga.push_back(make_args(launches[li]));
-                if (ga.back().x == 0) ++n_z;
+        // descriptors of the group, staged in one copy: the finish's, those
+        // of a small state's Z-type and one-mask sweeps, the joint sweeps'
+        std::vector<FinishArgs> fa;
+        std::vector<ExpectArgs> za;
+        size_t n_z = 0;
+        std::vector<JointArgs> ja;
+        for (size_t li = g0; li < g1; ++li) {
+            const Launch& L = launches[li];
+            FinishArgs f{};
+            f.n_terms = int(L.idx.size());
+            if (!L.masks.empty()) {
+                f.nb = joint_blocks(L.masks.size());
+                ja.push_back(make_joint(L, li == 0));
+            } else {
+                const ExpectArgs a = make_args(L);
+                f.nb = partition(a.x != 0 ? dim / 2 : dim).nb;
+                if (grouped) za.push_back(a);
+                n_z += grouped && a.x == 0;
             }
-            const uint32_t n_all = uint32_t(ga.size());
-            const ExpectArgs* dargs =
-                static_cast<const ExpectArgs*>(stage_matrix(h, ga.data(), sizeof(ExpectArgs) * ga.size()));
-            if (n_z > 0)
-                hipLaunchKernelGGL((k_expect_z_group<R>), dim3(unsigned(Pz.nb), n_z), dim3(kThreads), 0, h->stream,
-                                   psi, dargs, parts, stride);
-            if (n_all > n_z)
-                hipLaunchKernelGGL((k_expect_xy_group<R>), dim3(unsigned(Pxy.nb), n_all - n_z), dim3(kThreads), 0,
-                                   h->stream, psi, dargs + n_z, parts + n_z * stride, stride);
-            SV_HIP(hipGetLastError());
-            hipLaunchKernelGGL(k_finish_group, dim3(unsigned(kSlot), n_all), dim3(kThreads), 0, h->stream, parts,
-                               stride, dargs, n_z, Pz.nb, Pxy.nb, res_dev, uint32_t(kSlot));
-            SV_HIP(hipGetLastError());
-        } else {
-            for (size_t li = g0; li < g1; ++li) {
-                const ExpectArgs a = make_args(launches[li]);
-                const Partition P = partition(a.x != 0 ? dim / 2 : dim);
-                if (a.x != 0)
-                    hipLaunchKernelGGL((k_expect_xy<R>), dim3(unsigned(P.nb)), dim3(kThreads), 0, h->stream, psi, a,
-                                       parts);
-                else
-                    hipLaunchKernelGGL((k_expect_z<R>), dim3(unsigned(P.nb)), dim3(kThreads), 0, h->stream, psi, a,
-                                       parts);
-                SV_HIP(hipGetLastError());
-                hipLaunchKernelGGL(k_finish_sums, dim3(unsigned(a.n_terms + 1)), dim3(kThreads), 0, h->stream,
-                                   parts, P.nb, res_dev + (li - g0) * kSlot);
-                SV_HIP(hipGetLastError());
-            }
+            fa.push_back(f);
         }
+        auto padded = [](size_t b) { return (b + 63) & ~size_t(63); };
+        const size_t za_at = padded(sizeof(FinishArgs) * fa.size());
+        const size_t ja_at = za_at + padded(sizeof(ExpectArgs) * za.size());
+        staged.assign(ja_at + sizeof(JointArgs) * ja.size(), 0);
+        std::memcpy(staged.data(), fa.data(), sizeof(FinishArgs) * fa.size());
+        if (!za.empty()) std::memcpy(staged.data() + za_at, za.data(), sizeof(ExpectArgs) * za.size());
+        if (!ja.empty()) std::memcpy(staged.data() + ja_at, ja.data(), sizeof(JointArgs) * ja.size());
+        const char* dev = static_cast<const char*>(stage_matrix(h, staged.data(), staged.size()));
+        const auto* dz = reinterpret_cast<const ExpectArgs*>(dev + za_at);
+        const auto* dj = reinterpret_cast<const JointArgs*>(dev + ja_at);
+        // (the Z-type sweeps come first, then the sweeps of one mask, then the
+        // joint ones)
+        if (n_z > 0)
+            hipLaunchKernelGGL((k_expect_z_group<R>), dim3(unsigned(Pz.nb), unsigned(n_z)), dim3(kThreads), 0,
+                               h->stream, psi, dz, parts, stride);
+        if (za.size() > n_z)
+            hipLaunchKernelGGL((k_expect_xy_group<R>), dim3(unsigned(partition(dim / 2).nb), unsigned(za.size() - n_z)),
+                               dim3(kThreads), 0, h->stream, psi, dz + n_z, parts + n_z * stride, stride);
+        SV_HIP(hipGetLastError());
+        for (size_t li = g0 + za.size(); li < g1 && launches[li].masks.empty(); ++li) {
+            const ExpectArgs a = make_args(launches[li]);
+            const unsigned nb = unsigned(fa[li - g0].nb);
+            double* to = parts + (li - g0) * stride;
+            if (a.x != 0)
+                hipLaunchKernelGGL((k_expect_xy<R>), dim3(nb), dim3(kThreads), 0, h->stream, psi, a, to);
+            else
+                hipLaunchKernelGGL((k_expect_z<R>), dim3(nb), dim3(kThreads), 0, h->stream, psi, a, to);
+            SV_HIP(hipGetLastError());
+        }
+        size_t li = g1 - ja.size();
+        for (size_t j0 = 0; j0 < ja.size();) {
+            const size_t d = launches[li + j0].masks.size();
+            size_t j1 = j0;
+            while (j1 < ja.size() && launches[li + j1].masks.size() == d) ++j1;
+            launch_joint<R>(h->stream, int(d), dim3(unsigned(joint_blocks(d)), unsigned(j1 - j0)), psi, dj + j0,
+                            parts + (li + j0 - g0) * stride, stride);
+            j0 = j1;
+        }
+        hipLaunchKernelGGL(k_finish_group, dim3(unsigned(kSlot), unsigned(g1 - g0)), dim3(kThreads), 0, h->stream, parts,
+                           stride, reinterpret_cast<const FinishArgs*>(dev), res_dev, uint32_t(kSlot));
+        SV_HIP(hipGetLastError());
         SV_HIP(hipMemcpyAsync(host.data(), res_dev, sizeof(double) * kSlot * (g1 - g0), hipMemcpyDeviceToHost,
                               h->stream));
         SV_HIP(hipStreamSynchronize(h->stream));
-        for (size_t li = g0; li < g1; ++li) {
-            const Launch& L = launches[li];
+        for (size_t l = g0; l < g1; ++l) {
+            const Launch& L = launches[l];
             const int nt = int(L.idx.size());
-            const double* r = host.data() + (li - g0) * kSlot;
+            const double* r = host.data() + (l - g0) * kSlot;
             for (int t = 0; t < nt; ++t) sums[L.idx[t]] = r[t];
             if (norm < 0.0) norm = r[nt];
         }
