@@ -852,7 +852,7 @@ void make_steps(const sv_state_s* s, const sv_fused_s* f, int first, int end, st
         if (p.sweep.multi) {
             for (int b : p.sweep.blocks)
                 (void)make_desc(s->n, f->blocks[b].targets, f->blocks[b].k, nullptr, nullptr, 0);
-            p.bytes = sweep_bytes(s->dt, p.sweep, f->blocks);
+            p.bytes = sweep_bytes(s->dt, p.sweep);
         } else {
             make_lone(s->n, f->blocks[p.sweep.blocks[0]], p.lone);
             p.desc = make_desc(s->n, p.lone.b.targets, p.lone.b.k, nullptr, nullptr, 0);

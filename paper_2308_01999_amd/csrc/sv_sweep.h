@@ -10,43 +10,53 @@
 
 namespace sv {
 
+// How a block is swept: 1-4 qubits as they are (states of one tile), five on
+// the matrix cores or on the vector units (block5_rows).
+constexpr int32_t kSweepMfma5 = 5, kSweepRows5 = 6;
+
 // One block of a sweep (device).  Tile-local positions: index bit q of the
-// state below L is q, the others L plus their rank in hi_pos.
+// state below L is q, the others L plus their rank among the tile's high bits.
 struct SweepBlock {
     uint32_t ins[5];   // group index -> tile-local base: the bits at and above each target, ascending
-    int32_t k;         // matrix qubits as swept (5: matrix cores)
+    int32_t kind;
     uint32_t off[32];  // byte offset of matrix index r in the swizzled tile
-    uint32_t mat;      // byte offset of the packed matrix in the sweep's buffer
-    int32_t rows;      // five qubits on the vector units (block5_rows)
 };
+constexpr int kSweepBlockWords = int(sizeof(SweepBlock) / 4);
+static_assert(kSweepBlockWords <= 64, "a wave holds a descriptor, one word a lane");
+
+// Bytes from one block's packed matrix to the next's.
+constexpr uint32_t sweep_matrix_stride(bool c64) { return c64 ? 12u << 10 : 16u << 10; }
 
 // Geometry of a sweep (kernel argument).
 constexpr int kSweepMaxHigh = 12;
 struct SweepArgs {
     uint64_t n_tiles;
     uint64_t tiles_per_wg;
-    uint64_t amps;              // amplitudes of the state if it is a single tile
-    int32_t L;                  // run bits
-    int32_t n_hi;               // T - L
-    int32_t hi_pos[kSweepMaxHigh];
-    int32_t trot, lg_tiles;     // tile order, as TileArgs
+    uint64_t amps;                     // amplitudes of the state
+    uint64_t bit_off[13];              // byte offset of tile-local bit p
+    uint64_t hi_mask[kSweepMaxHigh];   // the bits at and above each high bit of the tile
+    int32_t L;                         // run bits
+    int32_t n_hi;                      // T - L
+    int32_t trot, lg_tiles;            // tile order, as TileArgs
     int32_t n_blocks;
+    int32_t warm_lines;                // 128-byte lines of descriptors and matrices to bring to the L2 first
 };
 
-// A step of a program: one block on its own kernel (blocks.size() == 1,
-// multi false) or a sweep of the listed blocks in this order.
+// A step of a program: one block on its own kernel (multi false) or a sweep
+// of the listed blocks in this order.
 struct SweepStep {
     bool multi = false;
     std::vector<int> blocks;
     SweepArgs args{};
     int tile_bits = 0;
+    int hi_pos[kSweepMaxHigh] = {};
 };
 
 // The steps of blocks [first, end) of f on an n-qubit state.
 std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const FusedBlock* blocks, int first, int end);
 
 // Device buffer of a multi step: its descriptors, then its packed matrices.
-size_t sweep_bytes(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks);
+size_t sweep_bytes(sv_dtype_t dt, const SweepStep& st);
 void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, void* dst);
 void launch_sweep(sv_handle_s* h, sv_dtype_t dt, void* psi, const SweepStep& st, const void* buffer);
 

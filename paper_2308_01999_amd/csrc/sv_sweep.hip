@@ -24,8 +24,8 @@
 // Measured, before (a sweep per block) and after: 30-qubit brickwork circuit
 // of depth 20, complex64, 52 blocks in 20 sweeps, 156 -> 115 ms; 28-qubit
 // random CNOT/CP circuit, complex128, 71 -> 53 ms; 19-qubit circuit on random
-// pairs, complex128, 660 -> 392 us; 14 qubits complex64 as a recorded graph,
-// 155 -> 104 us.
+// pairs, complex128, 660 -> 323 us; 14 qubits complex64 as a recorded graph,
+// 155 -> 92 us; 12 qubits complex128 194 -> 117 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -72,16 +72,55 @@ struct Amp<double> {
 __device__ __forceinline__ uint64_t tile_origin(uint64_t t, const SweepArgs& a)
 {
     if (a.trot > 0) t = ((t & ((uint64_t(1) << a.trot) - 1)) << (a.lg_tiles - a.trot)) | (t >> a.trot);
-    return insert_zero_bits(t << a.L, a.hi_pos, a.n_hi);
+    t <<= a.L;
+    for (int j = 0; j < a.n_hi; ++j) t += t & a.hi_mask[j];
+    return t;
 }
 
 // Group index -> tile-local base: a zero inserted at each target position
 // (v + the bits at and above the position, which moves them up by one).
-__device__ __forceinline__ uint32_t spread(uint32_t v, const uint32_t* ins, int k)
+template <int K>
+__device__ __forceinline__ uint32_t spread(uint32_t v, const uint32_t* ins)
 {
-    for (int j = 0; j < k; ++j) v += v & ins[j];
+#pragma unroll
+    for (int j = 0; j < K; ++j) v += v & ins[j];
     return v;
 }
+
+// A lane's share of a five-qubit matrix, as pack5 lays it out.
+template <typename R>
+struct Ops;
+template <>
+struct Ops<float> {
+    f32x4 re[4], im[4], sum[4];
+    template <bool SUM>
+    __device__ __forceinline__ void load(const f32x4* __restrict__ m, int lane)
+    {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            re[q] = m[q * 64 + lane];
+            im[q] = m[256 + q * 64 + lane];
+            if (SUM) sum[q] = m[512 + q * 64 + lane];
+        }
+    }
+};
+template <>
+struct Ops<double> {
+    f64x2 re[4], im[4];  // the rows 16 rt + i of one row tile
+    __device__ __forceinline__ void load_rows(const f64x2* __restrict__ m, int lane, int rt)
+    {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            re[h] = m[(rt * 4 + h) * 64 + lane];
+            im[h] = m[(8 + rt * 4 + h) * 64 + lane];
+        }
+    }
+    template <bool SUM>
+    __device__ __forceinline__ void load(const f64x2* __restrict__ m, int lane)
+    {
+        load_rows(m, lane, 0);  // block5 loads row tile 1 while it multiplies row tile 0
+    }
+};
 
 // complex64, five qubits, on v_mfma_f32_32x32x2_f32: one column tile of 32
 // groups per wave (the chain of tile_c64_k5_sweep).  in / out: LDS byte address of the
@@ -89,18 +128,15 @@ __device__ __forceinline__ uint32_t spread(uint32_t v, const uint32_t* ins, int 
 // r%4) before the XOR with the uniform part of the index.  SUM: Re M + Im M is
 // read too (states of fewer than 12 qubits take it as the host rounded it, as
 // k_apply_mfma_c64_k5 does), otherwise formed here.
-template <bool SUM>
-__device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f32x4* __restrict__ m, uint32_t g0, int lane)
+// READY: the lane's matrix entries (complex128: of the first row tile) are in
+// `o` already.
+template <bool SUM, bool READY>
+__device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f32x4* __restrict__ m, Ops<float>& o,
+                                       uint32_t g0, int lane)
 {
     const int col = lane & 31, half = lane >> 5;
-    f32x4 vr[4], vi[4], vt[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        vr[q] = m[q * 64 + lane];
-        vi[q] = m[256 + q * 64 + lane];
-        if (SUM) vt[q] = m[512 + q * 64 + lane];
-    }
-    const uint32_t base = 8u * slot(spread(uint32_t(col), b.ins, 5)) ^ 8u * slot(spread(g0, b.ins, 5));
+    if (!READY) o.load<SUM>(m, lane);
+    const uint32_t base = 8u * slot(spread<5>(uint32_t(col), b.ins)) ^ 8u * slot(spread<5>(g0, b.ins));
     uint32_t in = base ^ (half ? b.off[1] : 0u), out = base ^ (half ? b.off[4] : 0u);
     asm volatile("" : "+v"(in), "+v"(out));  // keep (base ^ half part) ^ uniform part: one XOR per access
     f32x2 x[16];
@@ -109,12 +145,12 @@ __device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f32
     f32x16 p1 = {0}, p2 = {0}, p3 = {0};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const f32x4 vs = SUM ? vt[q] : vr[q] + vi[q];
+        const f32x4 vs = SUM ? o.sum[q] : o.re[q] + o.im[q];
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
             const f32x2 xv = x[4 * q + jj];
-            p1 = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[q][jj], xv.x, p1, 0, 0, 0);
-            p2 = __builtin_amdgcn_mfma_f32_32x32x2f32(vi[q][jj], xv.y, p2, 0, 0, 0);
+            p1 = __builtin_amdgcn_mfma_f32_32x32x2f32(o.re[q][jj], xv.x, p1, 0, 0, 0);
+            p2 = __builtin_amdgcn_mfma_f32_32x32x2f32(o.im[q][jj], xv.y, p2, 0, 0, 0);
             p3 = __builtin_amdgcn_mfma_f32_32x32x2f32(vs[jj], xv.x + xv.y, p3, 0, 0, 0);
         }
     }
@@ -134,7 +170,7 @@ __device__ __forceinline__ void block4(char* lds, const SweepBlock& b, const f32
     const uint32_t lin = ((q & 1) ? b.off[1] : 0u) ^ ((q & 2) ? b.off[2] : 0u);
     const uint32_t lout = ((q & 1) ? b.off[4] : 0u) ^ ((q & 2) ? b.off[8] : 0u);
     for (int c = 0; c < steps; ++c) {
-        const uint32_t base = 8u * slot(spread(g0 + uint32_t(c * 16 + col), b.ins, 4));
+        const uint32_t base = 8u * slot(spread<4>(g0 + uint32_t(c * 16 + col), b.ins));
         f32x2 x[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) x[s] = *reinterpret_cast<const f32x2*>(lds + (base ^ lin ^ b.off[4 * s]));
@@ -154,28 +190,24 @@ __device__ __forceinline__ void block4(char* lds, const SweepBlock& b, const f32
 // complex128, five qubits, on v_mfma_f64_16x16x4_f64: one column tile of 16
 // groups per wave, two row tiles (the chain of k_tile_c128_k5).  The lane's
 // inputs are matrix columns 4s + q, its outputs rows 16 rt + 4v + q.
-template <bool SUM>
-__device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f64x2* __restrict__ m, uint32_t g0, int lane)
+template <bool SUM, bool READY>
+__device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f64x2* __restrict__ m, Ops<double>& o,
+                                       uint32_t g0, int lane)
 {
     const int col = lane & 15, q = lane >> 4;
-    const uint32_t base = 16u * slot(spread(uint32_t(col), b.ins, 5)) ^ 16u * slot(spread(g0, b.ins, 5));
+    const uint32_t base = 16u * slot(spread<5>(uint32_t(col), b.ins)) ^ 16u * slot(spread<5>(g0, b.ins));
     uint32_t at = base ^ ((q & 1) ? b.off[1] : 0u) ^ ((q & 2) ? b.off[2] : 0u);
     asm volatile("" : "+v"(at));
     f64x2 x[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) x[s] = *reinterpret_cast<const f64x2*>(lds + (at ^ b.off[4 * s]));
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-        f64x2 vr[4], vi[4];
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            vr[h] = m[(rt * 4 + h) * 64 + lane];
-            vi[h] = m[(8 + rt * 4 + h) * 64 + lane];
-        }
+    Ops<double> second;
+    if (READY) second.load_rows(m, lane, 1);
+    auto rows = [&](int rt, const Ops<double>& w) {
         f64x4 p1 = {0}, p2 = {0}, p3 = {0};
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const double a0 = vr[s >> 1][s & 1], a1 = vi[s >> 1][s & 1];
+            const double a0 = w.re[s >> 1][s & 1], a1 = w.im[s >> 1][s & 1];
             p1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, x[s].x, p1, 0, 0, 0);
             p2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, x[s].y, p2, 0, 0, 0);
             p3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0 + a1, x[s].x + x[s].y, p3, 0, 0, 0);
@@ -184,7 +216,11 @@ __device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f64
         for (int v = 0; v < 4; ++v)
             *reinterpret_cast<f64x2*>(lds + (at ^ b.off[16 * rt + 4 * v])) =
                 f64x2{p1[v] - p2[v], p3[v] - p1[v] - p2[v]};
-    }
+    };
+    if (!READY) o.load_rows(m, lane, 0);
+    rows(0, o);
+    if (!READY) second.load_rows(m, lane, 1);
+    rows(1, second);
 }
 
 // k <= 3 (complex64) or k <= 4 (complex128) on the vector units, one group
@@ -197,7 +233,7 @@ __device__ __forceinline__ void block_small(char* lds, const SweepBlock& b, cons
     constexpr int D = 1 << K;
     for (uint32_t g = threadIdx.x; g < groups; g += uint32_t(nt)) {
         asm volatile("" ::: "memory");  // the matrix stays out of the registers
-        const uint32_t base = Amp<R>::kBytes * slot(spread(g, b.ins, K));
+        const uint32_t base = Amp<R>::kBytes * slot(spread<K>(g, b.ins));
         V v[D];
 #pragma unroll
         for (int c = 0; c < D; ++c) v[c] = *reinterpret_cast<const V*>(lds + (base ^ b.off[c]));
@@ -222,7 +258,7 @@ __device__ __forceinline__ void block_small(char* lds, const SweepBlock& b, cons
 // groups, four waves).  Every wave reads its groups' inputs before any writes.
 __device__ __forceinline__ void block5_rows(char* lds, const SweepBlock& b, const f64x2* __restrict__ m, int wave, int lane)
 {
-    const uint32_t base = 16u * slot(spread(uint32_t(lane), b.ins, 5));
+    const uint32_t base = 16u * slot(spread<5>(uint32_t(lane), b.ins));
     f64x2 v[32], y[8];
 #pragma unroll
     for (int c = 0; c < 32; ++c) v[c] = *reinterpret_cast<const f64x2*>(lds + (base ^ b.off[c]));
@@ -244,39 +280,56 @@ __device__ __forceinline__ void block5_rows(char* lds, const SweepBlock& b, cons
     for (int r = 0; r < 8; ++r) *reinterpret_cast<f64x2*>(lds + (base ^ b.off[wave * 8 + r])) = y[r];
 }
 
-// NT threads on tiles of 2^T amplitudes; SMALL: the state is one tile (2^n <=
-// 2^T amplitudes, the rest of the tile zeros that no one stores), its blocks
-// of fewer than five qubits on the vector units.
+// A block's descriptor from the wave's copy of it (lane l holds word l).
+__device__ __forceinline__ SweepBlock unpack_block(uint32_t words)
+{
+    auto word = [&](int i) { return uint32_t(__builtin_amdgcn_readlane(int(words), i)); };
+    SweepBlock b;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) b.ins[j] = word(j);
+    b.kind = int32_t(word(5));
+#pragma unroll
+    for (int r = 0; r < 32; ++r) b.off[r] = word(6 + r);
+    return b;
+}
+
+// NT threads on tiles of 2^T amplitudes.  SMALL (states of fewer than
+// kPadQubits qubits): one tile a workgroup, blocks of fewer than five qubits on
+// the vector units; a state of less than a tile leaves the rest of it zeros
+// that no one stores.
 template <typename R, int T, int NT, bool SMALL>
 __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
-                                               const char* __restrict__ mats, SweepArgs a)
+                                                            const char* __restrict__ mats, SweepArgs a)
 {
     using A = Amp<R>;
     using W = typename A::W;
-    constexpr int NV = (1 << T) / A::kPerVec / NT;     // 16-byte vectors per thread
-    constexpr int kCols = sizeof(R) == 4 ? 32 : 16;    // groups per wave
+    constexpr int NV = (1 << T) / A::kPerVec / NT;       // 16-byte vectors per thread
+    constexpr int kCols = sizeof(R) == 4 ? 32 : 16;      // groups per wave
+    constexpr uint32_t kStride = sweep_matrix_stride(sizeof(R) == 4);
     static_assert((1 << (T - 5)) == kCols * (NT / 64), "one column tile per wave");
+    static_assert(NV == 8, "three tile-local bits of a vector's index");
     __shared__ __align__(16) char lds[A::kBytes << T];
     const uint64_t t0 = uint64_t(blockIdx.x) * a.tiles_per_wg;
     if (t0 >= a.n_tiles) return;
     const uint64_t t1 = (a.n_tiles - t0 < a.tiles_per_wg) ? a.n_tiles : t0 + a.tiles_per_wg;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // tile-local amplitude of the thread's vector u: (u NT + tid) amplitudes
-    // per vector; the lane's part of its address is a 32-bit offset (the
-    // lanes' index bits at or above L sit at the lowest of hi_pos), the rest
-    // is uniform
-    constexpr int kLaneBits = 6 + (A::kPerVec == 2 ? 1 : 0);
-    const uint32_t li = uint32_t(lane) * A::kPerVec;
-    uint32_t loff = li;
-    if (a.L < kLaneBits)
-        loff = (li & ((1u << a.L) - 1)) | uint32_t(deposit_bits(li >> a.L, a.hi_pos, kLaneBits - a.L));
-    loff *= A::kBytes;
+    // the thread's vector u is tile-local amplitude (u NT + tid) amplitudes
+    // per vector: the lane's bits give a 32-bit offset (they sit at the lowest
+    // of the tile's high bits), the wave's and u's a uniform one
+    constexpr int kLane0 = A::kPerVec - 1, kWave0 = kLane0 + 6, kU0 = kWave0 + __builtin_ctz(NT / 64);
+    uint32_t loff = 0;
+#pragma unroll
+    for (int b = 0; b < 6; ++b) loff += ((lane >> b) & 1) ? uint32_t(a.bit_off[kLane0 + b]) : 0u;
+    uint64_t woff = 0;
+#pragma unroll
+    for (int b = 0; b < kU0 - kWave0; ++b) woff += ((wave >> b) & 1) ? a.bit_off[kWave0 + b] : 0u;
     uint64_t roff[NV];
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
-        const uint32_t i = uint32_t(u * NT + wave * 64) * A::kPerVec;
-        roff[u] = A::kBytes * (SMALL ? uint64_t(i)
-                                     : deposit_bits(i >> a.L, a.hi_pos, a.n_hi) + uint64_t(i & ((1u << a.L) - 1)));
+        roff[u] = woff;
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+            if ((u >> b) & 1) roff[u] += a.bit_off[kU0 + b];
     }
     char* base = psi + A::kBytes * tile_origin(t0, a);
     W buf[NV];
@@ -287,7 +340,21 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ 
         else
             buf[u] = __builtin_nontemporal_load(reinterpret_cast<const W*>(base + roff[u] + loff));
     }
-    for (uint64_t t = t0; t < t1; ++t) {
+    // few workgroups: the descriptors and matrices of all blocks are brought
+    // to the L2 at once (one word of each 128-byte line), not block by block
+    // (14 qubits complex64 as a graph: 104 -> 92 us, with the offsets of a
+    // tile's bits from the host)
+    constexpr int kWarm = 4;
+    uint32_t warm[kWarm] = {};
+    if (!SMALL && a.warm_lines > 0) {
+#pragma unroll
+        for (int w = 0; w < kWarm; ++w) {
+            const int l = w * NT + tid;
+            if (l < a.warm_lines) warm[w] = reinterpret_cast<const uint32_t*>(blocks)[l * 32];
+        }
+    }
+    auto matrix = [&](int i) { return reinterpret_cast<const W*>(mats + uint64_t(i) * kStride); };
+    for (uint64_t t = t0; t < t1; ++t) {  // (SMALL: once)
 #pragma unroll
         for (int u = 0; u < NV; ++u)
             *reinterpret_cast<W*>(lds + A::kBytes * slot(uint32_t(u * NT + tid) * A::kPerVec)) = buf[u];
@@ -299,26 +366,51 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ 
             for (int u = 0; u < NV; ++u)
                 buf[u] = __builtin_nontemporal_load(reinterpret_cast<const W*>(nbase + roff[u] + loff));
         }
-        for (int i = 0; i < a.n_blocks; ++i) {
-            const SweepBlock& b = blocks[i];
-            const char* m = mats + b.mat;
-            if (!SMALL || (b.k == 5 && !b.rows)) {
-                block5<SMALL>(lds, b, reinterpret_cast<const W*>(m), uint32_t(wave * kCols), lane);
-            } else if constexpr (SMALL) {
-                const auto* mv = reinterpret_cast<const typename A::V*>(m);
-                if constexpr (sizeof(R) == 8 && T == 11)
-                    if (b.k == 5) block5_rows(lds, b, mv, wave, lane);
-                if (b.k == 1) block_small<R, 1>(lds, b, mv, 1u << (T - 1), NT);
-                if (b.k == 2) block_small<R, 2>(lds, b, mv, 1u << (T - 2), NT);
-                if (b.k == 3) block_small<R, 3>(lds, b, mv, 1u << (T - 3), NT);
-                if (b.k == 4) {
+        if constexpr (!SMALL) {
+            for (int i = 0; i < a.n_blocks; ++i) {
+                Ops<R> o;
+                block5<false, false>(lds, blocks[i], matrix(i), o, uint32_t(wave * kCols), lane);
+                __syncthreads();
+            }
+        } else {
+            // a workgroup whose one or two waves a SIMD cannot hide the way of
+            // a matrix from memory: block i + 1's matrix and block i + 2's
+            // descriptor are loaded during block i (12 qubits complex128, 22
+            // blocks: 118 -> 93 us)
+            auto words = [&](int i) {
+                return reinterpret_cast<const uint32_t*>(blocks + (i < a.n_blocks ? i : a.n_blocks - 1))[lane < kSweepBlockWords ? lane : 0];
+            };
+            Ops<R> o[2];
+            uint32_t d[2] = {words(0), words(1)};
+            o[0].template load<true>(matrix(0), lane);
+            auto one = [&](int i, Ops<R>& now, Ops<R>& next, uint32_t& dw) {
+                const SweepBlock b = unpack_block(dw);
+                dw = words(i + 2);
+                if (i + 1 < a.n_blocks) next.template load<true>(matrix(i + 1), lane);
+                if (b.kind == kSweepMfma5) {
+                    block5<true, true>(lds, b, matrix(i), now, uint32_t(wave * kCols), lane);
+                    return;
+                }
+                const auto* mv = reinterpret_cast<const typename A::V*>(matrix(i));
+                if constexpr (sizeof(R) == 8 && NT == 256)
+                    if (b.kind == kSweepRows5) block5_rows(lds, blocks[i], mv, wave, lane);
+                if (b.kind == 1) block_small<R, 1>(lds, b, mv, 1u << (T - 1), NT);
+                if (b.kind == 2) block_small<R, 2>(lds, b, mv, 1u << (T - 2), NT);
+                if (b.kind == 3) block_small<R, 3>(lds, b, mv, 1u << (T - 3), NT);
+                if (b.kind == 4) {
                     if constexpr (sizeof(R) == 8)
                         block_small<R, 4>(lds, b, mv, 1u << (T - 4), NT);
                     else
-                        block4(lds, b, reinterpret_cast<const W*>(m), uint32_t(wave * 64), 4, lane);
+                        block4(lds, b, matrix(i), uint32_t(wave * 64), 4, lane);
                 }
+            };
+            for (int i = 0; i < a.n_blocks; i += 2) {
+                one(i, o[0], o[1], d[0]);
+                __syncthreads();
+                if (i + 1 == a.n_blocks) break;
+                one(i + 1, o[1], o[0], d[1]);
+                __syncthreads();
             }
-            __syncthreads();
         }
 #pragma unroll
         for (int u = 0; u < NV; ++u) {
@@ -330,21 +422,29 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ 
         base = nbase;
         __syncthreads();
     }
+#pragma unroll
+    for (int w = 0; w < kWarm; ++w) asm volatile("" ::"v"(warm[w]));
 }
 
 constexpr int tile_bits(sv_dtype_t dt) { return dt == SV_C64 ? 12 : 11; }  // 32 KiB
 
-// Shortest runs of a tile: 128 bytes, the line of the L2.
-constexpr int min_run_bits(sv_dtype_t dt) { return dt == SV_C64 ? 4 : 3; }
-
-// Largest state that is swept as one tile, its whole program in one launch.
-constexpr int kOneTileQubitsC64 = 13, kOneTileQubitsC128 = 12;
+// States of fewer qubits sweep blocks of 1-4 qubits as they are (k_sweep's
+// SMALL form), larger ones as five-qubit blocks, as their own sweeps do
+// (pad_to_five).  A state of up to tile_bits qubits is one tile and its
+// program one launch, and so does one qubit more, with twice the threads on
+// a tile twice as large.
+constexpr int kPadQubits = 14;
 
 // Smallest state whose blocks may pass blocks on other qubits on their way
 // into a sweep (below, a program's blocks keep their order and its amplitudes
 // their bits).
 constexpr int kReorderQubits = 22;
 constexpr int kReorderWindow = 96;
+
+// Shortest runs of a tile: 128 bytes, the line of the L2.  (Runs of 64 bytes
+// below 22 qubits, for 7% fewer sweeps, measured no faster: 339 us against 324
+// on 19 qubits complex128.)
+constexpr int min_run_bits(sv_dtype_t dt) { return dt == SV_C64 ? 4 : 3; }
 
 // Most blocks of one sweep: its descriptors and matrices fit a segment of the
 // handle's matrix ring (16 KiB a block at most, 1 MiB).
@@ -370,6 +470,11 @@ void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, SweepStep& s
     a = SweepArgs{};
     a.n_blocks = int(st.blocks.size());
     a.amps = uint64_t(1) << n;
+    const uint64_t bytes = dt == SV_C64 ? 8 : 16;
+    for (int p = 0; p < T; ++p) a.bit_off[p] = bytes << p;
+    // states of up to a few tiles a CU: every workgroup meets its blocks'
+    // matrices for the first time
+    if (n > T && uint64_t(1) << (n - T) <= uint64_t(4 * cu_count)) a.warm_lines = int32_t(sweep_bytes(dt, st) / 128);
     if (n <= T) {
         a.n_tiles = a.tiles_per_wg = 1;
         a.L = T;
@@ -379,7 +484,11 @@ void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, SweepStep& s
     while (L < T && __builtin_popcountll(on >> L) + L < T) ++L;
     a.L = L;
     for (int q = L; q < n; ++q)
-        if ((on >> q) & 1) a.hi_pos[a.n_hi++] = q;
+        if ((on >> q) & 1) {
+            a.bit_off[L + a.n_hi] = bytes << q;
+            a.hi_mask[a.n_hi] = ~((uint64_t(1) << q) - 1);
+            st.hi_pos[a.n_hi++] = q;
+        }
     a.lg_tiles = n - T;
     a.n_tiles = uint64_t(1) << a.lg_tiles;
     uint64_t per = a.n_tiles / (uint64_t(cu_count) * SV_TILE_WGS_PER_CU);
@@ -394,24 +503,24 @@ void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, SweepStep& s
 std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const FusedBlock* blocks, int first, int end)
 {
     std::vector<SweepStep> steps;
-    const bool one_tile = n <= (dt == SV_C64 ? kOneTileQubitsC64 : kOneTileQubitsC128);
-    const int T = one_tile ? std::max(n, tile_bits(dt)) : tile_bits(dt);
+    const bool one_tile = n <= tile_bits(dt) + 1;
+    const int T = std::max(tile_bits(dt), one_tile ? n : 0);
     const int lo = min_run_bits(dt);
     auto eligible = [&](const FusedBlock& b) {
         if (b.diagonal || b.n_couple > 0 || b.k > 5) return false;
         if (n > (dt == SV_C64 ? kMaxSweepQubitsC64 : kMaxSweepQubitsC128)) return false;
         // larger states: blocks on 2-4 qubits are swept as five-qubit ones
-        // where their own sweep is (pad_to_five: from 14 qubits on, with
-        // enough qubits below or above theirs), single-qubit ones on their own
-        if (one_tile || b.k == 5) return true;
+        // where their own sweep is (with enough qubits below or above
+        // theirs), single-qubit ones on their own
+        if (n < kPadQubits || b.k == 5) return true;
         const uint64_t on = qubit_mask(b);
         const int outside = __builtin_ctzll(on) + n - 1 - (63 - __builtin_clzll(on));
-        return b.k >= 2 && n >= 14 && outside >= 5 - b.k;
+        return b.k >= 2 && outside >= 5 - b.k;
     };
     auto fits = [&](uint64_t on) { return one_tile || __builtin_popcountll(on >> lo) <= T - lo; };
     auto add = [&](std::vector<int>&& take, uint64_t on) {
         SweepStep st;
-        st.multi = take.size() > 1;
+        st.multi = take.size() > 1 || (n < kReorderQubits && eligible(blocks[take[0]]));
         st.blocks = std::move(take);
         if (st.multi) {
             st.tile_bits = T;
@@ -495,69 +604,64 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
 
 namespace {
 
-// Bytes of a block's packed matrix in a sweep.
-size_t sweep_matrix_bytes(sv_dtype_t dt, int k)
-{
-    if (k == 5) return dt == SV_C64 ? 3 * 1024 * sizeof(float) : 2 * 1024 * sizeof(double);
-    if (k == 4 && dt == SV_C64) return 3 * 256 * sizeof(float);
-    return (size_t(dt == SV_C64 ? 8 : 16)) << (2 * k);
-}
-
-int swept_qubits(const SweepStep& st, int n_state_tile, const FusedBlock& b)
-{
-    return st.args.n_tiles == 1 && st.args.L == n_state_tile ? b.k : 5;
-}
+// Place of matrix entry (i, c) in a part of the packed operands.  complex64:
+// float4 [q][lane] of A[i][2(4q + j) + half], lane = i + 32 half; complex128:
+// double2 [rt 4 + s/2][lane] of A[16 rt + i][4s + q], lane = i + 16 q.
+struct PackOrder {
+    uint16_t f32[1024], f64[1024];
+    PackOrder()
+    {
+        for (int i = 0; i < 32; ++i)
+            for (int c = 0; c < 32; ++c) {
+                f32[i * 32 + c] = uint16_t(((c >> 3) * 64 + i + 32 * (c & 1)) * 4 + ((c >> 1) & 3));
+                f64[i * 32 + c] =
+                    uint16_t((((i >> 4) * 4 + (c >> 3)) * 64 + (i & 15) + 16 * (c & 3)) * 2 + ((c >> 2) & 1));
+            }
+    }
+};
+const PackOrder kPackOrder;
 
 // Packed A operands of the five-qubit sweep of M (x) I (M on the block's k
-// qubits, the padding qubits the high matrix bits).  complex64: float4
-// [part][q][lane] of A[i][2(4q + j) + half], lane = i + 32 half; complex128:
-// double2 [part][rt 4 + s/2][lane] of A[16 rt + i][4s + q], lane = i + 16 q.
-// Parts Re M, Im M and, for complex64, Re M + Im M (of the entries as given for
-// states of fewer than 12 qubits, else of the rounded ones, as their
-// single-block kernels take it).
+// qubits, the padding qubits the high matrix bits): parts Re M, Im M and, for
+// complex64, Re M + Im M (of the entries as given for states of fewer than
+// 12 qubits, else of the rounded ones, as their single-block kernels take it).
 template <typename R>
 void pack5(const FusedBlock& b, int n, R* o)
 {
-    const int d = 1 << b.k;
-    for (int i = 0; i < 32; ++i)
-        for (int c = 0; c < 32; ++c) {
-            double re = 0.0, im = 0.0;
-            if ((i >> b.k) == (c >> b.k)) {
-                const double* e = b.m + 2 * (size_t(i & (d - 1)) * d + (c & (d - 1)));
-                re = e[0];
-                im = e[1];
+    const uint16_t* at = sizeof(R) == 4 ? kPackOrder.f32 : kPackOrder.f64;
+    const int parts = sizeof(R) == 4 ? 3 : 2, d = 1 << b.k;
+    if (b.k < 5) std::fill(o, o + parts * 1024, R(0));
+    for (int e = 0; e < 32; e += d)  // the diagonal blocks of M (x) I
+        for (int i = 0; i < d; ++i) {
+            const double* row = b.m + 2 * size_t(i) * d;
+            const uint16_t* to = at + (e + i) * 32 + e;
+            for (int c = 0; c < d; ++c) {
+                const R re = R(row[2 * c]), im = R(row[2 * c + 1]);
+                o[to[c]] = re;
+                o[1024 + to[c]] = im;
+                if (sizeof(R) == 4) o[2048 + to[c]] = n < 12 ? R(row[2 * c] + row[2 * c + 1]) : re + im;
             }
-            size_t at;
-            if (sizeof(R) == 4)
-                at = size_t(((c >> 3) * 64 + i + 32 * (c & 1)) * 4 + ((c >> 1) & 3));
-            else
-                at = size_t((((i >> 4) * 4 + (c >> 3)) * 64 + (i & 15) + 16 * (c & 3)) * 2 + ((c >> 2) & 1));
-            o[at] = R(re);
-            o[1024 + at] = R(im);
-            if (sizeof(R) == 4) o[2048 + at] = n < 12 ? R(re + im) : R(re) + R(im);
         }
 }
 
 }  // namespace
 
-size_t sweep_bytes(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks)
+size_t sweep_bytes(sv_dtype_t dt, const SweepStep& st)
 {
-    size_t bytes = sizeof(SweepBlock) * st.blocks.size();
-    bytes = (bytes + 255) & ~size_t(255);
-    for (int i : st.blocks) bytes += (sweep_matrix_bytes(dt, swept_qubits(st, st.tile_bits, blocks[i])) + 255) & ~size_t(255);
-    return bytes;
+    return ((sizeof(SweepBlock) * st.blocks.size() + 255) & ~size_t(255)) +
+           sweep_matrix_stride(dt == SV_C64) * st.blocks.size();
 }
 
 void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, void* dst)
 {
-    char* out = static_cast<char*>(dst);
+    char* mat = static_cast<char*>(dst) + ((sizeof(SweepBlock) * st.blocks.size() + 255) & ~size_t(255));
     auto* desc = static_cast<SweepBlock*>(dst);
-    size_t mat = (sizeof(SweepBlock) * st.blocks.size() + 255) & ~size_t(255);
-    const int L = st.args.L, T = st.tile_bits;
-    for (size_t j = 0; j < st.blocks.size(); ++j) {
+    const int L = st.args.L, T = st.tile_bits, n = 63 - __builtin_clzll(st.args.amps);
+    for (size_t j = 0; j < st.blocks.size(); ++j, mat += sweep_matrix_stride(dt == SV_C64)) {
         const FusedBlock& b = blocks[st.blocks[j]];
+        const int k = n < kPadQubits ? b.k : 5;
         SweepBlock s{};
-        s.k = swept_qubits(st, T, b);
+        s.kind = k < 5 ? k : (dt == SV_C128 && n < 11) ? kSweepRows5 : kSweepMfma5;
         // tile-local positions of the targets, then of the padding qubits
         // (the lowest positions that are free)
         int pos[5] = {};
@@ -566,13 +670,13 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, vo
             int p = b.targets[a];
             if (p >= L) {
                 int r = 0;
-                while (st.args.hi_pos[r] != p) ++r;
+                while (st.hi_pos[r] != p) ++r;
                 p = L + r;
             }
             pos[a] = p;
             used |= 1u << p;
         }
-        for (int a = b.k, p = 0; a < s.k; ++p)
+        for (int a = b.k, p = 0; a < k; ++p)
             if (!((used >> p) & 1)) {
                 pos[a++] = p;
                 used |= 1u << p;
@@ -580,26 +684,21 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, vo
         int w = 0;
         for (int p = 0; p < T; ++p)
             if ((used >> p) & 1) s.ins[w++] = ~((1u << p) - 1u);
-        for (int r = 0; r < (1 << s.k); ++r) {
+        for (int r = 0; r < (1 << k); ++r) {
             uint32_t o = 0;
-            for (int a = 0; a < s.k; ++a)
+            for (int a = 0; a < k; ++a)
                 if ((r >> a) & 1) o |= 1u << pos[a];
             s.off[r] = (dt == SV_C64 ? 8u : 16u) * slot(o);
         }
-        s.mat = uint32_t(mat);
-        const int n = 63 - __builtin_clzll(st.args.amps);
-        s.rows = s.k == 5 && dt == SV_C128 && n < 11;
         desc[j] = s;
-        if (s.k == 5 && dt == SV_C64) {
-            pack5(b, n, reinterpret_cast<float*>(out + mat));
-        } else if (s.k == 5 && !s.rows) {
-            pack5(b, n, reinterpret_cast<double*>(out + mat));
-        } else if (s.rows) {
-            std::memcpy(out + mat, b.m, 1024 * 2 * sizeof(double));
-        } else {
-            pack_matrix(dt, 12, s.k, 0, b.m, 0, out + mat);
-        }
-        mat += (sweep_matrix_bytes(dt, s.k) + 255) & ~size_t(255);
+        if (s.kind == kSweepRows5)
+            std::memcpy(mat, b.m, 1024 * 2 * sizeof(double));
+        else if (k < 5)
+            pack_matrix(dt, 12, k, 0, b.m, 0, mat);
+        else if (dt == SV_C64)
+            pack5(b, n, reinterpret_cast<float*>(mat));
+        else
+            pack5(b, n, reinterpret_cast<double*>(mat));
     }
 }
 
@@ -607,25 +706,29 @@ void launch_sweep(sv_handle_s* h, sv_dtype_t dt, void* psi_v, const SweepStep& s
 {
     char* psi = static_cast<char*>(psi_v);
     const auto* blocks = static_cast<const SweepBlock*>(buffer);
-    const auto* mats = static_cast<const char*>(buffer);
+    const auto* mats = static_cast<const char*>(buffer) + ((sizeof(SweepBlock) * st.blocks.size() + 255) & ~size_t(255));
     const SweepArgs& a = st.args;
     const dim3 grid{unsigned((a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg)};
-    const bool one = a.n_tiles == 1;
+    const bool small = a.amps < (uint64_t(1) << kPadQubits);
+    const bool large_tile = st.tile_bits > tile_bits(dt);
+#define SV_SWEEP(R, T, NT, SMALL) \
+    hipLaunchKernelGGL((k_sweep<R, T, NT, SMALL>), grid, dim3(NT), 0, h->stream, psi, blocks, mats, a)
     if (dt == SV_C64) {
-        if (one && st.tile_bits == 13)
-            hipLaunchKernelGGL((k_sweep<float, 13, 512, true>), grid, dim3(512), 0, h->stream, psi, blocks, mats, a);
-        else if (one)
-            hipLaunchKernelGGL((k_sweep<float, 12, 256, true>), grid, dim3(256), 0, h->stream, psi, blocks, mats, a);
+        if (large_tile)
+            SV_SWEEP(float, 13, 512, true);
+        else if (small)
+            SV_SWEEP(float, 12, 256, true);
         else
-            hipLaunchKernelGGL((k_sweep<float, 12, 256, false>), grid, dim3(256), 0, h->stream, psi, blocks, mats, a);
+            SV_SWEEP(float, 12, 256, false);
     } else {
-        if (one && st.tile_bits == 12)
-            hipLaunchKernelGGL((k_sweep<double, 12, 512, true>), grid, dim3(512), 0, h->stream, psi, blocks, mats, a);
-        else if (one)
-            hipLaunchKernelGGL((k_sweep<double, 11, 256, true>), grid, dim3(256), 0, h->stream, psi, blocks, mats, a);
+        if (large_tile)
+            SV_SWEEP(double, 12, 512, true);
+        else if (small)
+            SV_SWEEP(double, 11, 256, true);
         else
-            hipLaunchKernelGGL((k_sweep<double, 11, 256, false>), grid, dim3(256), 0, h->stream, psi, blocks, mats, a);
+            SV_SWEEP(double, 11, 256, false);
     }
+#undef SV_SWEEP
     SV_HIP(hipGetLastError());
 }
 

@@ -29,17 +29,9 @@ static uint64_t h_origin(uint64_t t, const SweepArgs& a)
     if (a.trot > 0) t = ((t & ((uint64_t(1) << a.trot) - 1)) << (a.lg_tiles - a.trot)) | (t >> a.trot);
     uint64_t v = t << a.L;
     for (int j = 0; j < a.n_hi; ++j) {
-        const int p = a.hi_pos[j];
-        v = ((v >> p) << (p + 1)) | (v & ((uint64_t(1) << p) - 1));
+        v += v & a.hi_mask[j];
     }
     return v;
-}
-
-static uint64_t h_deposit(uint64_t r, const int32_t* pos, int n)
-{
-    uint64_t o = 0;
-    for (int b = 0; b < n; ++b) o |= ((r >> b) & 1u) << pos[b];
-    return o;
 }
 
 static uint32_t h_spread(uint32_t v, const uint32_t* ins, int k)
@@ -52,23 +44,22 @@ static void check_sweep(sv_dtype_t dt, int n, const SweepStep& st, const FusedBl
 {
     ++sweeps;
     const SweepArgs& a = st.args;
-    const int T = st.tile_bits, apv = dt == SV_C64 ? 2 : 1, lane_bits = dt == SV_C64 ? 7 : 6;
+    const int T = st.tile_bits, apv = dt == SV_C64 ? 2 : 1;
     const uint32_t bytes = dt == SV_C64 ? 8 : 16;
     const int nt = (1 << T) / apv / 8;
-    const bool one = a.n_tiles == 1;
+    const bool one = n <= T;
     if (!one && (a.L + a.n_hi != T || a.n_tiles != uint64_t(1) << (n - T))) return fail("tile shape", n, dt, step);
     // the tile's global offsets, through the kernel's lane and vector parts
     std::vector<uint64_t> glob(size_t(1) << T, ~uint64_t(0));
     for (int u = 0; u < 8; ++u)
         for (int tid = 0; tid < nt; ++tid) {
-            const uint32_t li = uint32_t(tid & 63) * apv;
-            uint64_t loff = li;
-            if (a.L < lane_bits)
-                loff = (li & ((1u << a.L) - 1)) | h_deposit(li >> a.L, a.hi_pos, lane_bits - a.L);
-            if (loff * bytes >> 32) fail("lane offset over 32 bits", n, dt, step);
-            const uint32_t i = uint32_t(u * nt + (tid & ~63)) * apv;
-            const uint64_t roff =
-                one ? i : h_deposit(i >> a.L, a.hi_pos, a.n_hi) + uint64_t(i & ((1u << a.L) - 1));
+            const uint32_t local = uint32_t(u * nt + tid) * apv, lane_mask = uint32_t(64 * apv - 1);
+            uint64_t loff = 0, roff = 0;
+            for (int p = 0; p < T; ++p)
+                if ((local >> p) & 1) ((lane_mask >> p) & 1 ? loff : roff) += a.bit_off[p];
+            if (loff >> 32 || loff % bytes || roff % bytes) fail("lane offset", n, dt, step);
+            loff /= bytes;
+            roff /= bytes;
             const uint32_t s = slot(uint32_t(u * nt + tid) * apv);
             for (int e = 0; e < apv; ++e) {
                 if (s + e >= glob.size() || glob[s + e] != ~uint64_t(0)) return fail("tile slot taken twice", n, dt, step);
@@ -88,12 +79,12 @@ static void check_sweep(sv_dtype_t dt, int n, const SweepStep& st, const FusedBl
         for (uint64_t g : glob) most = std::max(most, g);
         if (top + most != (uint64_t(1) << n) - 1) fail("last amplitude", n, dt, step);
     }
-    std::vector<char> buf(sweep_bytes(dt, st, blocks));
+    std::vector<char> buf(sweep_bytes(dt, st));
     pack_sweep(dt, st, blocks, buf.data());
     const auto* d = reinterpret_cast<const SweepBlock*>(buf.data());
     for (size_t j = 0; j < st.blocks.size(); ++j) {
         const FusedBlock& b = blocks[st.blocks[j]];
-        const int k = d[j].k;
+        const int k = std::min(d[j].kind, 5);
         std::vector<char> used(size_t(1) << T, 0);
         for (uint32_t g = 0; g < (1u << (T - k)); ++g) {
             const uint32_t base = slot(h_spread(g, d[j].ins, k));
@@ -136,7 +127,7 @@ int main()
                 int step = 0;
                 for (const SweepStep& st : plan) {
                     for (int i : st.blocks) order.push_back(i);
-                    if (st.multi != (st.blocks.size() > 1)) fail("step kind", n, dt, step);
+                    if (!st.multi && st.blocks.size() > 1) fail("step kind", n, dt, step);
                     if (st.multi) check_sweep(dt, n, st, blocks.data(), step);
                     ++step;
                 }
