@@ -262,7 +262,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? SV_K5_WIDE_WAVES : 1) void k_tile_c
     // the packed A operands (same for every wave): 3 x 64 lanes x 4 float4,
     // read back four k-steps at a time so only 12 of them are live at once
     __shared__ float4 amat[kK5AStaged * 64 * 4];
-    tile_c64_k5_sweep<NT, false>(psi, mats, a, blockIdx.x, lds, amat, ZSums{nullptr, -1, nullptr, nullptr});
+    tile_c64_k5_sweep<NT>(psi, mats, a, blockIdx.x, lds, amat);
 }
 
 // The same sweep for a block of coupled fusion: each group's inputs are first
@@ -273,8 +273,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? SV_K5_WIDE_WAVES : 3) void k_tile_c
 {
     __shared__ float4 lds[NT * kTileVecs];
     __shared__ float4 amat[kK5AStaged * 64 * 4];
-    tile_c64_k5_sweep<NT, false, true>(psi, mats, a, blockIdx.x, lds, amat, ZSums{nullptr, -1, nullptr, nullptr},
-                                       cp);
+    tile_c64_k5_sweep<NT, true>(psi, mats, a, blockIdx.x, lds, amat, cp);
 }
 
 __global__ __launch_bounds__(kTileThreads) void k_tile_c64_k4(float2* __restrict__ psi,

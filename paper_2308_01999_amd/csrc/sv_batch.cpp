@@ -59,8 +59,9 @@ struct BatchHost {
     std::vector<uint64_t> z_masks;
     uint64_t state_amps = 0;
     // level path
-    std::vector<BatchTileDesc> tdescs;
-    std::vector<float4> tmats;
+    std::vector<BatchSweep> sweeps;
+    std::vector<SweepBlock> sweep_blocks;
+    std::vector<char> sweep_mats;
     std::vector<BatchLevelEntry> entries;
     std::vector<BatchFinish> finish;
     std::vector<BatchLevel> levels;
@@ -235,79 +236,39 @@ void free_fused(sv_fused_s* f)
     delete f;
 }
 
-// Builds the device-side descriptors for circuits `sel` with widths kmax.
-// Block b (k targets tq, 2^k x 2^k complex128 m) as a five-qubit gate: the
-// targets, then free qubits below the lowest target and above the highest as
-// the high matrix bits, the matrix M (x) I (32 x 32 complex128).
-void pad_block_to_five(int n, int k, const int* tq, const double* m, int32_t* out_t, std::vector<double>& out_m)
-{
-    uint64_t used = 0;
-    int lo = n, hi = -1;
-    for (int a = 0; a < k; ++a) {
-        out_t[a] = tq[a];
-        used |= uint64_t(1) << tq[a];
-        lo = std::min(lo, tq[a]);
-        hi = std::max(hi, tq[a]);
-    }
-    int kk = k;
-    for (int q = lo - 1; q >= 0 && kk < 5; --q)
-        if (!((used >> q) & 1)) out_t[kk++] = q;
-    for (int q = hi + 1; q < n && kk < 5; ++q)
-        if (!((used >> q) & 1)) out_t[kk++] = q;
-    if (kk < 5) throw Error{SV_ERR_INTERNAL, "level path: no free qubits to pad a block"};
-    const int d = 1 << k, D = 32;
-    out_m.assign(size_t(2) * D * D, 0.0);
-    for (int e = 0; e < D / d; ++e)
-        for (int r = 0; r < d; ++r)
-            for (int c = 0; c < d; ++c) {
-                const size_t dst = size_t(e * d + r) * D + size_t(e * d + c);
-                out_m[2 * dst] = m[2 * (size_t(r) * d + c)];
-                out_m[2 * dst + 1] = m[2 * (size_t(r) * d + c) + 1];
-            }
-}
-
-// Level-path descriptors of circuit j (state at c.state_off, fused blocks f):
-// one tile-sweep descriptor and packed matrix per block, in tile shape s.
-// Returns the index of its first descriptor.
+// Level-path steps of circuit c (its state at c.state_off, fused blocks f) in
+// tile shape s: one sweep of consecutive blocks per step.  Returns their number;
+// the first is H.sweeps.size() before the call.
 uint32_t add_level_circuit(BatchHost& H, const BatchCircuit& c, const sv_fused_s* f, int cu_count,
                            const LevelShape& s)
 {
-    const uint32_t first = uint32_t(H.tdescs.size());
-    const size_t mat_bytes = packed_matrix_bytes(SV_C64, c.n, 5, 0);
-    std::vector<double> pm;
-    for (int bi = 0; bi < f->n_blocks; ++bi) {
-        const FusedBlock& fb = f->blocks[bi];
-        int32_t t5[5];
-        const double* m5 = fb.m;
-        if (fb.k < 5) {
-            pad_block_to_five(c.n, fb.k, fb.targets, fb.m, t5, pm);
-            m5 = pm.data();
-        } else {
-            for (int a = 0; a < 5; ++a) t5[a] = fb.targets[a];
-        }
-        GateDesc d{};
-        d.n = c.n;
-        d.k = 5;
-        for (int a = 0; a < 5; ++a) d.tbit[a] = uint64_t(1) << t5[a];
-        BatchTileDesc td{};
-        // the single-state sweep's narrow tiles, in the spread or the plain
-        // layout; a workgroup takes tiles_per_wg tiles in strided order.
-        // The last block also takes the Z-type sums (its partial sums are
-        // placed once the level schedule is fixed).
-        td.t = make_tile_args(d, c.n, 12, cu_count, s.spread ? 12 : 0, false);
-        td.t.tiles_per_wg = std::min<uint64_t>(uint64_t(s.tiles_per_wg), td.t.n_tiles);
-        td.t.trot = 0;
-        while ((uint64_t(1) << td.t.trot) < td.t.tiles_per_wg) ++td.t.trot;
-        td.state_off = c.state_off;
-        td.term0 = c.term0;
-        td.n_terms = bi + 1 == f->n_blocks ? int32_t(c.n_terms) : -1;
-        td.red_off = 0;
-        td.mat_off = H.tmats.size();
-        H.tmats.resize(H.tmats.size() + mat_bytes / sizeof(float4));
-        pack_matrix(SV_C64, c.n, 5, 0, m5, 0, H.tmats.data() + td.mat_off);
-        H.tdescs.push_back(td);
+    SweepRules rules;
+    rules.keep_order = true;
+    rules.pad_all = true;
+    rules.spread_lo = s.spread ? 12 : 0;
+    const auto steps = plan_sweeps(SV_C64, c.n, cu_count, f->blocks, 0, f->n_blocks, rules);
+    constexpr size_t stride = sweep_matrix_stride(true);
+    for (size_t i = 0; i < steps.size(); ++i) {
+        BatchSweep b{};
+        b.a = steps[i].args;
+        b.a.warm_lines = 0;
+        // a workgroup takes tiles_per_wg tiles in strided order
+        b.a.tiles_per_wg = std::min<uint64_t>(uint64_t(s.tiles_per_wg), b.a.n_tiles);
+        b.a.trot = 0;
+        while ((uint64_t(1) << b.a.trot) < b.a.tiles_per_wg) ++b.a.trot;
+        b.state_off = c.state_off;
+        b.block0 = uint32_t(H.sweep_blocks.size());
+        // the last step also takes the Z-type sums (its partial sums are
+        // placed once the level schedule is fixed)
+        b.term0 = c.term0;
+        b.n_terms = i + 1 == steps.size() ? int32_t(c.n_terms) : -1;
+        H.sweep_blocks.resize(H.sweep_blocks.size() + steps[i].blocks.size());
+        H.sweep_mats.resize(H.sweep_blocks.size() * stride);
+        pack_sweep(SV_C64, steps[i], f->blocks, H.sweep_blocks.data() + b.block0,
+                   H.sweep_mats.data() + size_t(b.block0) * stride);
+        H.sweeps.push_back(b);
     }
-    return first;
+    return uint32_t(steps.size());
 }
 
 // Fused programs of circuits (input index -> program) that a caller keeps
@@ -346,7 +307,8 @@ BatchHost build_host(const std::vector<CircuitInput>& in, const std::vector<int>
     }
     BatchHost H;
     H.circuits.resize(sel.size());
-    std::vector<uint32_t> level_circuits, level_first;
+    // circuits on the level path, their first step and their number of steps
+    std::vector<uint32_t> level_circuits, level_first, level_steps;
     uint64_t off = 0;
     for (size_t j = 0; j < sel.size(); ++j) {
         const int i = sel[j];
@@ -362,7 +324,8 @@ BatchHost build_host(const std::vector<CircuitInput>& in, const std::vector<int>
         const SizePlan& pl = plan_of(c.n);
         if (pl.level && fused[j]->n_blocks > 0) {
             level_circuits.push_back(uint32_t(j));
-            level_first.push_back(add_level_circuit(H, c, fused[j], cu_count, pl.shape));
+            level_first.push_back(uint32_t(H.sweeps.size()));
+            level_steps.push_back(add_level_circuit(H, c, fused[j], cu_count, pl.shape));
             if (blocks_out) (*blocks_out)[i] = fused[j]->n_blocks;
             continue;
         }
@@ -396,46 +359,42 @@ BatchHost build_host(const std::vector<CircuitInput>& in, const std::vector<int>
         if (cum > kShortShare * total) break;
     }
     std::reverse(H.order.begin() + std::ptrdiff_t(n_short), H.order.end());
-    // Level path: launch l sweeps block l of every circuit that has one;
-    // after it, the circuits whose last block it was are reduced.  In a
-    // launch, the circuits that end there come first (their tiles also take
-    // the Z-type sums, so they should not be the launch's last
-    // workgroups), then the others, most blocks first.
+    // Level path: launch l runs step l of every circuit that has one; after it,
+    // the circuits whose last step it was are reduced.  In a launch, the
+    // circuits that end there come first (their tiles also take the Z-type
+    // sums, so they should not be the launch's last workgroups), then the
+    // others, most steps first.
     std::vector<size_t> lorder(level_circuits.size());
     std::iota(lorder.begin(), lorder.end(), size_t(0));
-    std::stable_sort(lorder.begin(), lorder.end(), [&](size_t a, size_t b) {
-        return H.circuits[level_circuits[a]].n_blocks > H.circuits[level_circuits[b]].n_blocks;
-    });
+    std::stable_sort(lorder.begin(), lorder.end(), [&](size_t a, size_t b) { return level_steps[a] > level_steps[b]; });
     uint32_t depth = 0;
-    for (uint32_t j : level_circuits) depth = std::max(depth, H.circuits[j].n_blocks);
+    for (uint32_t d : level_steps) depth = std::max(depth, d);
     // A level with few tiles (the last levels, where a few deep circuits are
     // left) takes fewer tiles per workgroup, so that it still has about four
     // rounds of workgroups for the device: at most its tiles / (4 x the
     // workgroups that fit at once, three per CU), a power of two.  Not a
-    // circuit's last block: the order of its Z-type sums follows its tiles
+    // circuit's last step: the order of its Z-type sums follows its tiles
     // per workgroup, which thus stays the plan's, whatever the rest of the
-    // batch.  The last block gets room for its workgroups' sums.
+    // batch.  The last step gets room for its workgroups' sums.
     {
         std::vector<uint64_t> level_tiles(depth, 0);
-        for (size_t q = 0; q < level_circuits.size(); ++q) {
-            const BatchCircuit& c = H.circuits[level_circuits[q]];
-            for (uint32_t l = 0; l < c.n_blocks; ++l) level_tiles[l] += H.tdescs[level_first[q] + l].t.n_tiles;
-        }
+        for (size_t q = 0; q < level_circuits.size(); ++q)
+            for (uint32_t l = 0; l < level_steps[q]; ++l) level_tiles[l] += H.sweeps[level_first[q] + l].a.n_tiles;
         const uint64_t fill = uint64_t(cu_count) * 3 * 4;
         for (size_t q = 0; q < level_circuits.size(); ++q) {
             const BatchCircuit& c = H.circuits[level_circuits[q]];
-            for (uint32_t l = 0; l < c.n_blocks; ++l) {
-                BatchTileDesc& td = H.tdescs[level_first[q] + l];
-                TileArgs& t = td.t;
+            for (uint32_t l = 0; l < level_steps[q]; ++l) {
+                BatchSweep& sw = H.sweeps[level_first[q] + l];
+                SweepArgs& t = sw.a;
                 uint64_t cap = 1;
                 while (cap * 2 * fill <= level_tiles[l]) cap *= 2;
-                if (l + 1 < c.n_blocks && t.tiles_per_wg > cap) {
+                if (l + 1 < level_steps[q] && t.tiles_per_wg > cap) {
                     t.tiles_per_wg = cap;
                     t.trot = 0;
                     while ((uint64_t(1) << t.trot) < t.tiles_per_wg) ++t.trot;
                 }
-                if (l + 1 == c.n_blocks) {
-                    td.red_off = H.n_partials;
+                if (l + 1 == level_steps[q]) {
+                    sw.red_off = H.n_partials;
                     H.n_partials += (t.n_tiles + t.tiles_per_wg - 1) / t.tiles_per_wg * (c.n_terms + 1);
                 }
             }
@@ -447,16 +406,15 @@ BatchHost build_host(const std::vector<CircuitInput>& in, const std::vector<int>
         L.finish0 = H.finish.size();
         std::vector<size_t> here;
         for (size_t q : lorder)
-            if (H.circuits[level_circuits[q]].n_blocks == l + 1) here.push_back(q);
+            if (level_steps[q] == l + 1) here.push_back(q);
         for (size_t q : lorder)
-            if (H.circuits[level_circuits[q]].n_blocks > l + 1) here.push_back(q);
+            if (level_steps[q] > l + 1) here.push_back(q);
         for (size_t q : here) {
-            const BatchCircuit& c = H.circuits[level_circuits[q]];
-            const uint32_t di = level_first[q] + l;
-            const TileArgs& t = H.tdescs[di].t;
+            const uint32_t si = level_first[q] + l;
+            const SweepArgs& t = H.sweeps[si].a;
             const uint64_t n_wg = (t.n_tiles + t.tiles_per_wg - 1) / t.tiles_per_wg;
-            for (uint64_t w = 0; w < n_wg; ++w) H.entries.push_back({di, uint32_t(w)});
-            if (c.n_blocks == l + 1) H.finish.push_back({level_circuits[q], uint32_t(n_wg), H.tdescs[di].red_off});
+            for (uint64_t w = 0; w < n_wg; ++w) H.entries.push_back({si, uint32_t(w)});
+            if (level_steps[q] == l + 1) H.finish.push_back({level_circuits[q], uint32_t(n_wg), H.sweeps[si].red_off});
         }
         L.n_entries = uint32_t(H.entries.size() - L.entry0);
         L.n_finish = uint32_t(H.finish.size() - L.finish0);
@@ -491,8 +449,9 @@ char* upload(const BatchHost& H, BatchArgs& a, hipStream_t stream, size_t* dev_b
         part(nullptr, H.circuits.size() * sizeof(uint64_t)),       // completion times
         part(nullptr, 256),                                        // run start
         part(nullptr, 256),                                        // queue
-        part(H.tdescs.data(), H.tdescs.size() * sizeof(BatchTileDesc)),
-        part(H.tmats.data(), H.tmats.size() * sizeof(float4)),
+        part(H.sweeps.data(), H.sweeps.size() * sizeof(BatchSweep)),
+        part(H.sweep_blocks.data(), H.sweep_blocks.size() * sizeof(SweepBlock)),
+        part(H.sweep_mats.data(), H.sweep_mats.size()),
         part(H.entries.data(), H.entries.size() * sizeof(BatchLevelEntry)),
         part(H.finish.data(), H.finish.size() * sizeof(BatchFinish)),
         part(nullptr, H.n_partials * sizeof(double)),             // last levels' sums
@@ -524,11 +483,12 @@ char* upload(const BatchHost& H, BatchArgs& a, hipStream_t stream, size_t* dev_b
     a.t_done = reinterpret_cast<uint64_t*>(where[6]);
     a.t_start = reinterpret_cast<uint64_t*>(where[7]);
     a.queue = reinterpret_cast<uint32_t*>(where[8]);
-    a.tdescs = reinterpret_cast<const BatchTileDesc*>(where[9]);
-    a.tmats = reinterpret_cast<const float4*>(where[10]);
-    a.entries = reinterpret_cast<const BatchLevelEntry*>(where[11]);
-    a.finish = reinterpret_cast<const BatchFinish*>(where[12]);
-    a.partials = reinterpret_cast<double*>(where[13]);
+    a.sweeps = reinterpret_cast<const BatchSweep*>(where[9]);
+    a.sweep_blocks = reinterpret_cast<const SweepBlock*>(where[10]);
+    a.sweep_mats = where[11];
+    a.entries = reinterpret_cast<const BatchLevelEntry*>(where[12]);
+    a.finish = reinterpret_cast<const BatchFinish*>(where[13]);
+    a.partials = reinterpret_cast<double*>(where[14]);
     a.n_queue = uint32_t(H.order.size());
     const hipError_t e = hipStreamSynchronize(stream);
     if (e != hipSuccess) {

@@ -4,7 +4,7 @@
 
 #include <cstdint>
 
-#include "sv_tile.h"
+#include "sv_sweep.h"
 
 namespace sv {
 
@@ -38,19 +38,19 @@ struct BatchCircuit {
     uint64_t state_off;  // amplitude offset in the states buffer
 };
 
-// One block of a circuit on the level path (states of at least the level
-// path's qubit count): the block as a five-qubit gate (smaller blocks padded
-// with free qubits) in the single-state tile sweep's geometry, and where the
-// circuit's state and the block's packed matrix live.
-struct BatchTileDesc {
-    TileArgs t;
+// One step of a circuit on the level path (states of at least the level path's
+// qubit count): a sweep of its blocks [block0, block0 + a.n_blocks), every
+// block as a five-qubit gate, their matrices at the same index.
+struct BatchSweep {
+    SweepArgs a;
     uint64_t state_off;  // amplitude offset of the circuit's state
-    uint64_t mat_off;    // float4 offset of the packed A operands
-    // the circuit's last block: its Z-type sums go to partials[red_off +
+    uint32_t block0;
+    // the circuit's last step: its Z-type sums go to partials[red_off +
     // wg * (n_terms + 1) ...] (terms, then the norm); n_terms = -1 otherwise
+    int32_t n_terms;
     uint64_t red_off;
     uint32_t term0;
-    int32_t n_terms;
+    uint32_t pad;
 };
 
 // A circuit whose last level is done: its n_wg workgroup sums at red_off.
@@ -60,10 +60,10 @@ struct BatchFinish {
     uint64_t red_off;
 };
 
-// Workgroup w of a level launch sweeps tiles of block desc[entries[w].x],
-// as workgroup entries[w].y of that block's single-state sweep.
+// Workgroup w of a level launch is workgroup entries[w].wg of step
+// entries[w].sweep.
 struct BatchLevelEntry {
-    uint32_t desc;
+    uint32_t sweep;
     uint32_t wg;
 };
 
@@ -79,8 +79,9 @@ struct BatchArgs {
     uint64_t* t_start;  // device wall clock at the run's start (the reset kernel)
     uint32_t* queue;
     uint32_t n_queue;  // circuits the persistent kernel takes (order[0 .. n_queue))
-    const BatchTileDesc* tdescs;     // level path
-    const float4* tmats;
+    const BatchSweep* sweeps;        // level path
+    const SweepBlock* sweep_blocks;
+    const char* sweep_mats;
     const BatchLevelEntry* entries;
     const BatchFinish* finish;       // circuits whose last level is done, per level
     double* partials;                // per-workgroup Z-type sums of the last levels

@@ -7,11 +7,10 @@
 //     written to HBM once;
 //   - larger states are swept block by block through 4096-amplitude tiles
 //     staged in LDS, the same tiling as the single-state sweep.
-// Larger circuits run on the level path: launch l applies block l of every
-// such circuit that has one, each block through the single-state
-// five-qubit tile sweep (many workgroups per state, so the streamed states
-// move at the single-state sweep's rate), and a circuit's expectations are
-// taken on a side stream right after its last level.
+// Larger circuits run on the level path (k_batch_level, sv_sweep.hip): launch l
+// runs step l of every such circuit that has one, a sweep of the blocks that
+// fit one tile, and a circuit's expectations are finished right after its last
+// level.
 // k = 4, 5 blocks run as three real GEMMs on the matrix cores (Gauss's
 // product), k <= 3 on the vector ALUs.  The workgroup records its
 // circuit's completion on the device wall clock.  Every workgroup exits
@@ -427,27 +426,6 @@ __global__ void k_batch_reset(uint32_t* queue, uint64_t* t_start)
     *t_start = wall_clock64();
 }
 
-// Level path: workgroup w sweeps its tiles of one block of one circuit; on a
-// circuit's last block it also leaves the Z-type sums of its tiles.
-template <bool FIRST>
-__global__ __launch_bounds__(tile::kTileThreads, 3) void k_batch_level(float2* __restrict__ states,
-                                                                    const BatchTileDesc* __restrict__ descs,
-                                                                    const BatchLevelEntry* __restrict__ entries,
-                                                                    const float4* __restrict__ mats,
-                                                                    const uint64_t* __restrict__ z_masks,
-                                                                    double* __restrict__ partials)
-{
-    __shared__ float4 lds[tile::kTileThreads * tile::kTileVecs];
-    __shared__ float4 amat[tile::kK5AStaged * 64 * 4];
-    __shared__ double zacc[(tile::kTileThreads / 64) * (tile::kZSumsMax + 1)];
-    const BatchLevelEntry e = entries[blockIdx.x];
-    const BatchTileDesc& d = descs[e.desc];
-    const tile::ZSums zs{z_masks + d.term0, d.n_terms,
-                         partials + d.red_off + uint64_t(e.wg) * uint64_t(d.n_terms + 1), zacc};
-    tile::tile_c64_k5_sweep<tile::kTileThreads, FIRST>(states + d.state_off, mats + d.mat_off, d.t, e.wg, lds,
-                                                       amat, zs);
-}
-
 // Level path: a finished circuit's expectations from its workgroups' sums,
 // then its completion time.  Thread (g, c) of G = kThreads / S groups of S =
 // n_terms + 1 columns (the norm last) adds the rows g, g + G, ... of column
@@ -486,18 +464,6 @@ __global__ __launch_bounds__(kThreads) void k_batch_finish(BatchArgs A, const Ba
 void launch_batch_reset(hipStream_t stream, const BatchArgs& a)
 {
     hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(1), 0, stream, a.queue, a.t_start);
-    SV_HIP(hipGetLastError());
-}
-
-void launch_batch_level(hipStream_t stream, const BatchArgs& a, uint64_t first, uint32_t n_entries, bool first_level)
-{
-    float2* states = static_cast<float2*>(a.states);
-    if (first_level)
-        hipLaunchKernelGGL(k_batch_level<true>, dim3(n_entries), dim3(tile::kTileThreads), 0, stream, states, a.tdescs,
-                           a.entries + first, a.tmats, a.z_masks, a.partials);
-    else
-        hipLaunchKernelGGL(k_batch_level<false>, dim3(n_entries), dim3(tile::kTileThreads), 0, stream, states,
-                           a.tdescs, a.entries + first, a.tmats, a.z_masks, a.partials);
     SV_HIP(hipGetLastError());
 }
 

@@ -48,16 +48,27 @@ struct SweepStep {
     bool multi = false;
     std::vector<int> blocks;
     SweepArgs args{};
+    bool padded = false;  // blocks of fewer than five qubits are swept as five-qubit ones
     int tile_bits = 0;
     int hi_pos[kSweepMaxHigh] = {};
 };
 
+struct SweepRules {
+    bool keep_order = false;  // blocks in program order on states of any size
+    bool pad_all = false;     // every block is swept as a five-qubit one
+    int spread_lo = 0;        // > 0: tiles with runs of at most 1 KiB, filled up with free bits from here up
+};
+
 // The steps of blocks [first, end) of f on an n-qubit state.
-std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const FusedBlock* blocks, int first, int end);
+std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const FusedBlock* blocks, int first, int end,
+                                   const SweepRules& rules = SweepRules());
 
 // Device buffer of a multi step: its descriptors, then its packed matrices.
 size_t sweep_bytes(sv_dtype_t dt, const SweepStep& st);
 void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, void* dst);
+// The same into separate arrays: the blocks' descriptors, and their matrices
+// sweep_matrix_stride apart.
+void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, SweepBlock* desc, char* mats);
 void launch_sweep(sv_handle_s* h, sv_dtype_t dt, void* psi, const SweepStep& st, const void* buffer);
 
 }  // namespace sv

@@ -31,7 +31,7 @@
 #include <algorithm>
 #include <cstring>
 
-#include "sv_sweep.h"
+#include "sv_batch.h"
 #include "sv_tile.h"
 
 namespace sv {
@@ -293,13 +293,104 @@ __device__ __forceinline__ SweepBlock unpack_block(uint32_t words)
     return b;
 }
 
-// NT threads on tiles of 2^T amplitudes.  SMALL (states of fewer than
-// kPadQubits qubits): one tile a workgroup, blocks of fewer than five qubits on
-// the vector units; a state of less than a tile leaves the rest of it zeros
-// that no one stores.
-template <typename R, int T, int NT, bool SMALL>
-__global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
-                                                            const char* __restrict__ mats, SweepArgs a)
+// Z-type expectation sums of the state a sweep leaves behind, taken from its
+// tiles in LDS (no extra read of the state): for a workgroup, out[t] =
+// sum over its amplitudes i of |psi_i|^2 (-1)^popcount(i & zm[t]) for
+// t < n_terms, and out[n_terms] = sum |psi_i|^2, all FP64 in a fixed order
+// (per thread by a Walsh-Hadamard transform, per wave by a butterfly, waves
+// and tiles in order).  acc: LDS of 4 x (kZSumsMax + 1) doubles, zeroed.
+// n_terms < 0: no sums.
+constexpr int kZSumsMax = 32;
+struct ZSums {
+    const uint64_t* zm;
+    int n_terms;
+    double* out;
+    double* acc;
+};
+
+// Adds a complex64 tile's sums (256 threads, 8 pairs a thread).  i0: global
+// index of the thread's first amplitude.  The thread's 16 amplitudes differ in
+// the tile-local bits 0 and 9-11 (amplitude j = e + 2u is element e of vector u)
+// and share all others, so a term's sum over them is s * c[k]: c the
+// Walsh-Hadamard transform of their probabilities over j, c[k] = sum_j p_j
+// (-1)^popcount(j & k), k the term mask's bits at those four index bits, s its
+// parity over the bits the 16 share.  The norm is the term of mask 0.
+__device__ __forceinline__ void add_z_sums(char* lds, const SweepArgs& a, const ZSums& zs, uint64_t i0, int tid)
+{
+    constexpr int NT = 256;
+    const int lane = tid & 63, wave = tid >> 6;
+    double c[16];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(lds + 8u * slot(uint32_t(u * NT + tid) * 2));
+        c[2 * u] = fma(double(v.x), double(v.x), __dmul_rn(double(v.y), double(v.y)));
+        c[2 * u + 1] = fma(double(v.z), double(v.z), __dmul_rn(double(v.w), double(v.w)));
+    }
+#pragma unroll
+    for (int h = 1; h < 16; h <<= 1) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            if (j & h) continue;
+            const double x = c[j], y = c[j | h];
+            c[j] = __dadd_rn(x, y);
+            c[j | h] = __dsub_rn(x, y);
+        }
+    }
+    // the coefficients take the thread's own slots (its amplitudes are read;
+    // no other thread reads these slots before the next barrier)
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+        *reinterpret_cast<f64x2*>(lds + 8u * slot(uint32_t(u * NT + tid) * 2)) = f64x2{c[2 * u], c[2 * u + 1]};
+    int jpos[4];  // index bits of the tile-local bits 0 and 9-11
+#pragma unroll
+    for (int q = 0; q < 4; ++q) jpos[q] = __builtin_ctzll(a.bit_off[q == 0 ? 0 : 8 + q]) - 3;
+    // terms (the norm last, as term n_terms) in passes of eight; a pass's wave
+    // sums by a reduce-scatter butterfly: after the exchanges over lane bits
+    // 5, 4, 3 a lane holds one term, term (lane >> 3) & 7 of the pass, summed
+    // over 8 lanes, and three more exchanges sum the rest
+    double* row = zs.acc + wave * (kZSumsMax + 1);
+    const bool b5 = (lane & 32) != 0, b4 = (lane & 16) != 0, b3 = (lane & 8) != 0;
+    for (int p0 = 0; p0 <= zs.n_terms; p0 += 8) {
+        double v[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int tt = p0 + t;
+            const uint64_t m = tt < zs.n_terms ? zs.zm[tt] : 0;
+            const int k = int((m >> jpos[0]) & 1) | int(((m >> jpos[1]) & 1) << 1) | int(((m >> jpos[2]) & 1) << 2) |
+                          int(((m >> jpos[3]) & 1) << 3);
+            const double x =
+                *reinterpret_cast<const double*>(lds + 8u * slot(uint32_t((k >> 1) * NT + tid) * 2) + 8 * (k & 1));
+            v[t] = tt > zs.n_terms ? 0.0 : ((__popcll(i0 & m) & 1) ? -x : x);
+        }
+        double w4[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            w4[j] = __dadd_rn(b5 ? v[j + 4] : v[j], __shfl_xor(b5 ? v[j] : v[j + 4], 32, 64));
+        double w2[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            w2[j] = __dadd_rn(b4 ? w4[j + 2] : w4[j], __shfl_xor(b4 ? w4[j] : w4[j + 2], 16, 64));
+        double w = __dadd_rn(b3 ? w2[1] : w2[0], __shfl_xor(b3 ? w2[0] : w2[1], 8, 64));
+        w = __dadd_rn(w, __shfl_xor(w, 4, 64));
+        w = __dadd_rn(w, __shfl_xor(w, 2, 64));
+        w = __dadd_rn(w, __shfl_xor(w, 1, 64));
+        const int tt = p0 + ((lane >> 3) & 7);
+        if ((lane & 7) == 0 && tt <= zs.n_terms) {
+            const int r = tt == zs.n_terms ? kZSumsMax : tt;
+            row[r] = __dadd_rn(row[r], w);
+        }
+    }
+}
+
+// The sweep of workgroup wg, NT threads on tiles of 2^T amplitudes.  SMALL
+// (states of fewer than kPadQubits qubits): one tile a workgroup, blocks of
+// fewer than five qubits on the vector units; a state of less than a tile
+// leaves the rest of it zeros that no one stores.  FIRST: the state is |0..0>
+// and is not read.  zs: complex64 sweeps of 256 threads only.
+template <typename R, int T, int NT, bool SMALL, bool FIRST = false, bool SUMS = false>
+__device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
+                                            const char* __restrict__ mats, const SweepArgs& a, uint64_t wg,
+                                            char* lds, const ZSums& zs)
 {
     using A = Amp<R>;
     using W = typename A::W;
@@ -308,11 +399,11 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ 
     constexpr uint32_t kStride = sweep_matrix_stride(sizeof(R) == 4);
     static_assert((1 << (T - 5)) == kCols * (NT / 64), "one column tile per wave");
     static_assert(NV == 8, "three tile-local bits of a vector's index");
-    __shared__ __align__(16) char lds[A::kBytes << T];
-    const uint64_t t0 = uint64_t(blockIdx.x) * a.tiles_per_wg;
+    const uint64_t t0 = wg * a.tiles_per_wg;
     if (t0 >= a.n_tiles) return;
     const uint64_t t1 = (a.n_tiles - t0 < a.tiles_per_wg) ? a.n_tiles : t0 + a.tiles_per_wg;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (SUMS && zs.n_terms >= 0 && lane <= kZSumsMax) zs.acc[wave * (kZSumsMax + 1) + lane] = 0.0;
     // the thread's vector u is tile-local amplitude (u NT + tid) amplitudes
     // per vector: the lane's bits give a 32-bit offset (they sit at the lowest
     // of the tile's high bits), the wave's and u's a uniform one
@@ -335,11 +426,12 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ 
     W buf[NV];
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
-        if (SMALL && uint64_t(u * NT + tid) * A::kPerVec >= a.amps)
+        if (FIRST || (SMALL && uint64_t(u * NT + tid) * A::kPerVec >= a.amps))
             buf[u] = W{};
         else
             buf[u] = __builtin_nontemporal_load(reinterpret_cast<const W*>(base + roff[u] + loff));
     }
+    if (FIRST && base == psi && tid == 0) buf[0][0] = 1;
     // few workgroups: the descriptors and matrices of all blocks are brought
     // to the L2 at once (one word of each 128-byte line), not block by block
     // (14 qubits complex64 as a graph: 104 -> 92 us, with the offsets of a
@@ -355,6 +447,14 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ 
     }
     auto matrix = [&](int i) { return reinterpret_cast<const W*>(mats + uint64_t(i) * kStride); };
     for (uint64_t t = t0; t < t1; ++t) {  // (SMALL: once)
+        if (FIRST && base != psi) {
+            // |0..0> is zero on every tile but the first, and so is its image:
+            // such a tile is only written
+#pragma unroll
+            for (int u = 0; u < NV; ++u) __builtin_nontemporal_store(W{}, reinterpret_cast<W*>(base + roff[u] + loff));
+            if (t + 1 < t1) base = psi + A::kBytes * tile_origin(t + 1, a);
+            continue;
+        }
 #pragma unroll
         for (int u = 0; u < NV; ++u)
             *reinterpret_cast<W*>(lds + A::kBytes * slot(uint32_t(u * NT + tid) * A::kPerVec)) = buf[u];
@@ -362,9 +462,11 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ 
         char* nbase = base;
         if (!SMALL && t + 1 < t1) {
             nbase = psi + A::kBytes * tile_origin(t + 1, a);
+            if (!FIRST) {
 #pragma unroll
-            for (int u = 0; u < NV; ++u)
-                buf[u] = __builtin_nontemporal_load(reinterpret_cast<const W*>(nbase + roff[u] + loff));
+                for (int u = 0; u < NV; ++u)
+                    buf[u] = __builtin_nontemporal_load(reinterpret_cast<const W*>(nbase + roff[u] + loff));
+            }
         }
         if constexpr (!SMALL) {
             for (int i = 0; i < a.n_blocks; ++i) {
@@ -419,11 +521,52 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ 
                 *reinterpret_cast<const W*>(lds + A::kBytes * slot(uint32_t(u * NT + tid) * A::kPerVec)),
                 reinterpret_cast<W*>(base + roff[u] + loff));
         }
+        if constexpr (SUMS)
+            if (zs.n_terms >= 0) add_z_sums(lds, a, zs, uint64_t(base - psi + int64_t(roff[0]) + loff) / A::kBytes, tid);
         base = nbase;
         __syncthreads();
     }
+    if (SUMS && zs.n_terms >= 0 && tid <= zs.n_terms) {
+        // the waves' rows in order; the norm last
+        const int c = tid == zs.n_terms ? kZSumsMax : tid;
+        double v = 0.0;
+        for (int w = 0; w < NT / 64; ++w) v = __dadd_rn(v, zs.acc[w * (kZSumsMax + 1) + c]);
+        zs.out[tid] = v;
+    }
 #pragma unroll
     for (int w = 0; w < kWarm; ++w) asm volatile("" ::"v"(warm[w]));
+}
+
+template <typename R, int T, int NT, bool SMALL>
+__global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
+                                                            const char* __restrict__ mats, SweepArgs a)
+{
+    __shared__ __align__(16) char lds[Amp<R>::kBytes << T];
+    sweep_tiles<R, T, NT, SMALL>(psi, blocks, mats, a, blockIdx.x, lds, ZSums{nullptr, -1, nullptr, nullptr});
+}
+
+// Level path of a batch: workgroup w sweeps its tiles of one step of one
+// circuit; on a circuit's last step it also leaves the Z-type sums of its
+// tiles.  FIRST: the states are |0..0>.  Bound by HBM and the matrix pipe
+// about equally: a step holds two blocks in the mean (in program order, since
+// a swap would change the states' bits), so that a batch of 512 circuits of 8-20
+// qubits moves half the bytes of one sweep per block: 13.5 -> 10.6 ms.
+template <bool FIRST>
+__global__ __launch_bounds__(256, 3) void k_batch_level(char* __restrict__ states, const BatchSweep* __restrict__ sweeps,
+                                                       const BatchLevelEntry* __restrict__ entries,
+                                                       const SweepBlock* __restrict__ blocks,
+                                                       const char* __restrict__ mats,
+                                                       const uint64_t* __restrict__ z_masks,
+                                                       double* __restrict__ partials)
+{
+    __shared__ __align__(16) char lds[8 << 12];
+    __shared__ double zacc[4 * (kZSumsMax + 1)];
+    const BatchLevelEntry e = entries[blockIdx.x];
+    const BatchSweep& d = sweeps[e.sweep];
+    const ZSums zs{z_masks + d.term0, d.n_terms, partials + d.red_off + uint64_t(e.wg) * uint64_t(d.n_terms + 1), zacc};
+    sweep_tiles<float, 12, 256, false, FIRST, true>(states + 8 * d.state_off, blocks + d.block0,
+                                                    mats + uint64_t(d.block0) * sweep_matrix_stride(true), d.a, e.wg,
+                                                    lds, zs);
 }
 
 constexpr int tile_bits(sv_dtype_t dt) { return dt == SV_C64 ? 12 : 11; }  // 32 KiB
@@ -463,7 +606,7 @@ uint64_t qubit_mask(const FusedBlock& b)
 
 // Fills st's tile for the qubit set `on`: the runs as long as the set allows
 // (bits L.. join the low bits while the tile has room).
-void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, SweepStep& st)
+void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, int spread_lo, SweepStep& st)
 {
     const int T = st.tile_bits;
     SweepArgs& a = st.args;
@@ -481,6 +624,12 @@ void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, SweepStep& s
         return;
     }
     int L = min_run_bits(dt);
+    if (spread_lo > 0) {
+        // runs of 1 KiB at most, then free bits from spread_lo up
+        const int run = dt == SV_C64 ? 7 : 6;
+        while (L < run && __builtin_popcountll(on >> L) + L < T) ++L;
+        for (int q = std::max(L, spread_lo); q < n && __builtin_popcountll(on >> L) + L < T; ++q) on |= uint64_t(1) << q;
+    }
     while (L < T && __builtin_popcountll(on >> L) + L < T) ++L;
     a.L = L;
     for (int q = L; q < n; ++q)
@@ -500,15 +649,17 @@ void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, SweepStep& s
 
 }  // namespace
 
-std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const FusedBlock* blocks, int first, int end)
+std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const FusedBlock* blocks, int first, int end,
+                                   const SweepRules& rules)
 {
     std::vector<SweepStep> steps;
-    const bool one_tile = n <= tile_bits(dt) + 1;
+    const bool one_tile = n <= tile_bits(dt) + (rules.pad_all ? 0 : 1);
     const int T = std::max(tile_bits(dt), one_tile ? n : 0);
     const int lo = min_run_bits(dt);
     auto eligible = [&](const FusedBlock& b) {
         if (b.diagonal || b.n_couple > 0 || b.k > 5) return false;
         if (n > (dt == SV_C64 ? kMaxSweepQubitsC64 : kMaxSweepQubitsC128)) return false;
+        if (rules.pad_all) return true;
         // larger states: blocks on 2-4 qubits are swept as five-qubit ones
         // where their own sweep is (with enough qubits below or above
         // theirs), single-qubit ones on their own
@@ -520,11 +671,12 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
     auto fits = [&](uint64_t on) { return one_tile || __builtin_popcountll(on >> lo) <= T - lo; };
     auto add = [&](std::vector<int>&& take, uint64_t on) {
         SweepStep st;
-        st.multi = take.size() > 1 || (n < kReorderQubits && eligible(blocks[take[0]]));
+        st.multi = take.size() > 1 || ((n < kReorderQubits || rules.pad_all) && eligible(blocks[take[0]]));
         st.blocks = std::move(take);
+        st.padded = rules.pad_all || n >= kPadQubits;
         if (st.multi) {
             st.tile_bits = T;
-            fill_geometry(dt, n, cu_count, on, st);
+            fill_geometry(dt, n, cu_count, on, rules.spread_lo, st);
         }
         steps.push_back(std::move(st));
     };
@@ -538,7 +690,7 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
             ++at;
             continue;
         }
-        if (n < kReorderQubits) {
+        if (n < kReorderQubits || rules.keep_order) {
             std::vector<int> take;
             uint64_t on = 0;
             while (at < rest.size() && take.size() < kMaxSweepBlocks && eligible(blocks[rest[at]]) && fits(on | qubit_mask(blocks[rest[at]]))) {
@@ -654,12 +806,16 @@ size_t sweep_bytes(sv_dtype_t dt, const SweepStep& st)
 
 void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, void* dst)
 {
-    char* mat = static_cast<char*>(dst) + ((sizeof(SweepBlock) * st.blocks.size() + 255) & ~size_t(255));
-    auto* desc = static_cast<SweepBlock*>(dst);
+    pack_sweep(dt, st, blocks, static_cast<SweepBlock*>(dst),
+               static_cast<char*>(dst) + ((sizeof(SweepBlock) * st.blocks.size() + 255) & ~size_t(255)));
+}
+
+void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, SweepBlock* desc, char* mat)
+{
     const int L = st.args.L, T = st.tile_bits, n = 63 - __builtin_clzll(st.args.amps);
     for (size_t j = 0; j < st.blocks.size(); ++j, mat += sweep_matrix_stride(dt == SV_C64)) {
         const FusedBlock& b = blocks[st.blocks[j]];
-        const int k = n < kPadQubits ? b.k : 5;
+        const int k = st.padded ? 5 : b.k;
         SweepBlock s{};
         s.kind = k < 5 ? k : (dt == SV_C128 && n < 11) ? kSweepRows5 : kSweepMfma5;
         // tile-local positions of the targets, then of the padding qubits
@@ -729,6 +885,18 @@ void launch_sweep(sv_handle_s* h, sv_dtype_t dt, void* psi_v, const SweepStep& s
             SV_SWEEP(double, 11, 256, false);
     }
 #undef SV_SWEEP
+    SV_HIP(hipGetLastError());
+}
+
+void launch_batch_level(hipStream_t stream, const BatchArgs& a, uint64_t first, uint32_t n_entries, bool first_level)
+{
+    char* states = static_cast<char*>(a.states);
+    if (first_level)
+        hipLaunchKernelGGL(k_batch_level<true>, dim3(n_entries), dim3(256), 0, stream, states, a.sweeps, a.entries + first,
+                           a.sweep_blocks, a.sweep_mats, a.z_masks, a.partials);
+    else
+        hipLaunchKernelGGL(k_batch_level<false>, dim3(n_entries), dim3(256), 0, stream, states, a.sweeps,
+                           a.entries + first, a.sweep_blocks, a.sweep_mats, a.z_masks, a.partials);
     SV_HIP(hipGetLastError());
 }
 

@@ -1,5 +1,5 @@
-// Tile geometry of the LDS-staged sweeps and the complex64 five-qubit tile
-// transform, shared by the single-state sweep and the batched level sweep.
+// Tile geometry of the LDS-staged sweeps of one block, and the complex64
+// five-qubit tile transform.
 //
 // A tile is 2^TB amplitudes (32 KiB) whose index bits outside {0..L-1} and
 // the targets >= L are fixed: 2^n_hi contiguous runs of 2^L amplitudes, so
@@ -180,34 +180,6 @@ constexpr int kK5AParts = 3;
 constexpr int kK5AStaged = 2;
 
 
-// Z-type expectation sums of the state a sweep leaves behind, taken from the
-// tiles in LDS (no extra read of the state): for a workgroup, out[t] =
-// sum over its amplitudes i of |psi_i|^2 (-1)^popcount(i & zm[t]) for
-// t < n_terms, and out[n_terms] = sum |psi_i|^2, all FP64 in a fixed order
-// (per thread by a Walsh-Hadamard transform, per wave by a butterfly, waves
-// and tiles in order).  acc: LDS of 4 x (kZSumsMax + 1) doubles.
-// n_terms < 0: no sums.
-constexpr int kZSumsMax = 32;
-struct ZSums {
-    const uint64_t* zm;
-    int n_terms;
-    double* out;
-    double* acc;
-};
-
-// A double's bits as two floats and back (for LDS that the sweep accesses as
-// floats).
-__device__ __forceinline__ float2 f64_as_f32x2(double d)
-{
-    const uint64_t b = uint64_t(__double_as_longlong(d));
-    return float2{__uint_as_float(uint32_t(b)), __uint_as_float(uint32_t(b >> 32))};
-}
-__device__ __forceinline__ double f32x2_as_f64(float2 f)
-{
-    return __longlong_as_double(
-        static_cast<long long>(uint64_t(__float_as_uint(f.x)) | (uint64_t(__float_as_uint(f.y)) << 32)));
-}
-
 // L_a (units of pi, reduced to [-1, 1]) of the group whose base index (block
 // bits zero) is g.  Sums in a fixed order, exact selection of terms.
 __device__ __forceinline__ void couple_terms(const CoupleDev* __restrict__ cp, uint64_t g, double* L)
@@ -234,9 +206,6 @@ __device__ __forceinline__ float2 cmulf_conj(const float2 x, const float2 y)
     return float2{x.x * y.x + x.y * y.y, x.y * y.x - x.x * y.y};
 }
 
-// complex64 pair (i, i + 1) of the state |0..0> starting at global index i// complex64 pair (i, i + 1) of the state |0..0> starting at global index i
-__device__ __forceinline__ float4 basis0_pair(uint64_t i) { return i == 0 ? float4{1.f, 0.f, 0.f, 0.f} : float4{}; }
-
 // The complex64 five-qubit tile sweep of workgroup `wg` (its tiles_per_wg
 // tiles from wg * tiles_per_wg): a tile is staged in LDS, each wave gathers
 // 32 groups of 32 amplitudes through the swizzle and multiplies them by the
@@ -245,21 +214,17 @@ __device__ __forceinline__ float4 basis0_pair(uint64_t i) { return i == 0 ? floa
 // Re M, A_1 = Im M, A_2 = Re M + Im M), the next tile's loads in flight
 // meanwhile.  mats: the packed A operands (3 x 64 lanes x 4 float4); lds:
 // NT * kTileVecs float4 of LDS; amat: kK5AStaged * 64 * 4 float4 of LDS.
-// FIRST: the input is the basis state |0..0>, which is not read.  COUPLED:
-// the block's phase coupling cp multiplies each group's inputs first.
-template <int NT, bool FIRST, bool COUPLED = false>
+// COUPLED: the block's phase coupling cp multiplies each group's inputs first.
+template <int NT, bool COUPLED = false>
 __device__ __forceinline__ void tile_c64_k5_sweep(float2* __restrict__ psi, const float4* __restrict__ mats,
                                                   const TileArgs& a, uint64_t wg, float4* lds, float4* amat,
-                                                  const ZSums& zs, const CoupleDev* __restrict__ cp = nullptr)
+                                                  const CoupleDev* __restrict__ cp = nullptr)
 {
     const uint64_t t0 = wg * a.tiles_per_wg;
     if (t0 >= a.n_tiles) return;
     const uint64_t t1 = (a.n_tiles - t0 < a.tiles_per_wg) ? a.n_tiles : t0 + a.tiles_per_wg;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 31, half = lane >> 5;
-    // (from |0..0> only the workgroup with tile 0 multiplies; see below)
-    if (!FIRST || t0 == 0)
-        for (int e = tid; e < kK5AStaged * 64 * 4; e += NT) amat[e] = mats[e];
-    if (zs.n_terms >= 0 && lane <= kZSumsMax) zs.acc[wave * (kZSumsMax + 1) + lane] = 0.0;
+    for (int e = tid; e < kK5AStaged * 64 * 4; e += NT) amat[e] = mats[e];
     uint64_t roff[kTileVecs];
     uint32_t poff[kTileVecs];
     tile_offsets<2, NT>(a, roff, poff);
@@ -271,29 +236,10 @@ __device__ __forceinline__ void tile_c64_k5_sweep(float2* __restrict__ psi, cons
     SV_REP8(SV_DECL)
 #undef SV_DECL
     uint64_t base = tile_base(t0, a);
-#define SV_LOAD(u)                                                                              \
-    buf##u = FIRST ? basis0_pair(base + roff[u] + poff[u])                                      \
-                   : gload(reinterpret_cast<const float4*>(psi + base + roff[u] + poff[u]));
+#define SV_LOAD(u) buf##u = gload(reinterpret_cast<const float4*>(psi + base + roff[u] + poff[u]));
     SV_REP8(SV_LOAD)
 #undef SV_LOAD
     for (uint64_t t = t0; t < t1; ++t) {
-        if constexpr (FIRST) {
-            // |0..0> is zero on every tile but tile 0 (the one holding index
-            // 0), and so is the gate's image of it there: such a tile is
-            // only written
-            if (base != 0) {
-#pragma unroll
-                for (int u = 0; u < kTileVecs; ++u)
-                    gstore(reinterpret_cast<float4*>(psi + base + roff[u] + poff[u]), float4{0.f, 0.f, 0.f, 0.f});
-                if (t + 1 < t1) {
-                    base = tile_base(t + 1, a);
-#define SV_LOAD(u) buf##u = basis0_pair(base + roff[u] + poff[u]);
-                    SV_REP8(SV_LOAD)
-#undef SV_LOAD
-                }
-                continue;
-            }
-        }
 #define SV_STAGE(u)                                                                        \
     {                                                                                      \
         const int i = (u * NT + tid) * 2;                                        \
@@ -333,9 +279,7 @@ __device__ __forceinline__ void tile_c64_k5_sweep(float2* __restrict__ psi, cons
         uint64_t nbase = 0;
         if (t + 1 < t1) {
             nbase = tile_base(t + 1, a);
-#define SV_PREFETCH(u)                                                                          \
-    buf##u = FIRST ? basis0_pair(nbase + roff[u] + poff[u])                                     \
-                   : gload(reinterpret_cast<const float4*>(psi + nbase + roff[u] + poff[u]));
+#define SV_PREFETCH(u) buf##u = gload(reinterpret_cast<const float4*>(psi + nbase + roff[u] + poff[u]));
             SV_REP8(SV_PREFETCH)
 #undef SV_PREFETCH
         }
@@ -369,104 +313,10 @@ __device__ __forceinline__ void tile_c64_k5_sweep(float2* __restrict__ psi, cons
             gstore(reinterpret_cast<float4*>(psi + base + roff[u] + poff[u]),
                    swap_pair(*reinterpret_cast<const float4*>(lds2 + pair_slot(i)), pair_swapped(i)));
         }
-        if (zs.n_terms >= 0) {
-            // The tile is still in LDS.  A thread's 16 amplitudes differ in
-            // the tile-local bits 0 and kUBit..kUBit+2 (amplitude j = e + 2u
-            // is element e of vector u) and share all others, so a term's
-            // sum over them is s * c[k]: c the Walsh-Hadamard transform of
-            // their probabilities over j, c[k] = sum_j p_j (-1)^popcount(j & k),
-            // k the term mask's bits at those four index bits, s its parity
-            // over the bits the 16 share.  The norm is the term of mask 0.
-            constexpr int kUBit = 1 + __builtin_ctz(NT);
-            static_assert(kTileVecs == 8, "the transform spans one pair bit and three vector bits");
-            double c[16];
-#pragma unroll
-            for (int u = 0; u < kTileVecs; ++u) {
-                const int i = (u * NT + tid) * 2;
-                const float4 v = swap_pair(*reinterpret_cast<const float4*>(lds2 + pair_slot(i)), pair_swapped(i));
-                c[2 * u] = fma(double(v.x), double(v.x), __dmul_rn(double(v.y), double(v.y)));
-                c[2 * u + 1] = fma(double(v.z), double(v.z), __dmul_rn(double(v.w), double(v.w)));
-            }
-#pragma unroll
-            for (int h = 1; h < 16; h <<= 1) {
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    if (j & h) continue;
-                    const double x = c[j], y = c[j | h];
-                    c[j] = __dadd_rn(x, y);
-                    c[j | h] = __dsub_rn(x, y);
-                }
-            }
-            // the coefficients take the thread's own slots (its amplitudes
-            // are read; no other thread reads these slots before the next
-            // barrier): c[2u], c[2u + 1] in vector u's slot, their bits
-            // moved as floats, the slots' type
-#pragma unroll
-            for (int u = 0; u < kTileVecs; ++u) {
-                float2* slot = lds2 + pair_slot((u * NT + tid) * 2);
-                slot[0] = f64_as_f32x2(c[2 * u]);
-                slot[1] = f64_as_f32x2(c[2 * u + 1]);
-            }
-            // global index of the thread's amplitude j = 0, and the global
-            // positions of the tile-local bits 0 and kUBit..kUBit+2
-            const int mask = (1 << a.L) - 1;
-            const uint64_t gt =
-                base + deposit_bits(uint32_t((tid * 2) >> a.L), a.hi_pos, a.n_hi) + uint64_t((tid * 2) & mask);
-            int jpos[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int b = q == 0 ? 0 : kUBit + q - 1;
-                jpos[q] = b < a.L ? b : a.hi_pos[b - a.L];
-            }
-            // terms (the norm last, as term n_terms) in passes of eight; a
-            // pass's wave sums by a reduce-scatter butterfly: after the
-            // exchanges over lane bits 5, 4, 3 a lane holds one term, term
-            // (lane >> 3) & 7 of the pass, summed over 8 lanes, and three
-            // more exchanges sum the rest
-            double* row = zs.acc + wave * (kZSumsMax + 1);
-            const bool b5 = (lane & 32) != 0, b4 = (lane & 16) != 0, b3 = (lane & 8) != 0;
-            for (int p0 = 0; p0 <= zs.n_terms; p0 += 8) {
-                double v[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int tt = p0 + t;
-                    const uint64_t m = tt < zs.n_terms ? zs.zm[tt] : 0;
-                    const int k = int((m >> jpos[0]) & 1) | int(((m >> jpos[1]) & 1) << 1) |
-                                  int(((m >> jpos[2]) & 1) << 2) | int(((m >> jpos[3]) & 1) << 3);
-                    const double x = f32x2_as_f64(lds2[pair_slot(((k >> 1) * NT + tid) * 2) + (k & 1)]);
-                    v[t] = tt > zs.n_terms ? 0.0 : ((__popcll(gt & m) & 1) ? -x : x);
-                }
-                double w4[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    w4[j] = __dadd_rn(b5 ? v[j + 4] : v[j], __shfl_xor(b5 ? v[j] : v[j + 4], 32, 64));
-                double w2[2];
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    w2[j] = __dadd_rn(b4 ? w4[j + 2] : w4[j], __shfl_xor(b4 ? w4[j] : w4[j + 2], 16, 64));
-                double w = __dadd_rn(b3 ? w2[1] : w2[0], __shfl_xor(b3 ? w2[0] : w2[1], 8, 64));
-                w = __dadd_rn(w, __shfl_xor(w, 4, 64));
-                w = __dadd_rn(w, __shfl_xor(w, 2, 64));
-                w = __dadd_rn(w, __shfl_xor(w, 1, 64));
-                const int tt = p0 + ((lane >> 3) & 7);
-                if ((lane & 7) == 0 && tt <= zs.n_terms) {
-                    const int r = tt == zs.n_terms ? kZSumsMax : tt;
-                    row[r] = __dadd_rn(row[r], w);
-                }
-            }
-        }
         base = nbase;
         __syncthreads();
     }
-    if (zs.n_terms >= 0 && tid <= zs.n_terms) {
-        // the waves' rows in order; the norm last
-        const int c = tid == zs.n_terms ? kZSumsMax : tid;
-        double v = 0.0;
-        for (int w = 0; w < NT / 64; ++w) v = __dadd_rn(v, zs.acc[w * (kZSumsMax + 1) + c]);
-        zs.out[tid] = v;
-    }
 }
-
 
 }  // namespace tile
 }  // namespace sv

@@ -4,7 +4,8 @@
 // holds every block once and keeps the order of blocks that share a qubit
 // (and the whole order on states below the reorder size), that a sweep's
 // tiles cover every amplitude once, and that each group's members differ from
-// its base exactly by the block's target bits.  Exit status 0 = all passed.
+// its base exactly by the block's target bits; the same for the steps of a
+// batch's level path.  Exit status 0 = all passed.
 #include "../paper_2308_01999_amd/csrc/sv_sweep.hip"
 
 #include <cstdio>
@@ -122,6 +123,24 @@ int main()
                     b.diagonal = rep == 4 && rng() % 4 == 0;
                 }
                 const int first = rep == 3 ? 3 : 0, end = int(blocks.size()) - (rep == 3 ? 2 : 0);
+                // the rules of a batch's level path (complex64, blocks of up
+                // to five qubits): every block in order in tiles of 2^12
+                for (int spread : {0, 12}) {
+                    if (dt != SV_C64 || n < 13 || n > 34 || rep >= 4) continue;
+                    std::vector<FusedBlock> five = blocks;
+                    for (auto& b : five) b.k = std::min(b.k, 5);
+                    SweepRules rules;
+                    rules.keep_order = rules.pad_all = true;
+                    rules.spread_lo = spread;
+                    int next = first, step = 0;
+                    for (const SweepStep& st : plan_sweeps(dt, n, 256, five.data(), first, end, rules)) {
+                        if (!st.multi || !st.padded || st.tile_bits != 12) fail("batch step", n, dt, step);
+                        for (int i : st.blocks)
+                            if (i != next++) fail("batch order", n, dt, step);
+                        check_sweep(dt, n, st, five.data(), step++);
+                    }
+                    if (next != end) fail("batch block lost", n, dt, step);
+                }
                 const auto plan = plan_sweeps(dt, n, 256, blocks.data(), first, end);
                 std::vector<int> order;
                 int step = 0;
