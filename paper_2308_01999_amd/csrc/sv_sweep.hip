@@ -604,6 +604,15 @@ uint64_t qubit_mask(const FusedBlock& b)
     return m;
 }
 
+// The qubits that decide which blocks commute with b: its targets and the
+// qubits its phases depend on.
+uint64_t touched_mask(const FusedBlock& b)
+{
+    uint64_t m = qubit_mask(b);
+    for (int c = 0; c < b.n_couple; ++c) m |= uint64_t(1) << b.couple_q[c];
+    return m;
+}
+
 // Fills st's tile for the qubit set `on`: the runs as long as the set allows
 // (bits L.. join the low bits while the tile has room).
 void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, int spread_lo, SweepStep& st)
@@ -711,7 +720,7 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
         for (size_t s = at; s < hi && seeds < 8; ++s) {
             const uint64_t qs = qubit_mask(blocks[rest[s]]);
             const bool ready = !(qs & before) && eligible(blocks[rest[s]]);
-            before |= qs;
+            before |= touched_mask(blocks[rest[s]]);
             if (!ready) continue;
             ++seeds;
             std::vector<int> take{rest[s]};
@@ -731,7 +740,7 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
                             pick = int(j);
                         }
                     }
-                    blocked |= q;
+                    blocked |= touched_mask(blocks[rest[j]]);
                 }
                 if (pick < 0) break;
                 in[pick - at] = 1;

@@ -121,6 +121,12 @@ int main()
                     std::sort(b.targets, b.targets + b.k);
                     b.m = m.data();
                     b.diagonal = rep == 4 && rng() % 4 == 0;
+                    // phase couplings to qubits outside the targets
+                    if (rep == 1 && n > b.k && rng() % 2) {
+                        b.n_couple = 1;
+                        b.couple_q[0] = q[b.k + int(rng() % uint32_t(n - b.k))];
+                        b.couple = m.data();
+                    }
                 }
                 const int first = rep == 3 ? 3 : 0, end = int(blocks.size()) - (rep == 3 ? 2 : 0);
                 // the rules of a batch's level path (complex64, blocks of up
@@ -128,7 +134,7 @@ int main()
                 for (int spread : {0, 12}) {
                     if (dt != SV_C64 || n < 13 || n > 34 || rep >= 4) continue;
                     std::vector<FusedBlock> five = blocks;
-                    for (auto& b : five) b.k = std::min(b.k, 5);
+                    for (auto& b : five) b.k = std::min(b.k, 5), b.n_couple = 0;
                     SweepRules rules;
                     rules.keep_order = rules.pad_all = true;
                     rules.spread_lo = spread;
@@ -161,7 +167,12 @@ int main()
                         if (at[i] < at[j]) continue;
                         ++reordered;
                         if (n < 22) fail("order changed on a small state", n, dt, i);
-                        if (qubit_mask(blocks[i]) & qubit_mask(blocks[j])) fail("blocks on one qubit swapped", n, dt, i);
+                        auto touched = [&](const FusedBlock& b) {
+                            uint64_t t = qubit_mask(b);
+                            for (int c = 0; c < b.n_couple; ++c) t |= uint64_t(1) << b.couple_q[c];
+                            return t;
+                        };
+                        if (touched(blocks[i]) & touched(blocks[j])) fail("blocks on one qubit swapped", n, dt, i);
                     }
             }
     printf("sweeps %d reordered pairs %d fails %d\n", sweeps, reordered, fails);
