@@ -17,9 +17,17 @@ constexpr int32_t kSweepMfma5 = 5, kSweepRows5 = 6;
 // One block of a sweep (device).  Tile-local positions: index bit q of the
 // state below L is q, the others L plus their rank among the tile's high bits.
 struct SweepBlock {
-    uint32_t ins[5];   // group index -> tile-local base: the bits at and above each target, ascending
+    uint32_t bit[5];   // byte offset in the swizzled tile of each bit of the matrix index
     int32_t kind;
-    uint32_t off[32];  // byte offset of matrix index r in the swizzled tile
+    uint32_t grp[12];  // and of each bit of the group index
+    uint32_t pad[2];
+    // byte offset of matrix index r
+    __host__ __device__ __forceinline__ constexpr uint32_t off(int r) const
+    {
+        uint32_t o = 0;
+        for (int a = 0; a < 5; ++a) o ^= ((r >> a) & 1) ? bit[a] : 0u;
+        return o;
+    }
 };
 constexpr int kSweepBlockWords = int(sizeof(SweepBlock) / 4);
 static_assert(kSweepBlockWords <= 64, "a wave holds a descriptor, one word a lane");
@@ -49,6 +57,7 @@ struct SweepStep {
     std::vector<int> blocks;
     SweepArgs args{};
     bool padded = false;  // blocks of fewer than five qubits are swept as five-qubit ones
+    bool split = false;   // products of bf16 pieces (block5_split)
     int tile_bits = 0;
     int hi_pos[kSweepMaxHigh] = {};
 };

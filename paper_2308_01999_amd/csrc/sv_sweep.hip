@@ -8,24 +8,27 @@
 // one tile: its whole program runs in one launch of one workgroup.
 //
 // Per block, each wave gathers whole groups (the 2^k amplitudes a matrix
-// mixes) and multiplies them in the same order of operations as the
-// single-block sweeps (sv_tile.h, sv_apply.hip), so a state has the same bits
-// whichever sweep ran.
+// mixes).  Below 22 qubits it multiplies them in the same order of operations
+// as the single-block sweeps (sv_tile.h, sv_apply.hip), so a state has the same
+// bits whichever sweep ran.
 //
-// What bounds it: a block alone is bound by HBM (the 30-qubit complex64 sweep:
-// 2.9 ms).  In a sweep of several, the matrix cores take about 1.7 ms a block
-// there, and they share their issue slots with the vector ALUs (a vector
-// instruction costs the matrix pipe 2.7 cycles with several waves on a SIMD), so the
-// kernel keeps the address work to one XOR per LDS access.  32 KiB tiles and
-// 256 threads: the runs of 128 bytes that they leave for eight free bits
-// stream at 4.6-5.4 TB/s, and three workgroups a CU overlap one's loads with
-// another's products; tiles of 64 and 128 KiB (fewer sweeps) measured slower,
-// 2.4 and 2.5 ms for two blocks on 29 qubits against 2.35.
+// What bounds it: HBM for a block alone (30 qubits complex64: 2.9 ms), the matrix
+// cores for several.  A block costs a wave 48 MFMAs: of v_mfma_f32_32x32x2_f32
+// 3072 cycles (1.7 ms a block at 30 qubits), of v_mfma_f64_16x16x4_f64 the same,
+// of v_mfma_f32_32x32x16_bf16 1536 (block5_split, states of 22 qubits and
+// more).  A tile is 32 KiB and a workgroup 256 threads and one tile: the runs of 128
+// bytes that this leaves for eight free bits stream at 4.6-5.4 TB/s (64 and
+// 128 KiB tiles, fewer sweeps, measured slower), and four workgroups a CU, at most
+// 128 vector registers a thread, hide each other's loads, stores and
+// barriers.  They do it better than three that load their next tile during a
+// tile's blocks: loads return in order, so a matrix behind a tile waits for
+// HBM (28 qubits, sweeps of 4 blocks: complex64 1.38 -> 1.18 ms, complex128 on
+// 27 qubits 1.91 -> 1.83).
 // Measured, before (a sweep per block) and after: 30-qubit brickwork circuit
-// of depth 20, complex64, 52 blocks in 20 sweeps, 156 -> 115 ms; 28-qubit
-// random CNOT/CP circuit, complex128, 71 -> 53 ms; 19-qubit circuit on random
-// pairs, complex128, 660 -> 323 us; 14 qubits complex64 as a recorded graph,
-// 155 -> 92 us; 12 qubits complex128 194 -> 117 us.
+// of depth 20, complex64, 52 blocks in 20 sweeps, 156 -> 92 ms; 28-qubit
+// random CNOT/CP circuit, complex128, 71 -> 51 ms; 19-qubit circuit on random
+// pairs, complex128, 660 -> 310 us; 14 qubits complex64 as a recorded graph,
+// 155 -> 91 us; 12 qubits complex128 194 -> 117 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -44,12 +47,30 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// LDS slot of tile-local amplitude a: bits 1-4 XORed with bits 6-9.  Bit 0
-// stays, so a pair (i, i + 1) keeps its order and stages as one 16-byte
-// slot without a swap.  The XOR is linear over bits, so the slot of a group's
-// amplitude r is slot(base) ^ slot(off(r)): one XOR per access with the
-// host's swizzled offset as the scalar operand.
-__host__ __device__ __forceinline__ uint32_t slot(uint32_t a) { return a ^ ((a >> 5) & 30u); }
+// LDS slot of tile-local amplitude a: its low bits (5 of complex64's 8-byte
+// amplitudes, 4 of complex128's: the 64 banks) XORed with a vector for each
+// higher bit that is set.  It is linear over bits: the slot of a group's
+// amplitude r is slot(base) ^ slot(off(r)), one XOR per access with the
+// host's swizzled offset as the scalar operand.  complex64's vectors leave
+// bit 0 alone, so a pair (i, i + 1) keeps its order and stages as one 16-byte
+// slot.  An LDS access is as fast as the bank bits that its lanes reach: with
+// the vectors below a wave finds, for any five targets, lane bits among the
+// other tile bits (choose_lanes) for which a ds_read_b64 and a ds_write_b64
+// take 10.2 cycles in the mean and 12.3 at most (8.7 without any conflict), as
+// measured for each rank of the lanes' bits in the banks; the XOR of bits 1-4
+// with bits 6-9 and lanes on the lowest free bits took 13.7 and up to 48.
+constexpr uint32_t kSlot64[8] = {28, 26, 10, 18, 6, 14, 22, 30};      // of bits 5-12
+constexpr uint32_t kSlot128[9] = {11, 13, 7, 9, 3, 14, 12, 6, 10};    // of bits 4-12
+template <typename R>
+__host__ __device__ __forceinline__ constexpr uint32_t slot(uint32_t a)
+{
+    uint32_t r = a;
+    if constexpr (sizeof(R) == 4)
+        for (int p = 5; p < 13; ++p) r ^= (0u - ((a >> p) & 1u)) & kSlot64[p - 5];
+    else
+        for (int p = 4; p < 13; ++p) r ^= (0u - ((a >> p) & 1u)) & kSlot128[p - 4];
+    return r;
+}
 
 template <typename R>
 struct Amp;
@@ -77,14 +98,46 @@ __device__ __forceinline__ uint64_t tile_origin(uint64_t t, const SweepArgs& a)
     return t;
 }
 
-// Group index -> tile-local base: a zero inserted at each target position
-// (v + the bits at and above the position, which moves them up by one).
-template <int K>
-__device__ __forceinline__ uint32_t spread(uint32_t v, const uint32_t* ins)
+// An address of a uniform and a lane's 32-bit part, kept in that form: left
+// to itself the compiler adds the two in vector registers, two a load, and
+// holds them across the blocks.
+template <typename T>
+using Global = __attribute__((address_space(1))) T;
+template <typename T>
+__device__ __forceinline__ Global<T>* lane_address(const void* uniform, uint32_t lane_bytes)
 {
+    auto u = reinterpret_cast<uint64_t>(uniform);
+    asm volatile("" : "+s"(u), "+v"(lane_bytes));
+    return reinterpret_cast<Global<T>*>(reinterpret_cast<Global<char>*>(u) + lane_bytes);
+}
+
+// Masks of a lane's index bits (all ones where the bit is set).
+struct LaneBits {
+    uint32_t m[6];
+    __device__ __forceinline__ explicit LaneBits(int lane)
+    {
 #pragma unroll
-    for (int j = 0; j < K; ++j) v += v & ins[j];
-    return v;
+        for (int b = 0; b < 6; ++b) m[b] = 0u - ((uint32_t(lane) >> b) & 1u);
+    }
+};
+
+// Byte offset of a group in the swizzled tile: the lane's part (N bits of the
+// group index) and the part of the bits above, the same for the whole wave.
+template <int N>
+__device__ __forceinline__ uint32_t lane_part(const LaneBits& l, const uint32_t* grp)
+{
+    uint32_t o = 0;
+#pragma unroll
+    for (int b = 0; b < N; ++b) o ^= l.m[b] & grp[b];
+    return o;
+}
+template <int N>
+__device__ __forceinline__ uint32_t wave_part(uint32_t v, const uint32_t* grp)
+{
+    uint32_t o = 0;
+#pragma unroll
+    for (int b = 0; b < N; ++b) o ^= ((v >> b) & 1u) ? grp[b] : 0u;
+    return o;
 }
 
 // A lane's share of a five-qubit matrix, as pack5 lays it out.
@@ -98,9 +151,9 @@ struct Ops<float> {
     {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            re[q] = m[q * 64 + lane];
-            im[q] = m[256 + q * 64 + lane];
-            if (SUM) sum[q] = m[512 + q * 64 + lane];
+            re[q] = *lane_address<const f32x4>(m + q * 64, uint32_t(lane) * 16);
+            im[q] = *lane_address<const f32x4>(m + 256 + q * 64, uint32_t(lane) * 16);
+            if (SUM) sum[q] = *lane_address<const f32x4>(m + 512 + q * 64, uint32_t(lane) * 16);
         }
     }
 };
@@ -111,8 +164,8 @@ struct Ops<double> {
     {
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
-            re[h] = m[(rt * 4 + h) * 64 + lane];
-            im[h] = m[(8 + rt * 4 + h) * 64 + lane];
+            re[h] = *lane_address<const f64x2>(m + (rt * 4 + h) * 64, uint32_t(lane) * 16);
+            im[h] = *lane_address<const f64x2>(m + (8 + rt * 4 + h) * 64, uint32_t(lane) * 16);
         }
     }
     template <bool SUM>
@@ -132,48 +185,151 @@ struct Ops<double> {
 // `o` already.
 template <bool SUM, bool READY>
 __device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f32x4* __restrict__ m, Ops<float>& o,
-                                       uint32_t g0, int lane)
+                                       const LaneBits& lb, uint32_t wave, int lane)
 {
-    const int col = lane & 31, half = lane >> 5;
+    const int half = lane >> 5;
     if (!READY) o.load<SUM>(m, lane);
-    const uint32_t base = 8u * slot(spread<5>(uint32_t(col), b.ins)) ^ 8u * slot(spread<5>(g0, b.ins));
-    uint32_t in = base ^ (half ? b.off[1] : 0u), out = base ^ (half ? b.off[4] : 0u);
+    const uint32_t base = lane_part<5>(lb, b.grp) ^ wave_part<3>(wave, b.grp + 5);
+    uint32_t in = base ^ (half ? b.off(1) : 0u), out = base ^ (half ? b.off(4) : 0u);
     asm volatile("" : "+v"(in), "+v"(out));  // keep (base ^ half part) ^ uniform part: one XOR per access
-    f32x2 x[16];
+    f32x2 x[2][4];
+    auto fetch = [&](int q) {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) x[j] = *reinterpret_cast<const f32x2*>(lds + (in ^ b.off[2 * j]));
+        for (int jj = 0; jj < 4; ++jj) x[q & 1][jj] = *reinterpret_cast<const f32x2*>(lds + (in ^ b.off(2 * (4 * q + jj))));
+    };
+    fetch(0);
     f32x16 p1 = {0}, p2 = {0}, p3 = {0};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+        if (q < 3) fetch(q + 1);
         const f32x4 vs = SUM ? o.sum[q] : o.re[q] + o.im[q];
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
-            const f32x2 xv = x[4 * q + jj];
+            const f32x2 xv = x[q & 1][jj];
             p1 = __builtin_amdgcn_mfma_f32_32x32x2f32(o.re[q][jj], xv.x, p1, 0, 0, 0);
             p2 = __builtin_amdgcn_mfma_f32_32x32x2f32(o.im[q][jj], xv.y, p2, 0, 0, 0);
             p3 = __builtin_amdgcn_mfma_f32_32x32x2f32(vs[jj], xv.x + xv.y, p3, 0, 0, 0);
         }
+        if (!READY) __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-        *reinterpret_cast<f32x2*>(lds + (out ^ b.off[8 * (r / 4) + (r % 4)])) =
+        *reinterpret_cast<f32x2*>(lds + (out ^ b.off(8 * (r / 4) + (r % 4)))) =
             f32x2{p1[r] - p2[r], p3[r] - p1[r] - p2[r]};
 }
 
-// complex64, four qubits, on v_mfma_f32_16x16x4_f32 (the chain of
-// k_tile_c64_k4), `steps` column tiles of 16 groups per wave.
-__device__ __forceinline__ void block4(char* lds, const SweepBlock& b, const f32x4* __restrict__ m, uint32_t g0, int steps,
-                                       int lane)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y)
 {
-    const int col = lane & 15, q = lane >> 4;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x, y}), bf16x2));
+}
+
+// x and y as three bf16 each, exactly: x = x0 + x1 + x2, x0 = bf16(x), x1 =
+// bf16(x - x0), x2 the rest (24 bits in 8 + 8 + 8, both differences exact).
+__device__ __forceinline__ void split_bf16(float x, float y, uint32_t& w0, uint32_t& w1, uint32_t& w2)
+{
+    w0 = pack_bf16(x, y);
+    x -= __builtin_bit_cast(float, w0 << 16);
+    y -= __builtin_bit_cast(float, w0 & 0xffff0000u);
+    w1 = pack_bf16(x, y);
+    x -= __builtin_bit_cast(float, w1 << 16);
+    y -= __builtin_bit_cast(float, w1 & 0xffff0000u);
+    w2 = pack_bf16(x, y);
+}
+
+// One half (columns 16 s ...) of a lane's share of a matrix in pieces: three of
+// Re M, three of Im M.
+struct SplitOps {
+    u32x4 re[3], im[3];
+    __device__ __forceinline__ void load(const u32x4* __restrict__ m, int s, int lane)
+    {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            re[q] = *lane_address<const u32x4>(m + (q * 2 + s) * 64, uint32_t(lane) * 16);
+            im[q] = *lane_address<const u32x4>(m + (6 + q * 2 + s) * 64, uint32_t(lane) * 16);
+        }
+    }
+};
+
+// complex64, five qubits, on v_mfma_f32_32x32x16_bf16: matrix and amplitudes as
+// three bf16 each (together all 24 bits, at any exponent), and of their nine
+// products the six down to 2^-16 of the first, smallest first, summed in
+// FP32; the three left out are below 2^-26 of it, a quarter of an FP32
+// product's own rounding.  Four real products instead of the three of the FP32
+// kernels (Re M, Im M, Re M + Im M), whose differences cancel: of random
+// unitaries on random groups the error against 64 bits is 0.93e-7 in the mean
+// and 0.8e-6 at most of the group's 2-norm, theirs 1.55e-7 and 1.3e-6; of a
+// 30-qubit circuit's state 6.1e-7 against 9.9e-7.  A block costs 1536 cycles of the
+// matrix cores instead of 3072, and 270 vector instructions of which
+// 176 split the amplitudes (a difference as v_dot2_f32_bf16, one instruction for two,
+// was no gain: it takes the matrix cores' time).  In a sweep a block takes 0.18 ms
+// on 28 qubits, 0.41 on FP32.  A lane's outputs are its inputs' slots.  (Parts
+// below the smallest normal number may be dropped: an amplitude of less than 1e-33 keeps
+// an absolute error of 1e-38.)
+__device__ __forceinline__ void block5_split(char* lds, const SweepBlock& b, const u32x4* __restrict__ m,
+                                             const u32x4* __restrict__ next, SplitOps& o, const LaneBits& lb,
+                                             uint32_t wave, int lane)
+{
+    uint32_t at = lane_part<5>(lb, b.grp) ^ wave_part<2>(wave, b.grp + 5) ^ (lb.m[5] & b.off(4));
+    asm volatile("" : "+v"(at));
+    f32x16 re = {0}, im = {0};
+    // 16 columns: eight inputs of the lane, the six products of each pair of parts
+    auto half_sum = [&](int s) {
+        f32x2 x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = *reinterpret_cast<const f32x2*>(lds + (at ^ b.off(16 * s + 8 * (e / 4) + (e % 4))));
+        u32x4 xr[3], xi[3], xn[3];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const f32x2 u = x[2 * p], v = x[2 * p + 1];
+            uint32_t w0, w1, w2;
+            split_bf16(u.x, v.x, w0, w1, w2);
+            xr[0][p] = w0, xr[1][p] = w1, xr[2][p] = w2;
+            split_bf16(u.y, v.y, w0, w1, w2);
+            xi[0][p] = w0, xi[1][p] = w1, xi[2][p] = w2;
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) xn[q] = xi[q] ^ 0x80008000u;
+        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, px[6] = {0, 2, 1, 0, 1, 0};
+#define SV_MFMA(A, X, C) \
+    C = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A), __builtin_bit_cast(bf16x8, X), C, 0, 0, 0)
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            SV_MFMA(o.re[pa[i]], xr[px[i]], re);
+            SV_MFMA(o.re[pa[i]], xi[px[i]], im);
+            SV_MFMA(o.im[pa[i]], xn[px[i]], re);
+            SV_MFMA(o.im[pa[i]], xr[px[i]], im);
+        }
+#undef SV_MFMA
+        __builtin_amdgcn_sched_barrier(0);  // one half's operands at a time
+    };
+    half_sum(0);
+    o.load(m, 1, lane);
+    half_sum(1);
+    o.load(next, 0, lane);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        *reinterpret_cast<f32x2*>(lds + (at ^ b.off(8 * (r / 4) + (r % 4)))) = f32x2{re[r], im[r]};
+}
+
+// complex64, four qubits, on v_mfma_f32_16x16x4_f32 (the chain of
+// k_tile_c64_k4), four column tiles of 16 groups per wave.
+__device__ __forceinline__ void block4(char* lds, const SweepBlock& b, const f32x4* __restrict__ m, const LaneBits& lb,
+                                       uint32_t wave, int lane)
+{
+    constexpr int steps = 4;
+    const int q = lane >> 4;
     const f32x4 ar = m[lane], ai = m[64 + lane], as = m[128 + lane];
-    const uint32_t lin = ((q & 1) ? b.off[1] : 0u) ^ ((q & 2) ? b.off[2] : 0u);
-    const uint32_t lout = ((q & 1) ? b.off[4] : 0u) ^ ((q & 2) ? b.off[8] : 0u);
+    const uint32_t lin = ((q & 1) ? b.off(1) : 0u) ^ ((q & 2) ? b.off(2) : 0u);
+    const uint32_t lout = ((q & 1) ? b.off(4) : 0u) ^ ((q & 2) ? b.off(8) : 0u);
     for (int c = 0; c < steps; ++c) {
-        const uint32_t base = 8u * slot(spread<4>(g0 + uint32_t(c * 16 + col), b.ins));
+        const uint32_t base = lane_part<4>(lb, b.grp) ^ wave_part<5>(wave * steps + uint32_t(c), b.grp + 4);
         f32x2 x[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) x[s] = *reinterpret_cast<const f32x2*>(lds + (base ^ lin ^ b.off[4 * s]));
+        for (int s = 0; s < 4; ++s) x[s] = *reinterpret_cast<const f32x2*>(lds + (base ^ lin ^ b.off(4 * s)));
         f32x4 p1 = {0}, p2 = {0}, p3 = {0};
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -183,7 +339,7 @@ __device__ __forceinline__ void block4(char* lds, const SweepBlock& b, const f32
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            *reinterpret_cast<f32x2*>(lds + (base ^ lout ^ b.off[r])) = f32x2{p1[r] - p2[r], p3[r] - p1[r] - p2[r]};
+            *reinterpret_cast<f32x2*>(lds + (base ^ lout ^ b.off(r))) = f32x2{p1[r] - p2[r], p3[r] - p1[r] - p2[r]};
     }
 }
 
@@ -192,15 +348,13 @@ __device__ __forceinline__ void block4(char* lds, const SweepBlock& b, const f32
 // inputs are matrix columns 4s + q, its outputs rows 16 rt + 4v + q.
 template <bool SUM, bool READY>
 __device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f64x2* __restrict__ m, Ops<double>& o,
-                                       uint32_t g0, int lane)
+                                       const LaneBits& lb, uint32_t wave, int lane)
 {
-    const int col = lane & 15, q = lane >> 4;
-    const uint32_t base = 16u * slot(spread<5>(uint32_t(col), b.ins)) ^ 16u * slot(spread<5>(g0, b.ins));
-    uint32_t at = base ^ ((q & 1) ? b.off[1] : 0u) ^ ((q & 2) ? b.off[2] : 0u);
+    uint32_t at = lane_part<4>(lb, b.grp) ^ wave_part<3>(wave, b.grp + 4) ^ (lb.m[4] & b.off(1)) ^ (lb.m[5] & b.off(2));
     asm volatile("" : "+v"(at));
     f64x2 x[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) x[s] = *reinterpret_cast<const f64x2*>(lds + (at ^ b.off[4 * s]));
+    for (int s = 0; s < 8; ++s) x[s] = *reinterpret_cast<const f64x2*>(lds + (at ^ b.off(4 * s)));
     Ops<double> second;
     if (READY) second.load_rows(m, lane, 1);
     auto rows = [&](int rt, const Ops<double>& w) {
@@ -214,29 +368,32 @@ __device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f64
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            *reinterpret_cast<f64x2*>(lds + (at ^ b.off[16 * rt + 4 * v])) =
+            *reinterpret_cast<f64x2*>(lds + (at ^ b.off(16 * rt + 4 * v))) =
                 f64x2{p1[v] - p2[v], p3[v] - p1[v] - p2[v]};
     };
     if (!READY) o.load_rows(m, lane, 0);
     rows(0, o);
-    if (!READY) second.load_rows(m, lane, 1);
+    if (!READY) {
+        __builtin_amdgcn_sched_barrier(0);
+        second.load_rows(m, lane, 1);
+    }
     rows(1, second);
 }
 
 // k <= 3 (complex64) or k <= 4 (complex128) on the vector units, one group
 // per thread and step, in the order of k_apply_dense.
-template <typename R, int K>
+template <typename R, int K, int T, int NT>
 __device__ __forceinline__ void block_small(char* lds, const SweepBlock& b, const typename Amp<R>::V* __restrict__ m,
-                                            uint32_t groups, int nt)
+                                            const LaneBits& lb, uint32_t wave)
 {
     using V = typename Amp<R>::V;
     constexpr int D = 1 << K;
-    for (uint32_t g = threadIdx.x; g < groups; g += uint32_t(nt)) {
+    for (uint32_t w = wave; w < (1u << (T - K - 6)); w += NT / 64) {
         asm volatile("" ::: "memory");  // the matrix stays out of the registers
-        const uint32_t base = Amp<R>::kBytes * slot(spread<K>(g, b.ins));
+        const uint32_t base = lane_part<6>(lb, b.grp) ^ wave_part<T - K - 6>(w, b.grp + 6);
         V v[D];
 #pragma unroll
-        for (int c = 0; c < D; ++c) v[c] = *reinterpret_cast<const V*>(lds + (base ^ b.off[c]));
+        for (int c = 0; c < D; ++c) v[c] = *reinterpret_cast<const V*>(lds + (base ^ b.off(c)));
 #pragma unroll
         for (int r = 0; r < D; ++r) {
             R re = 0, im = 0;
@@ -248,7 +405,7 @@ __device__ __forceinline__ void block_small(char* lds, const SweepBlock& b, cons
                 im = fma(e.x, v[c].y, im);
                 im = fma(e.y, v[c].x, im);
             }
-            *reinterpret_cast<V*>(lds + (base ^ b.off[r])) = V{re, im};
+            *reinterpret_cast<V*>(lds + (base ^ b.off(r))) = V{re, im};
         }
     }
 }
@@ -256,12 +413,13 @@ __device__ __forceinline__ void block_small(char* lds, const SweepBlock& b, cons
 // complex128, five qubits, states of fewer than 11 qubits: on the vector units
 // in the order of k_apply_dense, one group per lane and 8 rows per wave (64
 // groups, four waves).  Every wave reads its groups' inputs before any writes.
-__device__ __forceinline__ void block5_rows(char* lds, const SweepBlock& b, const f64x2* __restrict__ m, int wave, int lane)
+__device__ __forceinline__ void block5_rows(char* lds, const SweepBlock& b, const f64x2* __restrict__ m,
+                                            const LaneBits& lb, int wave)
 {
-    const uint32_t base = 16u * slot(spread<5>(uint32_t(lane), b.ins));
+    const uint32_t base = lane_part<6>(lb, b.grp);
     f64x2 v[32], y[8];
 #pragma unroll
-    for (int c = 0; c < 32; ++c) v[c] = *reinterpret_cast<const f64x2*>(lds + (base ^ b.off[c]));
+    for (int c = 0; c < 32; ++c) v[c] = *reinterpret_cast<const f64x2*>(lds + (base ^ b.off(c)));
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         const f64x2* row = m + (wave * 8 + r) * 32;
@@ -277,19 +435,35 @@ __device__ __forceinline__ void block5_rows(char* lds, const SweepBlock& b, cons
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) *reinterpret_cast<f64x2*>(lds + (base ^ b.off[wave * 8 + r])) = y[r];
+    for (int r = 0; r < 8; ++r) *reinterpret_cast<f64x2*>(lds + (base ^ b.off(wave * 8 + r))) = y[r];
+}
+
+// The first 16 words of a block's descriptor (all that a five-qubit block
+// needs) in scalar registers, by one load: left to itself the compiler loads
+// words one by one where they are used.
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ u32x16 load_words(const SweepBlock* p) { return *reinterpret_cast<const u32x16*>(p); }
+__device__ __forceinline__ SweepBlock block_of(const u32x16& w)
+{
+    SweepBlock b{};
+#pragma unroll
+    for (int j = 0; j < 5; ++j) b.bit[j] = w[j];
+    b.kind = int32_t(w[5]);
+#pragma unroll
+    for (int j = 0; j < 10; ++j) b.grp[j] = w[6 + j];
+    return b;
 }
 
 // A block's descriptor from the wave's copy of it (lane l holds word l).
 __device__ __forceinline__ SweepBlock unpack_block(uint32_t words)
 {
     auto word = [&](int i) { return uint32_t(__builtin_amdgcn_readlane(int(words), i)); };
-    SweepBlock b;
+    SweepBlock b{};
 #pragma unroll
-    for (int j = 0; j < 5; ++j) b.ins[j] = word(j);
+    for (int j = 0; j < 5; ++j) b.bit[j] = word(j);
     b.kind = int32_t(word(5));
 #pragma unroll
-    for (int r = 0; r < 32; ++r) b.off[r] = word(6 + r);
+    for (int j = 0; j < 12; ++j) b.grp[j] = word(6 + j);
     return b;
 }
 
@@ -319,10 +493,11 @@ __device__ __forceinline__ void add_z_sums(char* lds, const SweepArgs& a, const 
 {
     constexpr int NT = 256;
     const int lane = tid & 63, wave = tid >> 6;
+    const uint32_t at = 8u * slot<float>(uint32_t(tid) * 2);
     double c[16];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(lds + 8u * slot(uint32_t(u * NT + tid) * 2));
+        const f32x4 v = *reinterpret_cast<const f32x4*>(lds + (at ^ 8u * slot<float>(uint32_t(u * NT) * 2)));
         c[2 * u] = fma(double(v.x), double(v.x), __dmul_rn(double(v.y), double(v.y)));
         c[2 * u + 1] = fma(double(v.z), double(v.z), __dmul_rn(double(v.w), double(v.w)));
     }
@@ -340,7 +515,7 @@ __device__ __forceinline__ void add_z_sums(char* lds, const SweepArgs& a, const 
     // no other thread reads these slots before the next barrier)
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-        *reinterpret_cast<f64x2*>(lds + 8u * slot(uint32_t(u * NT + tid) * 2)) = f64x2{c[2 * u], c[2 * u + 1]};
+        *reinterpret_cast<f64x2*>(lds + (at ^ 8u * slot<float>(uint32_t(u * NT) * 2))) = f64x2{c[2 * u], c[2 * u + 1]};
     int jpos[4];  // index bits of the tile-local bits 0 and 9-11
 #pragma unroll
     for (int q = 0; q < 4; ++q) jpos[q] = __builtin_ctzll(a.bit_off[q == 0 ? 0 : 8 + q]) - 3;
@@ -359,7 +534,7 @@ __device__ __forceinline__ void add_z_sums(char* lds, const SweepArgs& a, const 
             const int k = int((m >> jpos[0]) & 1) | int(((m >> jpos[1]) & 1) << 1) | int(((m >> jpos[2]) & 1) << 2) |
                           int(((m >> jpos[3]) & 1) << 3);
             const double x =
-                *reinterpret_cast<const double*>(lds + 8u * slot(uint32_t((k >> 1) * NT + tid) * 2) + 8 * (k & 1));
+                *reinterpret_cast<const double*>(lds + (at ^ 8u * slot<float>(uint32_t((k >> 1) * NT) * 2)) + 8 * (k & 1));
             v[t] = tt > zs.n_terms ? 0.0 : ((__popcll(i0 & m) & 1) ? -x : x);
         }
         double w4[4];
@@ -387,7 +562,7 @@ __device__ __forceinline__ void add_z_sums(char* lds, const SweepArgs& a, const 
 // fewer than five qubits on the vector units; a state of less than a tile
 // leaves the rest of it zeros that no one stores.  FIRST: the state is |0..0>
 // and is not read.  zs: complex64 sweeps of 256 threads only.
-template <typename R, int T, int NT, bool SMALL, bool FIRST = false, bool SUMS = false>
+template <typename R, int T, int NT, bool SMALL, bool SPLIT = false, bool FIRST = false, bool SUMS = false>
 __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
                                             const char* __restrict__ mats, const SweepArgs& a, uint64_t wg,
                                             char* lds, const ZSums& zs)
@@ -422,16 +597,8 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
         for (int b = 0; b < 3; ++b)
             if ((u >> b) & 1) roff[u] += a.bit_off[kU0 + b];
     }
-    char* base = psi + A::kBytes * tile_origin(t0, a);
-    W buf[NV];
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-        if (FIRST || (SMALL && uint64_t(u * NT + tid) * A::kPerVec >= a.amps))
-            buf[u] = W{};
-        else
-            buf[u] = __builtin_nontemporal_load(reinterpret_cast<const W*>(base + roff[u] + loff));
-    }
-    if (FIRST && base == psi && tid == 0) buf[0][0] = 1;
+    const uint32_t staged = A::kBytes * slot<R>(uint32_t(tid) * A::kPerVec);
+    const LaneBits lb(lane);
     // few workgroups: the descriptors and matrices of all blocks are brought
     // to the L2 at once (one word of each 128-byte line), not block by block
     // (14 qubits complex64 as a graph: 104 -> 92 us, with the offsets of a
@@ -447,31 +614,44 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
     }
     auto matrix = [&](int i) { return reinterpret_cast<const W*>(mats + uint64_t(i) * kStride); };
     for (uint64_t t = t0; t < t1; ++t) {  // (SMALL: once)
+        char* base = psi + A::kBytes * tile_origin(t, a);
         if (FIRST && base != psi) {
             // |0..0> is zero on every tile but the first, and so is its image:
             // such a tile is only written
 #pragma unroll
-            for (int u = 0; u < NV; ++u) __builtin_nontemporal_store(W{}, reinterpret_cast<W*>(base + roff[u] + loff));
-            if (t + 1 < t1) base = psi + A::kBytes * tile_origin(t + 1, a);
+            for (int u = 0; u < NV; ++u) __builtin_nontemporal_store(W{}, lane_address<W>(base + roff[u], loff));
             continue;
         }
+        W buf[NV];
+#pragma unroll
+        for (int u = 0; u < NV; ++u) {
+            if (FIRST || (SMALL && uint64_t(u * NT + tid) * A::kPerVec >= a.amps))
+                buf[u] = W{};
+            else
+                buf[u] = __builtin_nontemporal_load(lane_address<const W>(base + roff[u], loff));
+        }
+        if (FIRST && tid == 0) buf[0][0] = 1;
 #pragma unroll
         for (int u = 0; u < NV; ++u)
-            *reinterpret_cast<W*>(lds + A::kBytes * slot(uint32_t(u * NT + tid) * A::kPerVec)) = buf[u];
+            *reinterpret_cast<W*>(lds + (staged ^ A::kBytes * slot<R>(uint32_t(u * NT) * A::kPerVec))) = buf[u];
         __syncthreads();
-        char* nbase = base;
-        if (!SMALL && t + 1 < t1) {
-            nbase = psi + A::kBytes * tile_origin(t + 1, a);
-            if (!FIRST) {
-#pragma unroll
-                for (int u = 0; u < NV; ++u)
-                    buf[u] = __builtin_nontemporal_load(reinterpret_cast<const W*>(nbase + roff[u] + loff));
-            }
-        }
         if constexpr (!SMALL) {
+            // the next block's descriptor is on its way during a block
+            u32x16 w = load_words(blocks);
+            [[maybe_unused]] SplitOps split;
+            if constexpr (SPLIT) split.load(reinterpret_cast<const u32x4*>(mats), 0, lane);
             for (int i = 0; i < a.n_blocks; ++i) {
-                Ops<R> o;
-                block5<false, false>(lds, blocks[i], matrix(i), o, uint32_t(wave * kCols), lane);
+                const int next = i + 1 < a.n_blocks ? i + 1 : i;
+                asm volatile("" : "+s"(w));
+                const SweepBlock b = block_of(w);
+                w = load_words(blocks + next);
+                if constexpr (SPLIT) {
+                    block5_split(lds, b, reinterpret_cast<const u32x4*>(matrix(i)),
+                                 reinterpret_cast<const u32x4*>(matrix(next)), split, lb, uint32_t(wave), lane);
+                } else {
+                    Ops<R> o;
+                    block5<false, false>(lds, b, matrix(i), o, lb, uint32_t(wave), lane);
+                }
                 __syncthreads();
             }
         } else {
@@ -490,20 +670,20 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
                 dw = words(i + 2);
                 if (i + 1 < a.n_blocks) next.template load<true>(matrix(i + 1), lane);
                 if (b.kind == kSweepMfma5) {
-                    block5<true, true>(lds, b, matrix(i), now, uint32_t(wave * kCols), lane);
+                    block5<true, true>(lds, b, matrix(i), now, lb, uint32_t(wave), lane);
                     return;
                 }
                 const auto* mv = reinterpret_cast<const typename A::V*>(matrix(i));
                 if constexpr (sizeof(R) == 8 && NT == 256)
-                    if (b.kind == kSweepRows5) block5_rows(lds, blocks[i], mv, wave, lane);
-                if (b.kind == 1) block_small<R, 1>(lds, b, mv, 1u << (T - 1), NT);
-                if (b.kind == 2) block_small<R, 2>(lds, b, mv, 1u << (T - 2), NT);
-                if (b.kind == 3) block_small<R, 3>(lds, b, mv, 1u << (T - 3), NT);
+                    if (b.kind == kSweepRows5) block5_rows(lds, b, mv, lb, wave);
+                if (b.kind == 1) block_small<R, 1, T, NT>(lds, b, mv, lb, uint32_t(wave));
+                if (b.kind == 2) block_small<R, 2, T, NT>(lds, b, mv, lb, uint32_t(wave));
+                if (b.kind == 3) block_small<R, 3, T, NT>(lds, b, mv, lb, uint32_t(wave));
                 if (b.kind == 4) {
                     if constexpr (sizeof(R) == 8)
-                        block_small<R, 4>(lds, b, mv, 1u << (T - 4), NT);
+                        block_small<R, 4, T, NT>(lds, b, mv, lb, uint32_t(wave));
                     else
-                        block4(lds, b, matrix(i), uint32_t(wave * 64), 4, lane);
+                        block4(lds, b, matrix(i), lb, uint32_t(wave), lane);
                 }
             };
             for (int i = 0; i < a.n_blocks; i += 2) {
@@ -518,12 +698,11 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
         for (int u = 0; u < NV; ++u) {
             if (SMALL && uint64_t(u * NT + tid) * A::kPerVec >= a.amps) continue;
             __builtin_nontemporal_store(
-                *reinterpret_cast<const W*>(lds + A::kBytes * slot(uint32_t(u * NT + tid) * A::kPerVec)),
-                reinterpret_cast<W*>(base + roff[u] + loff));
+                *reinterpret_cast<const W*>(lds + (staged ^ A::kBytes * slot<R>(uint32_t(u * NT) * A::kPerVec))),
+                lane_address<W>(base + roff[u], loff));
         }
         if constexpr (SUMS)
             if (zs.n_terms >= 0) add_z_sums(lds, a, zs, uint64_t(base - psi + int64_t(roff[0]) + loff) / A::kBytes, tid);
-        base = nbase;
         __syncthreads();
     }
     if (SUMS && zs.n_terms >= 0 && tid <= zs.n_terms) {
@@ -537,12 +716,12 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
     for (int w = 0; w < kWarm; ++w) asm volatile("" ::"v"(warm[w]));
 }
 
-template <typename R, int T, int NT, bool SMALL>
-__global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
+template <typename R, int T, int NT, bool SMALL, bool SPLIT = false>
+__global__ __launch_bounds__(NT, SMALL ? 1 : 4) void k_sweep(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
                                                             const char* __restrict__ mats, SweepArgs a)
 {
     __shared__ __align__(16) char lds[Amp<R>::kBytes << T];
-    sweep_tiles<R, T, NT, SMALL>(psi, blocks, mats, a, blockIdx.x, lds, ZSums{nullptr, -1, nullptr, nullptr});
+    sweep_tiles<R, T, NT, SMALL, SPLIT>(psi, blocks, mats, a, blockIdx.x, lds, ZSums{nullptr, -1, nullptr, nullptr});
 }
 
 // Level path of a batch: workgroup w sweeps its tiles of one step of one
@@ -552,7 +731,7 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 3) void k_sweep(char* __restrict__ 
 // a swap would change the states' bits), so that a batch of 512 circuits of 8-20
 // qubits moves half the bytes of one sweep per block: 13.5 -> 10.6 ms.
 template <bool FIRST>
-__global__ __launch_bounds__(256, 3) void k_batch_level(char* __restrict__ states, const BatchSweep* __restrict__ sweeps,
+__global__ __launch_bounds__(256, 4) void k_batch_level(char* __restrict__ states, const BatchSweep* __restrict__ sweeps,
                                                        const BatchLevelEntry* __restrict__ entries,
                                                        const SweepBlock* __restrict__ blocks,
                                                        const char* __restrict__ mats,
@@ -564,7 +743,7 @@ __global__ __launch_bounds__(256, 3) void k_batch_level(char* __restrict__ state
     const BatchLevelEntry e = entries[blockIdx.x];
     const BatchSweep& d = sweeps[e.sweep];
     const ZSums zs{z_masks + d.term0, d.n_terms, partials + d.red_off + uint64_t(e.wg) * uint64_t(d.n_terms + 1), zacc};
-    sweep_tiles<float, 12, 256, false, FIRST, true>(states + 8 * d.state_off, blocks + d.block0,
+    sweep_tiles<float, 12, 256, false, false, FIRST, true>(states + 8 * d.state_off, blocks + d.block0,
                                                     mats + uint64_t(d.block0) * sweep_matrix_stride(true), d.a, e.wg,
                                                     lds, zs);
 }
@@ -580,7 +759,8 @@ constexpr int kPadQubits = 14;
 
 // Smallest state whose blocks may pass blocks on other qubits on their way
 // into a sweep (below, a program's blocks keep their order and its amplitudes
-// their bits).
+// their bits), and whose complex64 sweeps multiply bf16 parts (block5_split): a
+// state of 22 qubits is the first that keeps every CU's matrix cores busy.
 constexpr int kReorderQubits = 22;
 constexpr int kReorderWindow = 96;
 
@@ -649,11 +829,8 @@ void fill_geometry(sv_dtype_t dt, int n, int cu_count, uint64_t on, int spread_l
         }
     a.lg_tiles = n - T;
     a.n_tiles = uint64_t(1) << a.lg_tiles;
-    uint64_t per = a.n_tiles / (uint64_t(cu_count) * SV_TILE_WGS_PER_CU);
-    per = std::max<uint64_t>(1, std::min<uint64_t>(per, SV_TILES_PER_WG_MAX_K5));
-    a.tiles_per_wg = per;
-    if ((per & (per - 1)) == 0)
-        while ((uint64_t(1) << a.trot) < per) ++a.trot;
+    // one tile a workgroup: four fit a CU and hide each other's loads and stores
+    a.tiles_per_wg = 1;
 }
 
 }  // namespace
@@ -683,6 +860,7 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
         st.multi = take.size() > 1 || ((n < kReorderQubits || rules.pad_all) && eligible(blocks[take[0]]));
         st.blocks = std::move(take);
         st.padded = rules.pad_all || n >= kPadQubits;
+        st.split = dt == SV_C64 && n >= kReorderQubits && !rules.keep_order;
         if (st.multi) {
             st.tile_bits = T;
             fill_geometry(dt, n, cu_count, on, rules.spread_lo, st);
@@ -765,6 +943,46 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
 
 namespace {
 
+uint32_t slot_bytes(sv_dtype_t dt, uint32_t a) { return dt == SV_C64 ? 8u * slot<float>(a) : 16u * slot<double>(a); }
+
+// Byte offsets of the group index's bits: the tile bits outside `used`, the
+// lanes' first.  The first 4 (complex64; complex128 3) lane bits are to be
+// independent in the 32 banks a write sees, and one more with them in the 64
+// of a read, as far as there are such bits.
+void choose_lanes(sv_dtype_t dt, int T, uint32_t used, uint32_t* grp)
+{
+    const int width = dt == SV_C64 ? 5 : 4;
+    uint32_t left = ((1u << T) - 1u) & ~used;
+    // the vectors taken, reduced: basis[i] has its top bit at i
+    uint32_t low[5] = {}, full[5] = {};
+    auto add = [](uint32_t* basis, uint32_t v) {
+        while (v) {
+            const int i = 31 - __builtin_clz(v);
+            if (!basis[i]) {
+                basis[i] = v;
+                return true;
+            }
+            v ^= basis[i];
+        }
+        return false;
+    };
+    int n = 0;
+    auto take = [&](int p) {
+        left &= ~(1u << p);
+        grp[n++] = slot_bytes(dt, 1u << p);
+    };
+    auto bank = [&](int p) { return (dt == SV_C64 ? slot<float>(1u << p) : slot<double>(1u << p)) & ((1u << width) - 1u); };
+    for (int p = 0; p < T && n < width - 1; ++p)
+        if (((left >> p) & 1) && add(low, bank(p) & ((1u << (width - 1)) - 1u))) {
+            add(full, bank(p));
+            take(p);
+        }
+    for (int p = 0; p < T && n < width; ++p)
+        if (((left >> p) & 1) && add(full, bank(p))) take(p);
+    for (int p = 0; p < T; ++p)
+        if ((left >> p) & 1) take(p);
+}
+
 // Place of matrix entry (i, c) in a part of the packed operands.  complex64:
 // float4 [q][lane] of A[i][2(4q + j) + half], lane = i + 32 half; complex128:
 // double2 [rt 4 + s/2][lane] of A[16 rt + i][4s + q], lane = i + 16 q.
@@ -803,6 +1021,31 @@ void pack5(const FusedBlock& b, int n, R* o)
                 if (sizeof(R) == 4) o[2048 + to[c]] = n < 12 ? R(row[2 * c] + row[2 * c + 1]) : re + im;
             }
         }
+}
+
+// The operands of block5_split: part (Re M, Im M), piece, half of the columns
+// s, lane: row lane % 32, columns 8 (2 s + e / 4) + 4 (lane / 32) + e % 4 for e < 8.
+void pack5_split(const FusedBlock& b, uint16_t* o)
+{
+    const int d = 1 << b.k;
+    std::fill(o, o + 6 * 1024, uint16_t(0));
+    for (int e = 0; e < 32; e += d)  // the diagonal blocks of M (x) I
+        for (int i = 0; i < d; ++i)
+            for (int c = 0; c < d; ++c)
+                for (int part = 0; part < 2; ++part) {
+                    const int row = e + i, j = e + c;
+                    const int at = ((j >> 4) * 64 + row + 32 * ((j >> 2) & 1)) * 8 + ((j >> 3) & 1) * 4 + (j & 3);
+                    float v = float(b.m[2 * (size_t(i) * d + c) + part]);
+                    for (int q = 0; q < 3; ++q) {
+                        uint32_t w;
+                        std::memcpy(&w, &v, 4);
+                        w = (w + 0x7fffu + ((w >> 16) & 1u)) & 0xffff0000u;
+                        o[(part * 3 + q) * 1024 + at] = uint16_t(w >> 16);
+                        float f;
+                        std::memcpy(&f, &w, 4);
+                        v -= f;
+                    }
+                }
 }
 
 }  // namespace
@@ -846,20 +1089,15 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, Sw
                 pos[a++] = p;
                 used |= 1u << p;
             }
-        int w = 0;
-        for (int p = 0; p < T; ++p)
-            if ((used >> p) & 1) s.ins[w++] = ~((1u << p) - 1u);
-        for (int r = 0; r < (1 << k); ++r) {
-            uint32_t o = 0;
-            for (int a = 0; a < k; ++a)
-                if ((r >> a) & 1) o |= 1u << pos[a];
-            s.off[r] = (dt == SV_C64 ? 8u : 16u) * slot(o);
-        }
+        choose_lanes(dt, T, used, s.grp);
+        for (int a = 0; a < k; ++a) s.bit[a] = slot_bytes(dt, 1u << pos[a]);
         desc[j] = s;
         if (s.kind == kSweepRows5)
             std::memcpy(mat, b.m, 1024 * 2 * sizeof(double));
         else if (k < 5)
             pack_matrix(dt, 12, k, 0, b.m, 0, mat);
+        else if (st.split)
+            pack5_split(b, reinterpret_cast<uint16_t*>(mat));
         else if (dt == SV_C64)
             pack5(b, n, reinterpret_cast<float*>(mat));
         else
@@ -876,13 +1114,15 @@ void launch_sweep(sv_handle_s* h, sv_dtype_t dt, void* psi_v, const SweepStep& s
     const dim3 grid{unsigned((a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg)};
     const bool small = a.amps < (uint64_t(1) << kPadQubits);
     const bool large_tile = st.tile_bits > tile_bits(dt);
-#define SV_SWEEP(R, T, NT, SMALL) \
-    hipLaunchKernelGGL((k_sweep<R, T, NT, SMALL>), grid, dim3(NT), 0, h->stream, psi, blocks, mats, a)
+#define SV_SWEEP(...) \
+    hipLaunchKernelGGL((k_sweep<__VA_ARGS__>), grid, dim3(large_tile ? 512 : 256), 0, h->stream, psi, blocks, mats, a)
     if (dt == SV_C64) {
         if (large_tile)
             SV_SWEEP(float, 13, 512, true);
         else if (small)
             SV_SWEEP(float, 12, 256, true);
+        else if (st.split)
+            SV_SWEEP(float, 12, 256, false, true);
         else
             SV_SWEEP(float, 12, 256, false);
     } else {

@@ -35,10 +35,12 @@ static uint64_t h_origin(uint64_t t, const SweepArgs& a)
     return v;
 }
 
-static uint32_t h_spread(uint32_t v, const uint32_t* ins, int k)
+static uint32_t h_group(uint32_t v, const uint32_t* grp)
 {
-    for (int j = 0; j < k; ++j) v += v & ins[j];
-    return v;
+    uint32_t o = 0;
+    for (int j = 0; v >> j; ++j)
+        if ((v >> j) & 1) o ^= grp[j];
+    return o;
 }
 
 static void check_sweep(sv_dtype_t dt, int n, const SweepStep& st, const FusedBlock* blocks, int step)
@@ -61,7 +63,7 @@ static void check_sweep(sv_dtype_t dt, int n, const SweepStep& st, const FusedBl
             if (loff >> 32 || loff % bytes || roff % bytes) fail("lane offset", n, dt, step);
             loff /= bytes;
             roff /= bytes;
-            const uint32_t s = slot(uint32_t(u * nt + tid) * apv);
+            const uint32_t s = slot_bytes(dt, uint32_t(u * nt + tid) * apv) / bytes;
             for (int e = 0; e < apv; ++e) {
                 if (s + e >= glob.size() || glob[s + e] != ~uint64_t(0)) return fail("tile slot taken twice", n, dt, step);
                 glob[s + e] = roff + loff + e;
@@ -88,9 +90,9 @@ static void check_sweep(sv_dtype_t dt, int n, const SweepStep& st, const FusedBl
         const int k = std::min(d[j].kind, 5);
         std::vector<char> used(size_t(1) << T, 0);
         for (uint32_t g = 0; g < (1u << (T - k)); ++g) {
-            const uint32_t base = slot(h_spread(g, d[j].ins, k));
+            const uint32_t base = h_group(g, d[j].grp) / bytes;
             for (int r = 0; r < (1 << k); ++r) {
-                const uint32_t s = base ^ (d[j].off[r] / bytes);
+                const uint32_t s = base ^ (d[j].off(r) / bytes);
                 if (s >= used.size() || used[s]++) return fail("group member taken twice", n, dt, step);
                 uint64_t want = glob[base];
                 for (int q = 0; q < b.k; ++q)
