@@ -12,7 +12,7 @@ namespace sv {
 
 // How a block is swept: 1-4 qubits as they are (states of one tile), five on
 // the matrix cores or on the vector units (block5_rows).
-constexpr int32_t kSweepMfma5 = 5, kSweepRows5 = 6;
+constexpr int32_t kSweepMfma5 = 5, kSweepRows5 = 6, kSweepCoupled5 = 7;
 
 // One block of a sweep (device).  Tile-local positions: index bit q of the
 // state below L is q, the others L plus their rank among the tile's high bits.
@@ -34,6 +34,16 @@ static_assert(kSweepBlockWords <= 64, "a wave holds a descriptor, one word a lan
 
 // Bytes from one block's packed matrix to the next's.
 constexpr uint32_t sweep_matrix_stride(bool c64) { return c64 ? 12u << 10 : 16u << 10; }
+
+// The phases of a block of coupled fusion, behind each matrix of a coupled sweep.
+// Target a's phase is the sum of the terms of the coupled qubits that are set,
+// as fixed-point turns, whose sum wraps by itself.
+struct SweepCouple {
+    uint64_t out[5][36];  // of qubit q outside the tile, 2^-64 turns
+    uint32_t in[5][8];    // of bit j of the group index, 2^-32 turns
+    uint32_t pad[112];
+};
+static_assert(sizeof(SweepCouple) == 2048, "a matrix behind it stays aligned");
 
 // Geometry of a sweep (kernel argument).
 constexpr int kSweepMaxHigh = 12;
@@ -58,6 +68,7 @@ struct SweepStep {
     SweepArgs args{};
     bool padded = false;  // blocks of fewer than five qubits are swept as five-qubit ones
     bool split = false;   // products of bf16 pieces (block5_split)
+    bool coupled = false; // some of the blocks are coupled
     int tile_bits = 0;
     int hi_pos[kSweepMaxHigh] = {};
 };

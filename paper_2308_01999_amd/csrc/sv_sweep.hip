@@ -32,6 +32,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 
 #include "sv_batch.h"
@@ -41,6 +42,10 @@ namespace sv {
 namespace {
 
 using namespace tile;
+
+// Most blocks of one sweep: its descriptors and matrices fit a segment of the
+// handle's matrix ring (16 KiB a block at most, 1 MiB).
+constexpr size_t kMaxSweepBlocks = 48;
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -240,6 +245,24 @@ __device__ __forceinline__ void split_bf16(float x, float y, uint32_t& w0, uint3
     w2 = pack_bf16(x, y);
 }
 
+__device__ __forceinline__ f32x2 cmul(f32x2 a, f32x2 b)
+{
+    return f32x2{fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.x, b.y, a.y * b.x)};
+}
+
+// exp(2 pi i u / 2^32) by the Taylor polynomials of sine and cosine on the
+// quadrant's [-pi/4, pi/4] (the terms left out are below 2e-9).
+__device__ __forceinline__ f32x2 unit(uint32_t u)
+{
+    const uint32_t q = (u + 0x20000000u) >> 30;
+    const float y = float(int32_t(u - (q << 30))) * 1.46291807926715969e-9f;  // 2 pi / 2^32
+    const float z = y * y;
+    const float sn = fmaf(y * z, fmaf(z, fmaf(z, fmaf(z, 2.75573192e-6f, -1.98412698e-4f), 8.33333333e-3f), -1.66666667e-1f), y);
+    const float cs = fmaf(z, fmaf(z, fmaf(z, fmaf(z, fmaf(z, -2.75573192e-7f, 2.48015873e-5f), -1.38888889e-3f), 4.16666667e-2f), -0.5f), 1.f);
+    const float a = (q & 1u) ? -sn : cs, b = (q & 1u) ? cs : sn;
+    return (q & 2u) ? f32x2{-a, -b} : f32x2{a, b};
+}
+
 // One half (columns 16 s ...) of a lane's share of a matrix in pieces: three of
 // Re M, three of Im M.
 struct SplitOps {
@@ -269,18 +292,46 @@ struct SplitOps {
 // on 28 qubits, 0.41 on FP32.  A lane's outputs are its inputs' slots.  (Parts
 // below the smallest normal number may be dropped: an amplitude of less than 1e-33 keeps
 // an absolute error of 1e-38.)
+// COUPLED: a block of kind kSweepCoupled5 first multiplies each amplitude by its
+// phase, exp of the sum of the phases of the targets set in it; turns: their
+// parts from outside the tile, cp: from the group index.
+template <bool COUPLED>
 __device__ __forceinline__ void block5_split(char* lds, const SweepBlock& b, const u32x4* __restrict__ m,
                                              const u32x4* __restrict__ next, SplitOps& o, const LaneBits& lb,
-                                             uint32_t wave, int lane)
+                                             uint32_t wave, int lane, const SweepCouple* __restrict__ cp,
+                                             const uint32_t* turns)
 {
     uint32_t at = lane_part<5>(lb, b.grp) ^ wave_part<2>(wave, b.grp + 5) ^ (lb.m[5] & b.off(4));
     asm volatile("" : "+v"(at));
+    // factors of the rows' target bits 0-1, and 2-4 (bit 2 is the lane's half)
+    const bool coupled = COUPLED && b.kind == kSweepCoupled5;
+    f32x2 f01[4], f234[4];
+    if (coupled) {
+        f32x2 w[5];
+#pragma unroll
+        for (int a = 0; a < 5; ++a) {
+            uint32_t u = turns[a] + ((wave & 1u) ? cp->in[a][5] : 0u) + ((wave & 2u) ? cp->in[a][6] : 0u);
+#pragma unroll
+            for (int j = 0; j < 5; ++j) u += lb.m[j] & cp->in[a][j];
+            w[a] = unit(u);
+        }
+        f01[0] = f32x2{1.f, 0.f}, f01[1] = w[0], f01[2] = w[1], f01[3] = cmul(w[0], w[1]);
+        f234[0] = lane >= 32 ? w[2] : f01[0];
+        f234[1] = cmul(f234[0], w[3]), f234[2] = cmul(f234[0], w[4]), f234[3] = cmul(f234[1], w[4]);
+    }
     f32x16 re = {0}, im = {0};
     // 16 columns: eight inputs of the lane, the six products of each pair of parts
     auto half_sum = [&](int s) {
         f32x2 x[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = *reinterpret_cast<const f32x2*>(lds + (at ^ b.off(16 * s + 8 * (e / 4) + (e % 4))));
+        if (coupled) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const f32x2 g = f234[2 * s + e / 4];
+                x[e] = cmul(x[e], e % 4 ? cmul(f01[e % 4], g) : g);
+            }
+        }
         u32x4 xr[3], xi[3], xn[3];
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -562,16 +613,18 @@ __device__ __forceinline__ void add_z_sums(char* lds, const SweepArgs& a, const 
 // fewer than five qubits on the vector units; a state of less than a tile
 // leaves the rest of it zeros that no one stores.  FIRST: the state is |0..0>
 // and is not read.  zs: complex64 sweeps of 256 threads only.
-template <typename R, int T, int NT, bool SMALL, bool SPLIT = false, bool FIRST = false, bool SUMS = false>
+template <typename R, int T, int NT, bool SMALL, bool SPLIT = false, bool COUPLED = false, bool FIRST = false,
+          bool SUMS = false>
 __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
                                             const char* __restrict__ mats, const SweepArgs& a, uint64_t wg,
-                                            char* lds, const ZSums& zs)
+                                            char* lds, const ZSums& zs, [[maybe_unused]] uint32_t* turns)
 {
     using A = Amp<R>;
     using W = typename A::W;
     constexpr int NV = (1 << T) / A::kPerVec / NT;       // 16-byte vectors per thread
     constexpr int kCols = sizeof(R) == 4 ? 32 : 16;      // groups per wave
-    constexpr uint32_t kStride = sweep_matrix_stride(sizeof(R) == 4);
+    constexpr uint32_t kStride = sweep_matrix_stride(sizeof(R) == 4) + (COUPLED ? sizeof(SweepCouple) : 0);
+    auto phases = [&](int i) { return reinterpret_cast<const SweepCouple*>(mats + uint64_t(i + 1) * kStride) - 1; };
     static_assert((1 << (T - 5)) == kCols * (NT / 64), "one column tile per wave");
     static_assert(NV == 8, "three tile-local bits of a vector's index");
     const uint64_t t0 = wg * a.tiles_per_wg;
@@ -631,6 +684,18 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
                 buf[u] = __builtin_nontemporal_load(lane_address<const W>(base + roff[u], loff));
         }
         if (FIRST && tid == 0) buf[0][0] = 1;
+        if constexpr (COUPLED) {
+            // the phases from outside the tile of every block and target,
+            // while the tile is on its way
+            const uint64_t origin = uint64_t(base - psi) / A::kBytes;
+            const int bits = 64 - __builtin_clzll(a.amps - 1);
+            for (int j = tid; j < 5 * a.n_blocks; j += NT) {
+                const uint64_t* p = phases(j / 5)->out[j % 5];
+                uint64_t u = 0x80000000u;
+                for (int q = 0; q < bits; ++q) u += ((origin >> q) & 1) ? p[q] : 0;
+                turns[j / 5 * 8 + j % 5] = uint32_t(u >> 32);
+            }
+        }
 #pragma unroll
         for (int u = 0; u < NV; ++u)
             *reinterpret_cast<W*>(lds + (staged ^ A::kBytes * slot<R>(uint32_t(u * NT) * A::kPerVec))) = buf[u];
@@ -646,8 +711,9 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
                 const SweepBlock b = block_of(w);
                 w = load_words(blocks + next);
                 if constexpr (SPLIT) {
-                    block5_split(lds, b, reinterpret_cast<const u32x4*>(matrix(i)),
-                                 reinterpret_cast<const u32x4*>(matrix(next)), split, lb, uint32_t(wave), lane);
+                    block5_split<COUPLED>(lds, b, reinterpret_cast<const u32x4*>(matrix(i)),
+                                          reinterpret_cast<const u32x4*>(matrix(next)), split, lb, uint32_t(wave), lane,
+                                          phases(i), turns + 8 * i);
                 } else {
                     Ops<R> o;
                     block5<false, false>(lds, b, matrix(i), o, lb, uint32_t(wave), lane);
@@ -716,12 +782,14 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
     for (int w = 0; w < kWarm; ++w) asm volatile("" ::"v"(warm[w]));
 }
 
-template <typename R, int T, int NT, bool SMALL, bool SPLIT = false>
+template <typename R, int T, int NT, bool SMALL, bool SPLIT = false, bool COUPLED = false>
 __global__ __launch_bounds__(NT, SMALL ? 1 : 4) void k_sweep(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
                                                             const char* __restrict__ mats, SweepArgs a)
 {
     __shared__ __align__(16) char lds[Amp<R>::kBytes << T];
-    sweep_tiles<R, T, NT, SMALL, SPLIT>(psi, blocks, mats, a, blockIdx.x, lds, ZSums{nullptr, -1, nullptr, nullptr});
+    __shared__ uint32_t turns[COUPLED ? 8 * kMaxSweepBlocks : 1];
+    sweep_tiles<R, T, NT, SMALL, SPLIT, COUPLED>(psi, blocks, mats, a, blockIdx.x, lds,
+                                                 ZSums{nullptr, -1, nullptr, nullptr}, turns);
 }
 
 // Level path of a batch: workgroup w sweeps its tiles of one step of one
@@ -743,9 +811,9 @@ __global__ __launch_bounds__(256, 4) void k_batch_level(char* __restrict__ state
     const BatchLevelEntry e = entries[blockIdx.x];
     const BatchSweep& d = sweeps[e.sweep];
     const ZSums zs{z_masks + d.term0, d.n_terms, partials + d.red_off + uint64_t(e.wg) * uint64_t(d.n_terms + 1), zacc};
-    sweep_tiles<float, 12, 256, false, false, FIRST, true>(states + 8 * d.state_off, blocks + d.block0,
+    sweep_tiles<float, 12, 256, false, false, false, FIRST, true>(states + 8 * d.state_off, blocks + d.block0,
                                                     mats + uint64_t(d.block0) * sweep_matrix_stride(true), d.a, e.wg,
-                                                    lds, zs);
+                                                    lds, zs, nullptr);
 }
 
 constexpr int tile_bits(sv_dtype_t dt) { return dt == SV_C64 ? 12 : 11; }  // 32 KiB
@@ -768,10 +836,6 @@ constexpr int kReorderWindow = 96;
 // below 22 qubits, for 7% fewer sweeps, measured no faster: 339 us against 324
 // on 19 qubits complex128.)
 constexpr int min_run_bits(sv_dtype_t dt) { return dt == SV_C64 ? 4 : 3; }
-
-// Most blocks of one sweep: its descriptors and matrices fit a segment of the
-// handle's matrix ring (16 KiB a block at most, 1 MiB).
-constexpr size_t kMaxSweepBlocks = 48;
 
 // Largest state of multi-block sweeps: the lanes' part of an address (three
 // index bits below the fifth highest one) fits 32 bits.
@@ -843,7 +907,10 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
     const int T = std::max(tile_bits(dt), one_tile ? n : 0);
     const int lo = min_run_bits(dt);
     auto eligible = [&](const FusedBlock& b) {
-        if (b.diagonal || b.n_couple > 0 || b.k > 5) return false;
+        if (b.diagonal || b.k > 5) return false;
+        // coupled blocks: where the phases have a kernel (block5_split), and no
+        // padding qubit could be a coupled one
+        if (b.n_couple > 0 && !(dt == SV_C64 && n >= kReorderQubits && !rules.keep_order && b.k == 5)) return false;
         if (n > (dt == SV_C64 ? kMaxSweepQubitsC64 : kMaxSweepQubitsC128)) return false;
         if (rules.pad_all) return true;
         // larger states: blocks on 2-4 qubits are swept as five-qubit ones
@@ -860,6 +927,7 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
         st.multi = take.size() > 1 || ((n < kReorderQubits || rules.pad_all) && eligible(blocks[take[0]]));
         st.blocks = std::move(take);
         st.padded = rules.pad_all || n >= kPadQubits;
+        for (int i : st.blocks) st.coupled = st.coupled || (st.multi && blocks[i].n_couple > 0);
         st.split = dt == SV_C64 && n >= kReorderQubits && !rules.keep_order;
         if (st.multi) {
             st.tile_bits = T;
@@ -887,18 +955,20 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
             add(std::move(take), on);
             continue;
         }
-        // a block may join a sweep ahead of blocks left behind that share no
-        // qubit with it (they commute); of the first ready seeds, the one
+        // a block may join a sweep ahead of blocks left behind whose targets
+        // it does not touch and that do not touch its targets (they commute); of the first ready seeds, the one
         // whose sweep takes most blocks
         const size_t hi = std::min(rest.size(), at + kReorderWindow);
         std::vector<int> best;
         uint64_t best_on = 0;
         int seeds = 0;
-        uint64_t before = 0;
+        uint64_t before = 0, before_t = 0;  // qubits and targets of the blocks passed over
         for (size_t s = at; s < hi && seeds < 8; ++s) {
             const uint64_t qs = qubit_mask(blocks[rest[s]]);
-            const bool ready = !(qs & before) && eligible(blocks[rest[s]]);
-            before |= touched_mask(blocks[rest[s]]);
+            const uint64_t ts = touched_mask(blocks[rest[s]]);
+            const bool ready = !(qs & before) && !(ts & before_t) && eligible(blocks[rest[s]]);
+            before |= ts;
+            before_t |= qs;
             if (!ready) continue;
             ++seeds;
             std::vector<int> take{rest[s]};
@@ -907,18 +977,20 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
             in[s - at] = 1;
             while (take.size() < kMaxSweepBlocks) {
                 int pick = -1, cost = 65;
-                uint64_t blocked = 0;
+                uint64_t blocked = 0, blocked_t = 0;
                 for (size_t j = at; j < hi; ++j) {
                     if (in[j - at]) continue;
                     const uint64_t q = qubit_mask(blocks[rest[j]]);
-                    if (!(q & blocked) && eligible(blocks[rest[j]]) && fits(on | q)) {
+                    const uint64_t touched = touched_mask(blocks[rest[j]]);
+                    if (!(q & blocked) && !(touched & blocked_t) && eligible(blocks[rest[j]]) && fits(on | q)) {
                         const int c = __builtin_popcountll((on | q) >> lo);
                         if (c < cost) {
                             cost = c;
                             pick = int(j);
                         }
                     }
-                    blocked |= touched_mask(blocks[rest[j]]);
+                    blocked |= touched;
+                    blocked_t |= q;
                 }
                 if (pick < 0) break;
                 in[pick - at] = 1;
@@ -945,11 +1017,11 @@ namespace {
 
 uint32_t slot_bytes(sv_dtype_t dt, uint32_t a) { return dt == SV_C64 ? 8u * slot<float>(a) : 16u * slot<double>(a); }
 
-// Byte offsets of the group index's bits: the tile bits outside `used`, the
-// lanes' first.  The first 4 (complex64; complex128 3) lane bits are to be
+// Byte offsets (grp) and positions (pos) of the group index's bits: the tile
+// bits outside `used`, the lanes' first; returns their number.  The first 4 (complex64; complex128 3) lane bits are to be
 // independent in the 32 banks a write sees, and one more with them in the 64
 // of a read, as far as there are such bits.
-void choose_lanes(sv_dtype_t dt, int T, uint32_t used, uint32_t* grp)
+int choose_lanes(sv_dtype_t dt, int T, uint32_t used, uint32_t* grp, int* pos)
 {
     const int width = dt == SV_C64 ? 5 : 4;
     uint32_t left = ((1u << T) - 1u) & ~used;
@@ -969,6 +1041,7 @@ void choose_lanes(sv_dtype_t dt, int T, uint32_t used, uint32_t* grp)
     int n = 0;
     auto take = [&](int p) {
         left &= ~(1u << p);
+        pos[n] = p;
         grp[n++] = slot_bytes(dt, 1u << p);
     };
     auto bank = [&](int p) { return (dt == SV_C64 ? slot<float>(1u << p) : slot<double>(1u << p)) & ((1u << width) - 1u); };
@@ -981,6 +1054,7 @@ void choose_lanes(sv_dtype_t dt, int T, uint32_t used, uint32_t* grp)
         if (((left >> p) & 1) && add(full, bank(p))) take(p);
     for (int p = 0; p < T; ++p)
         if ((left >> p) & 1) take(p);
+    return n;
 }
 
 // Place of matrix entry (i, c) in a part of the packed operands.  complex64:
@@ -1050,10 +1124,16 @@ void pack5_split(const FusedBlock& b, uint16_t* o)
 
 }  // namespace
 
+// Bytes from one block's matrix to the next's in a step's buffer.
+size_t matrix_stride(sv_dtype_t dt, const SweepStep& st)
+{
+    return sweep_matrix_stride(dt == SV_C64) + (st.coupled ? sizeof(SweepCouple) : 0);
+}
+
 size_t sweep_bytes(sv_dtype_t dt, const SweepStep& st)
 {
     return ((sizeof(SweepBlock) * st.blocks.size() + 255) & ~size_t(255)) +
-           sweep_matrix_stride(dt == SV_C64) * st.blocks.size();
+           matrix_stride(dt, st) * st.blocks.size();
 }
 
 void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, void* dst)
@@ -1065,14 +1145,14 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, vo
 void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, SweepBlock* desc, char* mat)
 {
     const int L = st.args.L, T = st.tile_bits, n = 63 - __builtin_clzll(st.args.amps);
-    for (size_t j = 0; j < st.blocks.size(); ++j, mat += sweep_matrix_stride(dt == SV_C64)) {
+    for (size_t j = 0; j < st.blocks.size(); ++j, mat += matrix_stride(dt, st)) {
         const FusedBlock& b = blocks[st.blocks[j]];
         const int k = st.padded ? 5 : b.k;
         SweepBlock s{};
         s.kind = k < 5 ? k : (dt == SV_C128 && n < 11) ? kSweepRows5 : kSweepMfma5;
         // tile-local positions of the targets, then of the padding qubits
         // (the lowest positions that are free)
-        int pos[5] = {};
+        int pos[5] = {}, group[12] = {};
         uint32_t used = 0;
         for (int a = 0; a < b.k; ++a) {
             int p = b.targets[a];
@@ -1089,7 +1169,31 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, Sw
                 pos[a++] = p;
                 used |= 1u << p;
             }
-        choose_lanes(dt, T, used, s.grp);
+        const int left = choose_lanes(dt, T, used, s.grp, group);
+        if (b.n_couple > 0) s.kind = kSweepCoupled5;
+        if (st.coupled) {
+            // turns of each target's phase, by the coupled qubit's place: a bit
+            // of the group index, or outside the tile
+            SweepCouple cp{};
+            for (int a = 0; a < b.k; ++a)
+                for (int c = 0; c < b.n_couple; ++c) {
+                    const int q = b.couple_q[c];
+                    double turn = b.couple[a * b.n_couple + c] / 6.283185307179586476925286766559;
+                    turn -= std::floor(turn);
+                    int p = q;
+                    if (q >= L) {
+                        int r = 0;
+                        while (r < st.args.n_hi && st.hi_pos[r] != q) ++r;
+                        p = r < st.args.n_hi ? L + r : -1;
+                    }
+                    if (p < 0)  // in two steps: 2^64 does not fit
+                        cp.out[a][q] = uint64_t(std::llround(std::ldexp(turn, 62))) << 2;
+                    else
+                        for (int j = 0; j < left; ++j)
+                            if (group[j] == p) cp.in[a][j] = uint32_t(std::llround(std::ldexp(turn, 32)));
+                }
+            std::memcpy(mat + sweep_matrix_stride(true), &cp, sizeof cp);
+        }
         for (int a = 0; a < k; ++a) s.bit[a] = slot_bytes(dt, 1u << pos[a]);
         desc[j] = s;
         if (s.kind == kSweepRows5)
@@ -1121,6 +1225,8 @@ void launch_sweep(sv_handle_s* h, sv_dtype_t dt, void* psi_v, const SweepStep& s
             SV_SWEEP(float, 13, 512, true);
         else if (small)
             SV_SWEEP(float, 12, 256, true);
+        else if (st.coupled)
+            SV_SWEEP(float, 12, 256, false, true, true);
         else if (st.split)
             SV_SWEEP(float, 12, 256, false, true);
         else

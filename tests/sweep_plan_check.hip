@@ -174,7 +174,8 @@ int main()
                             for (int c = 0; c < b.n_couple; ++c) t |= uint64_t(1) << b.couple_q[c];
                             return t;
                         };
-                        if (touched(blocks[i]) & touched(blocks[j])) fail("blocks on one qubit swapped", n, dt, i);
+                        if ((qubit_mask(blocks[i]) & touched(blocks[j])) | (touched(blocks[i]) & qubit_mask(blocks[j])))
+                            fail("blocks that do not commute swapped", n, dt, i);
                     }
             }
     printf("sweeps %d reordered pairs %d fails %d\n", sweeps, reordered, fails);
