@@ -830,6 +830,12 @@ constexpr int kPadQubits = 14;
 // their bits), and whose complex64 sweeps multiply bf16 parts (block5_split): a
 // state of 22 qubits is the first that keeps every CU's matrix cores busy.
 constexpr int kReorderQubits = 22;
+
+// Largest state whose five-qubit blocks are swept by k_sweep also one at a time
+// (512 MiB, near the size of the memory-side cache): 22, 24 and 26 qubits
+// complex64 36, 67 and 209 us on the tile kernels of one block, 31, 52 and 182
+// here; on 28 qubits, where HBM alone counts, 686 and 730.
+constexpr int lone_qubits(sv_dtype_t dt) { return dt == SV_C64 ? 26 : 25; }
 constexpr int kReorderWindow = 96;
 
 // Shortest runs of a tile: 128 bytes, the line of the L2.  (Runs of 64 bytes
@@ -924,7 +930,9 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
     auto fits = [&](uint64_t on) { return one_tile || __builtin_popcountll(on >> lo) <= T - lo; };
     auto add = [&](std::vector<int>&& take, uint64_t on) {
         SweepStep st;
-        st.multi = take.size() > 1 || ((n < kReorderQubits || rules.pad_all) && eligible(blocks[take[0]]));
+        const FusedBlock& b0 = blocks[take[0]];
+        const bool lone = n < kReorderQubits || rules.pad_all || (n <= lone_qubits(dt) && b0.k == 5);
+        st.multi = take.size() > 1 || (lone && eligible(b0));
         st.blocks = std::move(take);
         st.padded = rules.pad_all || n >= kPadQubits;
         for (int i : st.blocks) st.coupled = st.coupled || (st.multi && blocks[i].n_couple > 0);
