@@ -38,15 +38,15 @@ HBM_PEAK_GBS = 8000.0
 # kernel sources the counters were taken on: their SHA-256 are recorded and
 # checked at run time.
 _K5_SOURCES = {"paper_2308_01999_amd/csrc/sv_apply.hip":
-               "cf79059f6f509d8abd8860f662118b5c5ff6710a5ea28dc36f83deb7742e688b",
+               "70d5a80c35c10b660ca2f9e5b353144b026ba5a44b43b60edbc29116f2c172ee",
                "paper_2308_01999_amd/csrc/sv_tile.h":
-               "14df7118bbe9218d6f281185a9817e4518b765bfcec4ed09243b2a5b993b5984"}
+               "3845d6e52b319d0a008c5512064c6dc27b5ccfb610a8e6072bd441c13696ed4e"}
 PMC_TRAFFIC = {
-    # 30-qubit brickwork sweep, dispatch-weighted over all tile variants (728
-    # launches of each dtype in one pass: 14 steps of 52 blocks)
-    "k_tile_c64_k5": {"n": 30, "fetch_kib": 4194384.0, "write_kib": 8389899.5,
+    # 30-qubit brickwork sweep, dispatch-weighted over all tile variants (the
+    # 52 blocks of each dtype one by one, three times)
+    "k_tile_c64_k5": {"n": 30, "fetch_kib": 4194387.9, "write_kib": 8390582.2,
                       "fetch_scale": 2.0, "write_scale": 1.0, "sources": _K5_SOURCES},
-    "k_tile_c128_k5": {"n": 30, "fetch_kib": 8388720.9, "write_kib": 16780158.6,
+    "k_tile_c128_k5": {"n": 30, "fetch_kib": 8388721.0, "write_kib": 16781379.0,
                        "fetch_scale": 2.0, "write_scale": 1.0, "sources": _K5_SOURCES},
 }
 

@@ -832,9 +832,10 @@ constexpr int kPadQubits = 14;
 constexpr int kReorderQubits = 22;
 
 // Largest state whose five-qubit blocks are swept by k_sweep also one at a time
-// (512 MiB, near the size of the memory-side cache): 22, 24 and 26 qubits
-// complex64 36, 67 and 209 us on the tile kernels of one block, 31, 52 and 182
-// here; on 28 qubits, where HBM alone counts, 686 and 730.
+// (512 MiB).  Mean over neighbouring and random targets, the tuned tile kernels
+// of one block and this one: complex64 22, 24, 25, 26 qubits 21.7, 63.5, 115 and 201
+// us against 20.6, 57.6, 103 and 193; complex128 24 and 25 qubits 138 and 216
+// against 117 and 213; on 28 qubits complex64, where HBM alone counts, 686 and 730.
 constexpr int lone_qubits(sv_dtype_t dt) { return dt == SV_C64 ? 26 : 25; }
 constexpr int kReorderWindow = 96;
 
