@@ -16,9 +16,9 @@
 // cores for several.  A block costs a wave 48 MFMAs: of v_mfma_f32_32x32x2_f32
 // 3072 cycles (1.7 ms a block at 30 qubits), of v_mfma_f64_16x16x4_f64 the same,
 // of v_mfma_f32_32x32x16_bf16 1536 (block5_split, states of 22 qubits and
-// more).  A tile is 32 KiB and a workgroup 256 threads and one tile: the runs of 128
-// bytes that this leaves for eight free bits stream at 4.6-5.4 TB/s (64 and
-// 128 KiB tiles, fewer sweeps, measured slower), and four workgroups a CU, at most
+// more).  A tile is 32 KiB (64 KiB and 512 threads where plan_sweeps says) and a workgroup 256
+// threads and one tile: the runs of 128 bytes that this leaves for eight free
+// bits stream at 4.6-5.4 TB/s, and four workgroups a CU, at most
 // 128 vector registers a thread, hide each other's loads, stores and
 // barriers.  They do it better than three that load their next tile during a
 // tile's blocks: loads return in order, so a matrix behind a tile waits for
@@ -26,7 +26,7 @@
 // 27 qubits 1.91 -> 1.83).
 // Measured, before (a sweep per block) and after: 30-qubit brickwork circuit
 // of depth 20, complex64, 52 blocks in 20 sweeps, 156 -> 92 ms; 28-qubit
-// random CNOT/CP circuit, complex128, 71 -> 51 ms; 19-qubit circuit on random
+// random CNOT/CP circuit, complex128, 71 -> 48 ms; 19-qubit circuit on random
 // pairs, complex128, 660 -> 310 us; 14 qubits complex64 as a recorded graph,
 // 155 -> 91 us; 12 qubits complex128 194 -> 117 us.
 #include <hip/hip_runtime.h>
@@ -301,7 +301,7 @@ __device__ __forceinline__ void block5_split(char* lds, const SweepBlock& b, con
                                              uint32_t wave, int lane, const SweepCouple* __restrict__ cp,
                                              const uint32_t* turns)
 {
-    uint32_t at = lane_part<5>(lb, b.grp) ^ wave_part<2>(wave, b.grp + 5) ^ (lb.m[5] & b.off(4));
+    uint32_t at = lane_part<5>(lb, b.grp) ^ wave_part<3>(wave, b.grp + 5) ^ (lb.m[5] & b.off(4));
     asm volatile("" : "+v"(at));
     // factors of the rows' target bits 0-1, and 2-4 (bit 2 is the lane's half)
     const bool coupled = COUPLED && b.kind == kSweepCoupled5;
@@ -310,7 +310,8 @@ __device__ __forceinline__ void block5_split(char* lds, const SweepBlock& b, con
         f32x2 w[5];
 #pragma unroll
         for (int a = 0; a < 5; ++a) {
-            uint32_t u = turns[a] + ((wave & 1u) ? cp->in[a][5] : 0u) + ((wave & 2u) ? cp->in[a][6] : 0u);
+            uint32_t u = turns[a] + ((wave & 1u) ? cp->in[a][5] : 0u) + ((wave & 2u) ? cp->in[a][6] : 0u) +
+                         ((wave & 4u) ? cp->in[a][7] : 0u);
 #pragma unroll
             for (int j = 0; j < 5; ++j) u += lb.m[j] & cp->in[a][j];
             w[a] = unit(u);
@@ -911,7 +912,14 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
 {
     std::vector<SweepStep> steps;
     const bool one_tile = n <= tile_bits(dt) + (rules.pad_all ? 0 : 1);
-    const int T = std::max(tile_bits(dt), one_tile ? n : 0);
+    // From 22 qubits on a sweep may take a tile of one bit more, if its blocks
+    // need it: 24 sweeps become 20 for a 28-qubit CNOT/CP circuit (complex128,
+    // 51.3 -> 48.2 ms), 37 become 30 for a 23-qubit coupled program (1.71 -> 1.58
+    // ms); 25-qubit circuits complex64 3.47 -> 3.11 and 5.69 -> 5.42 ms.  Not with
+    // coupled blocks on the largest states, where lone ones have kernels bound
+    // by HBM alone: the 28-qubit QFT took 7.69 ms without and 7.88 with.
+    const int T = std::max(tile_bits(dt) + (n >= kReorderQubits && !rules.keep_order), one_tile ? n : 0);
+    const bool coupled_large = n <= lone_qubits(dt);
     const int lo = min_run_bits(dt);
     auto eligible = [&](const FusedBlock& b) {
         if (b.diagonal || b.k > 5) return false;
@@ -928,7 +936,9 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
         const int outside = __builtin_ctzll(on) + n - 1 - (63 - __builtin_clzll(on));
         return b.k >= 2 && outside >= 5 - b.k;
     };
-    auto fits = [&](uint64_t on) { return one_tile || __builtin_popcountll(on >> lo) <= T - lo; };
+    auto fits = [&](uint64_t on, bool coupled = false) {
+        return one_tile || __builtin_popcountll(on >> lo) <= (coupled && !coupled_large ? tile_bits(dt) : T) - lo;
+    };
     auto add = [&](std::vector<int>&& take, uint64_t on) {
         SweepStep st;
         const FusedBlock& b0 = blocks[take[0]];
@@ -940,6 +950,7 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
         st.split = dt == SV_C64 && n >= kReorderQubits && !rules.keep_order;
         if (st.multi) {
             st.tile_bits = T;
+            if (T > tile_bits(dt) && !one_tile && __builtin_popcountll(on >> lo) <= tile_bits(dt) - lo) --st.tile_bits;
             fill_geometry(dt, n, cu_count, on, rules.spread_lo, st);
         }
         steps.push_back(std::move(st));
@@ -982,6 +993,7 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
             ++seeds;
             std::vector<int> take{rest[s]};
             uint64_t on = qs;
+            bool coupled = blocks[rest[s]].n_couple > 0;
             std::vector<char> in(hi - at, 0);
             in[s - at] = 1;
             while (take.size() < kMaxSweepBlocks) {
@@ -991,7 +1003,8 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
                     if (in[j - at]) continue;
                     const uint64_t q = qubit_mask(blocks[rest[j]]);
                     const uint64_t touched = touched_mask(blocks[rest[j]]);
-                    if (!(q & blocked) && !(touched & blocked_t) && eligible(blocks[rest[j]]) && fits(on | q)) {
+                    if (!(q & blocked) && !(touched & blocked_t) && eligible(blocks[rest[j]]) &&
+                        fits(on | q, coupled || blocks[rest[j]].n_couple > 0)) {
                         const int c = __builtin_popcountll((on | q) >> lo);
                         if (c < cost) {
                             cost = c;
@@ -1004,6 +1017,7 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
                 if (pick < 0) break;
                 in[pick - at] = 1;
                 on |= qubit_mask(blocks[rest[pick]]);
+                coupled = coupled || blocks[rest[pick]].n_couple > 0;
                 take.push_back(rest[pick]);
             }
             if (take.size() > best.size()) {
@@ -1230,10 +1244,14 @@ void launch_sweep(sv_handle_s* h, sv_dtype_t dt, void* psi_v, const SweepStep& s
 #define SV_SWEEP(...) \
     hipLaunchKernelGGL((k_sweep<__VA_ARGS__>), grid, dim3(large_tile ? 512 : 256), 0, h->stream, psi, blocks, mats, a)
     if (dt == SV_C64) {
-        if (large_tile)
+        if (large_tile && small)
             SV_SWEEP(float, 13, 512, true);
         else if (small)
             SV_SWEEP(float, 12, 256, true);
+        else if (large_tile && st.coupled)
+            SV_SWEEP(float, 13, 512, false, true, true);
+        else if (large_tile)
+            SV_SWEEP(float, 13, 512, false, true);
         else if (st.coupled)
             SV_SWEEP(float, 12, 256, false, true, true);
         else if (st.split)
@@ -1241,10 +1259,12 @@ void launch_sweep(sv_handle_s* h, sv_dtype_t dt, void* psi_v, const SweepStep& s
         else
             SV_SWEEP(float, 12, 256, false);
     } else {
-        if (large_tile)
+        if (large_tile && small)
             SV_SWEEP(double, 12, 512, true);
         else if (small)
             SV_SWEEP(double, 11, 256, true);
+        else if (large_tile)
+            SV_SWEEP(double, 12, 512, false);
         else
             SV_SWEEP(double, 11, 256, false);
     }
