@@ -315,7 +315,9 @@ sv_status_t sv_fused_free(sv_fused_t f);
 /* Applies all blocks of f (async), as if in order: consecutive blocks whose
  * qubits fit one tile share a sweep of the state (Sec. II-B: a sweep is bound
  * by the bandwidth), and on states of 22 qubits and more a block may pass
- * blocks on other qubits on its way into a sweep.  With a forced tile variant
+ * blocks it commutes with on its way into a sweep, and complex64 sweeps multiply
+ * exact bf16 parts of matrix and amplitudes, with FP32 sums (less error than the
+ * FP32 sweeps').  With a forced tile variant
  * (sv_handle_set_tile_mode) every block is swept on its own, in order.  Block
  * matrices are uploaded in batches of up to 1 MiB, one host-to-device copy per
  * batch. */
