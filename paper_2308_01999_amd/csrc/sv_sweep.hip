@@ -798,7 +798,7 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 4) void k_sweep(char* __restrict__ 
 // tiles.  FIRST: the states are |0..0>.  Bound by HBM and the matrix pipe
 // about equally: a step holds two blocks in the mean (in program order, since
 // a swap would change the states' bits), so that a batch of 512 circuits of 8-20
-// qubits moves half the bytes of one sweep per block: 13.5 -> 10.6 ms.
+// qubits moves half the bytes of one sweep per block: 13.5 -> 10.0 ms.
 template <bool FIRST>
 __global__ __launch_bounds__(256, 4) void k_batch_level(char* __restrict__ states, const BatchSweep* __restrict__ sweeps,
                                                        const BatchLevelEntry* __restrict__ entries,
