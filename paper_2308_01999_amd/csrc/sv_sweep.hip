@@ -772,6 +772,9 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
             if (zs.n_terms >= 0) add_z_sums(lds, a, zs, uint64_t(base - psi + int64_t(roff[0]) + loff) / A::kBytes, tid);
         __syncthreads();
     }
+    // a workgroup of written tiles only (FIRST) has met no barrier since the
+    // waves zeroed their rows
+    if constexpr (SUMS && FIRST) __syncthreads();
     if (SUMS && zs.n_terms >= 0 && tid <= zs.n_terms) {
         // the waves' rows in order; the norm last
         const int c = tid == zs.n_terms ? kZSumsMax : tid;
