@@ -220,16 +220,16 @@ void check_matrix_finite(const double* m, int k)
 // leaves a segment and waited on when it comes back to it.  On the device
 // side, stream order puts every later copy after the kernels that read the
 // earlier contents.
-const void* stage_matrix(sv_handle_s* h, const void* host, size_t bytes)
+const void* stage_matrix(sv_handle_s* h, const void* host, size_t size)
 {
     const size_t seg = kMatRingBytes / kMatRingSegments;
-    bytes = (bytes + 255) & ~size_t(255);
+    const size_t bytes = (size + 255) & ~size_t(255);  // of the ring; the caller's buffer ends at size
     if (bytes > seg) {
         // large gates (k >= 9): copy into the scratch part of the workspace
         // and wait, so that the host buffer may be released on return
         SV_CHECK(kMatRingBytes + bytes <= h->ws_bytes, "matrix larger than the handle's workspace");
         char* dst = h->ws + kMatRingBytes;
-        SV_HIP(hipMemcpyAsync(dst, host, bytes, hipMemcpyHostToDevice, h->stream));
+        SV_HIP(hipMemcpyAsync(dst, host, size, hipMemcpyHostToDevice, h->stream));
         SV_HIP(hipStreamSynchronize(h->stream));
         return dst;
     }
@@ -247,8 +247,8 @@ const void* stage_matrix(sv_handle_s* h, const void* host, size_t bytes)
         }
         h->ring_seg = new_seg;
     }
-    std::memcpy(h->pinned + pos, host, bytes);
-    SV_HIP(hipMemcpyAsync(h->ws + pos, h->pinned + pos, bytes, hipMemcpyHostToDevice, h->stream));
+    std::memcpy(h->pinned + pos, host, size);
+    SV_HIP(hipMemcpyAsync(h->ws + pos, h->pinned + pos, size, hipMemcpyHostToDevice, h->stream));
     h->ring_pos = pos + bytes;
     return h->ws + pos;
 }

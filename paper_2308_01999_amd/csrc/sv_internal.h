@@ -234,6 +234,6 @@ void run_expect_matrix(sv_handle_s* h, sv_dtype_t dt, const void* psi, int n, co
 
 // Copies `bytes` of host data into the matrix ring and returns the device
 // address (stream-ordered before any later launch on the handle).
-const void* stage_matrix(sv_handle_s* h, const void* host, size_t bytes);
+const void* stage_matrix(sv_handle_s* h, const void* host, size_t size);
 
 }  // namespace sv
