@@ -232,7 +232,7 @@ void run_accessor(sv_handle_s* h, sv_dtype_t dt, void* psi, int n, const int32_t
 void run_expect_matrix(sv_handle_s* h, sv_dtype_t dt, const void* psi, int n, const double* m,
                        const int32_t* targets, int k, double* out);
 
-// Copies `bytes` of host data into the matrix ring and returns the device
+// Copies `size` bytes of host data into the matrix ring and returns the device
 // address (stream-ordered before any later launch on the handle).
 const void* stage_matrix(sv_handle_s* h, const void* host, size_t size);
 

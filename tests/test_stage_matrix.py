@@ -19,8 +19,8 @@ def test_staging_reads_no_byte_behind_the_buffer(tmp_path):
     b = subprocess.run(compile_cmd, capture_output=True, text=True, timeout=600)
     assert b.returncode == 0, b.stderr[-4000:]
     # the file defines the HIP calls that staging makes; nothing else is reached
-    link = subprocess.run(["g++", obj, "-o", exe, "-Wl,--unresolved-symbols=ignore-all"], capture_output=True, text=True,
-                          timeout=600)
+    link_cmd = ["g++", "-no-pie", obj, "-o", exe, "-Wl,--unresolved-symbols=ignore-all"]
+    link = subprocess.run(link_cmd, capture_output=True, text=True, timeout=600)
     assert link.returncode == 0, link.stderr[-4000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "passed" in r.stdout, (r.returncode, r.stdout)
