@@ -16,7 +16,7 @@ constexpr int32_t kSweepMfma5 = 5, kSweepRows5 = 6, kSweepCoupled5 = 7;
 
 // One block of a sweep (device).  Tile-local positions: index bit q of the
 // state below L is q, the others L plus their rank among the tile's high bits.
-struct SweepBlock {
+struct alignas(16) SweepBlock {
     uint32_t bit[5];   // byte offset in the swizzled tile of each bit of the matrix index
     int32_t kind;
     uint32_t grp[12];  // and of each bit of the group index
@@ -31,6 +31,7 @@ struct SweepBlock {
 };
 constexpr int kSweepBlockWords = int(sizeof(SweepBlock) / 4);
 static_assert(kSweepBlockWords <= 64, "a wave holds a descriptor, one word a lane");
+static_assert(sizeof(SweepBlock) == 80, "descriptors lie one behind the other, 16-byte aligned");
 
 // Bytes from one block's packed matrix to the next's.
 constexpr uint32_t sweep_matrix_stride(bool c64) { return c64 ? 12u << 10 : 16u << 10; }

@@ -494,7 +494,11 @@ __device__ __forceinline__ void block5_rows(char* lds, const SweepBlock& b, cons
 // needs) in scalar registers, by one load: left to itself the compiler loads
 // words one by one where they are used.
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
-__device__ __forceinline__ u32x16 load_words(const SweepBlock* p) { return *reinterpret_cast<const u32x16*>(p); }
+__device__ __forceinline__ u32x16 load_words(const SweepBlock* p)
+{
+    typedef u32x16 Words __attribute__((aligned(alignof(SweepBlock))));
+    return *reinterpret_cast<const Words*>(p);
+}
 __device__ __forceinline__ SweepBlock block_of(const u32x16& w)
 {
     SweepBlock b{};
