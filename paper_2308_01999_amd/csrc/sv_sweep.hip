@@ -1208,6 +1208,7 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, Sw
             for (int a = 0; a < b.k; ++a)
                 for (int c = 0; c < b.n_couple; ++c) {
                     const int q = b.couple_q[c];
+                    if (q >= n) continue;  // no such qubit: never set
                     double turn = b.couple[a * b.n_couple + c] / 6.283185307179586476925286766559;
                     turn -= std::floor(turn);
                     int p = q;
