@@ -11,8 +11,10 @@
 namespace sv {
 
 // How a block is swept: 1-4 qubits as they are (states of one tile), five on
-// the matrix cores or on the vector units (block5_rows).
-constexpr int32_t kSweepMfma5 = 5, kSweepRows5 = 6, kSweepCoupled5 = 7;
+// the matrix cores or on the vector units (block5_rows); added to kSweepMfma5
+// of a split sweep: the block is coupled, and its products are FP32.
+constexpr int32_t kSweepMfma5 = 5, kSweepRows5 = 6;
+constexpr int32_t kSweepCoupled = 16, kSweepFp32 = 32;
 
 // One block of a sweep (device).  Tile-local positions: index bit q of the
 // state below L is q, the others L plus their rank among the tile's high bits.

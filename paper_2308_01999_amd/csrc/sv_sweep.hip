@@ -232,9 +232,11 @@ __device__ __forceinline__ uint32_t pack_bf16(float x, float y)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x, y}), bf16x2));
 }
 
-// x and y as three bf16 each, exactly: x = x0 + x1 + x2, x0 = bf16(x), x1 =
-// bf16(x - x0), x2 the rest (24 bits in 8 + 8 + 8, both differences exact).
-__device__ __forceinline__ void split_bf16(float x, float y, uint32_t& w0, uint32_t& w1, uint32_t& w2)
+// x and y as three bf16 each: x = x0 + x1 + x2, x0 = bf16(x), x1 = bf16(x - x0),
+// x2 the rest (24 bits in 8 + 8 + 8, both differences exact).  lost: bits 0-15
+// take those of the rests, which are zero as long as the parts are exact (they
+// are from 2^-110 up: a bf16 holds no bit below 2^-133).
+__device__ __forceinline__ void split_bf16(float x, float y, uint32_t& w0, uint32_t& w1, uint32_t& w2, uint32_t& lost)
 {
     w0 = pack_bf16(x, y);
     x -= __builtin_bit_cast(float, w0 << 16);
@@ -243,6 +245,7 @@ __device__ __forceinline__ void split_bf16(float x, float y, uint32_t& w0, uint3
     x -= __builtin_bit_cast(float, w1 << 16);
     y -= __builtin_bit_cast(float, w1 & 0xffff0000u);
     w2 = pack_bf16(x, y);
+    lost |= __builtin_bit_cast(uint32_t, x) | __builtin_bit_cast(uint32_t, y);
 }
 
 __device__ __forceinline__ f32x2 cmul(f32x2 a, f32x2 b)
@@ -278,21 +281,27 @@ struct SplitOps {
 };
 
 // complex64, five qubits, on v_mfma_f32_32x32x16_bf16: matrix and amplitudes as
-// three bf16 each (together all 24 bits, at any exponent), and of their nine
-// products the six down to 2^-16 of the first, smallest first, summed in
-// FP32; the three left out are below 2^-26 of it, a quarter of an FP32
-// product's own rounding.  Four real products instead of the three of the FP32
-// kernels (Re M, Im M, Re M + Im M), whose differences cancel: of random
-// unitaries on random groups the error against 64 bits is 0.93e-7 in the mean
-// and 0.8e-6 at most of the group's 2-norm, theirs 1.55e-7 and 1.3e-6; of a
-// 30-qubit circuit's state 6.1e-7 against 9.9e-7.  A block costs 1536 cycles of the
-// matrix cores instead of 3072, and 270 vector instructions of which
-// 176 split the amplitudes (a difference as v_dot2_f32_bf16, one instruction for two,
-// was no gain: it takes the matrix cores' time).  In a sweep a block takes 0.18 ms
-// on 28 qubits, 0.41 on FP32.  A lane's outputs are its inputs' slots.  (Parts
-// below the smallest normal number may be dropped: an amplitude of less than 1e-33 keeps
-// an absolute error of 1e-38.)
-// COUPLED: a block of kind kSweepCoupled5 first multiplies each amplitude by its
+// three bf16 each (together all 24 bits), and of their nine products the six down
+// to 2^-16 of the first, summed in FP32: the five small ones of all 32 columns
+// first, then the largest, so that a sum is rounded at its full size only as
+// often as largest products are added (two to eight times; the FP32 kernels
+// round each of 32 products).  The three products left out are at most 2^-24 of
+// the whole one and 2^-27.5 in the mean square, the rounding of an FP32 product
+// 2^-24 and 2^-25.2.  Four real products instead of the three of the FP32
+// kernels (Re M, Im M, Re M + Im M), whose differences cancel.  Of a dense block
+// on random amplitudes the error against 64 bits is 0.52e-7 of the 2-norm (FP32
+// kernels 1.49e-7), of a 30-qubit circuit's state 3.8e-7 (9.9e-7).
+// The wave takes FP32 products of the same matrix where the parts do not hold an
+// amplitude (below 2^-110, and next to the largest float), and for a matrix for
+// which the host chose them (kSweepFp32).
+// A block costs 1536 cycles of the matrix cores instead of 3072, and about 290
+// vector instructions of which 176 split the amplitudes (a difference as
+// v_dot2_f32_bf16, one instruction for two, was no gain: it takes the matrix
+// cores' time).  In a sweep a block takes 0.18 ms on 28 qubits, 0.41 on FP32.
+// The order of the products and the check for lost bits cost 0.9% of a 30-qubit
+// circuit (sums of one half of the columns after the other, unchecked: 92.6 against
+// 93.4 ms, error 6.1e-7).  A lane's outputs are its inputs' slots.
+// COUPLED: a block with kSweepCoupled first multiplies each amplitude by its
 // phase, exp of the sum of the phases of the targets set in it; turns: their
 // parts from outside the tile, cp: from the group index.
 template <bool COUPLED>
@@ -303,11 +312,9 @@ __device__ __forceinline__ void block5_split(char* lds, const SweepBlock& b, con
 {
     uint32_t at = lane_part<5>(lb, b.grp) ^ wave_part<3>(wave, b.grp + 5) ^ (lb.m[5] & b.off(4));
     asm volatile("" : "+v"(at));
-    // factors of the rows' target bits 0-1, and 2-4 (bit 2 is the lane's half)
-    const bool coupled = COUPLED && b.kind == kSweepCoupled5;
-    f32x2 f01[4], f234[4];
-    if (coupled) {
-        f32x2 w[5];
+    const bool coupled = COUPLED && (b.kind & kSweepCoupled);
+    // the phase factor of each target
+    auto phases = [&](f32x2* w) {
 #pragma unroll
         for (int a = 0; a < 5; ++a) {
             uint32_t u = turns[a] + ((wave & 1u) ? cp->in[a][5] : 0u) + ((wave & 2u) ? cp->in[a][6] : 0u) +
@@ -316,52 +323,105 @@ __device__ __forceinline__ void block5_split(char* lds, const SweepBlock& b, con
             for (int j = 0; j < 5; ++j) u += lb.m[j] & cp->in[a][j];
             w[a] = unit(u);
         }
-        f01[0] = f32x2{1.f, 0.f}, f01[1] = w[0], f01[2] = w[1], f01[3] = cmul(w[0], w[1]);
-        f234[0] = lane >= 32 ? w[2] : f01[0];
-        f234[1] = cmul(f234[0], w[3]), f234[2] = cmul(f234[0], w[4]), f234[3] = cmul(f234[1], w[4]);
-    }
+    };
     f32x16 re = {0}, im = {0};
-    // 16 columns: eight inputs of the lane, the six products of each pair of parts
-    auto half_sum = [&](int s) {
-        f32x2 x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = *reinterpret_cast<const f32x2*>(lds + (at ^ b.off(16 * s + 8 * (e / 4) + (e % 4))));
-        if (coupled) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const f32x2 g = f234[2 * s + e / 4];
-                x[e] = cmul(x[e], e % 4 ? cmul(f01[e % 4], g) : g);
-            }
-        }
-        u32x4 xr[3], xi[3], xn[3];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const f32x2 u = x[2 * p], v = x[2 * p + 1];
-            uint32_t w0, w1, w2;
-            split_bf16(u.x, v.x, w0, w1, w2);
-            xr[0][p] = w0, xr[1][p] = w1, xr[2][p] = w2;
-            split_bf16(u.y, v.y, w0, w1, w2);
-            xi[0][p] = w0, xi[1][p] = w1, xi[2][p] = w2;
-        }
-#pragma unroll
-        for (int q = 0; q < 3; ++q) xn[q] = xi[q] ^ 0x80008000u;
-        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, px[6] = {0, 2, 1, 0, 1, 0};
+    uint32_t lost = 0;
 #define SV_MFMA(A, X, C) \
     C = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A), __builtin_bit_cast(bf16x8, X), C, 0, 0, 0)
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            SV_MFMA(o.re[pa[i]], xr[px[i]], re);
-            SV_MFMA(o.re[pa[i]], xi[px[i]], im);
-            SV_MFMA(o.im[pa[i]], xn[px[i]], re);
-            SV_MFMA(o.im[pa[i]], xr[px[i]], im);
-        }
+    auto product = [&](u32x4 ar, u32x4 ai, u32x4 xr, u32x4 xi) {
+        SV_MFMA(ar, xr, re);
+        SV_MFMA(ar, xi, im);
+        SV_MFMA(ai, xi ^ 0x80008000u, re);
+        SV_MFMA(ai, xr, im);
+    };
 #undef SV_MFMA
+    // the lane's inputs: half s of the columns, 8 (2 s + e / 4) + 4 (lane / 32) + e % 4
+    f32x2 x[2][8];
+    auto fetch = [&](int s) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            x[s][e] = *reinterpret_cast<const f32x2*>(lds + (at ^ b.off(16 * s + 8 * (e / 4) + (e % 4))));
+    };
+    if (coupled) {
+        // all of them at once, so that the factors need no registers behind this
+        f32x2 w[5], f[4];
+        phases(w);
+        fetch(0);
+        fetch(1);
+        f[0] = lane >= 32 ? w[2] : f32x2{1.f, 0.f};
+        f[1] = cmul(f[0], w[0]), f[2] = cmul(f[0], w[1]), f[3] = cmul(f[1], w[1]);
+        const f32x2 high[4] = {f32x2{1.f, 0.f}, w[3], w[4], cmul(w[3], w[4])};
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            x[r / 8][r % 8] = cmul(x[r / 8][r % 8], r < 4 ? f[r] : cmul(f[r % 4], high[r / 4]));
+    }
+    // the products of half s but the largest, whose parts of the inputs go to x0
+    auto small_products = [&](int s, u32x4* x0) {
+        if (!coupled) fetch(s);
+        u32x4 xr[3], xi[3];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const f32x2 u = x[s][2 * p], v = x[s][2 * p + 1];
+            uint32_t w0, w1, w2;
+            split_bf16(u.x, v.x, w0, w1, w2, lost);
+            xr[0][p] = w0, xr[1][p] = w1, xr[2][p] = w2;
+            split_bf16(u.y, v.y, w0, w1, w2, lost);
+            xi[0][p] = w0, xi[1][p] = w1, xi[2][p] = w2;
+            asm volatile("" : "+v"(lost));  // summed here, not kept for later
+        }
+        constexpr int pa[5] = {2, 0, 1, 1, 0}, px[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+        for (int i = 0; i < 5; ++i) product(o.re[pa[i]], o.im[pa[i]], xr[px[i]], xi[px[i]]);
+        x0[0] = xr[0], x0[1] = xi[0];
         __builtin_amdgcn_sched_barrier(0);  // one half's operands at a time
     };
-    half_sum(0);
+    u32x4 x0[2], x1[2];
+    small_products(0, x0);
+    const u32x4 re0 = o.re[0], im0 = o.im[0];
     o.load(m, 1, lane);
-    half_sum(1);
+    small_products(1, x1);
+    product(re0, im0, x0[0], x0[1]);
+    product(o.re[0], o.im[0], x1[0], x1[1]);
     o.load(next, 0, lane);
+    // (an amplitude that rounds to no bf16, or is no number: its column holds no number)
+    const bool again = ((lost & 0xffffu) != 0) | (re[0] != re[0]);
+    if (__builtin_expect((b.kind & kSweepFp32) || __ballot(again) != 0, 0)) {
+        // the same sums of FP32 products, the matrix put together from its parts
+        re = f32x16{0}, im = f32x16{0};
+        f32x2 w[5];
+        if (coupled) phases(w);
+#pragma nounroll
+        for (int r = 0; r < 16; ++r) {
+            const int c = (r & 3) | (r & 12) << 1;  // the column of the lanes 0-31, that of the others is c + 4
+            f32x2 x = *reinterpret_cast<const f32x2*>(lds + (at ^ b.off(c)));
+            if (coupled) {
+                if (c & 1) x = cmul(x, w[0]);
+                if (c & 2) x = cmul(x, w[1]);
+                if (lane >= 32) x = cmul(x, w[2]);
+                if (c & 8) x = cmul(x, w[3]);
+                if (c & 16) x = cmul(x, w[4]);
+            }
+            float entry[2];
+#pragma unroll
+            for (int part = 0; part < 2; ++part) {
+                if (b.kind & kSweepFp32) {
+                    entry[part] = *lane_address<const float>(m + (part * 16 + r) * 16, uint32_t(lane) * 4);
+                    continue;
+                }
+                entry[part] = 0.f;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const uint32_t v = *lane_address<const uint32_t>(m + ((part * 3 + q) * 2 + (r >> 3)) * 64,
+                                                                     uint32_t(lane) * 16 + ((r & 6) << 1));
+                    entry[part] += __builtin_bit_cast(float, r & 1 ? v & 0xffff0000u : v << 16);
+                }
+            }
+            re = __builtin_amdgcn_mfma_f32_32x32x2f32(entry[0], x.x, re, 0, 0, 0);
+            im = __builtin_amdgcn_mfma_f32_32x32x2f32(entry[0], x.y, im, 0, 0, 0);
+            re = __builtin_amdgcn_mfma_f32_32x32x2f32(entry[1], -x.y, re, 0, 0, 0);
+            im = __builtin_amdgcn_mfma_f32_32x32x2f32(entry[1], x.x, im, 0, 0, 0);
+        }
+    }
 #pragma unroll
     for (int r = 0; r < 16; ++r)
         *reinterpret_cast<f32x2*>(lds + (at ^ b.off(8 * (r / 4) + (r % 4)))) = f32x2{re[r], im[r]};
@@ -863,6 +923,35 @@ uint64_t qubit_mask(const FusedBlock& b)
     return m;
 }
 
+// Whether FP32 products leave less error than block5_split's on some amplitudes: a
+// real matrix (or i times one) of at most two entries a row, not all of a bf16's
+// 8 bits.  One rotation among CNOTs on real amplitudes: FP32 3.2e-8 to 4.0e-8 of the
+// state's 2-norm, the parts up to 10% more, since FP32 rounds no more often there
+// and leaves nothing out (on complex amplitudes 5.5e-8 and 3.2e-8 to 4.1e-8).  With
+// two rotations the parts leave 0.84-0.89 of FP32's error, with five 0.41.
+bool few_products(const FusedBlock& b)
+{
+    const int d = 1 << b.k;
+    bool re = false, im = false, wide = false;
+    int most = 0;
+    for (int i = 0; i < d; ++i) {
+        int row = 0;
+        for (int c = 0; c < d; ++c) {
+            const float v[2] = {float(b.m[2 * (size_t(i) * d + c)]), float(b.m[2 * (size_t(i) * d + c) + 1])};
+            re |= v[0] != 0.f;
+            im |= v[1] != 0.f;
+            row += v[0] != 0.f || v[1] != 0.f;
+            for (float f : v) {
+                uint32_t w;
+                std::memcpy(&w, &f, 4);
+                wide |= (w & 0xffffu) != 0;
+            }
+        }
+        most = std::max(most, row);
+    }
+    return most <= 2 && !(re && im) && wide;
+}
+
 // The qubits that decide which blocks commute with b: its targets and the
 // qubits its phases depend on.
 uint64_t touched_mask(const FusedBlock& b)
@@ -928,11 +1017,12 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
     const int T = std::max(tile_bits(dt) + (n >= kReorderQubits && !rules.keep_order), one_tile ? n : 0);
     const bool coupled_large = n <= lone_qubits(dt);
     const int lo = min_run_bits(dt);
+    const bool split = dt == SV_C64 && n >= kReorderQubits && !rules.keep_order;
     auto eligible = [&](const FusedBlock& b) {
         if (b.diagonal || b.k > 5) return false;
         // coupled blocks: where the phases have a kernel (block5_split), and no
         // padding qubit could be a coupled one
-        if (b.n_couple > 0 && !(dt == SV_C64 && n >= kReorderQubits && !rules.keep_order && b.k == 5)) return false;
+        if (b.n_couple > 0 && !(split && b.k == 5)) return false;
         if (n > (dt == SV_C64 ? kMaxSweepQubitsC64 : kMaxSweepQubitsC128)) return false;
         if (rules.pad_all) return true;
         // larger states: blocks on 2-4 qubits are swept as five-qubit ones
@@ -954,7 +1044,7 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
         st.blocks = std::move(take);
         st.padded = rules.pad_all || n >= kPadQubits;
         for (int i : st.blocks) st.coupled = st.coupled || (st.multi && blocks[i].n_couple > 0);
-        st.split = dt == SV_C64 && n >= kReorderQubits && !rules.keep_order;
+        st.split = split;
         if (st.multi) {
             st.tile_bits = T;
             if (T > tile_bits(dt) && !one_tile && __builtin_popcountll(on >> lo) <= tile_bits(dt) - lo) --st.tile_bits;
@@ -1129,9 +1219,12 @@ void pack5(const FusedBlock& b, int n, R* o)
 
 // The operands of block5_split: part (Re M, Im M), piece, half of the columns
 // s, lane: row lane % 32, columns 8 (2 s + e / 4) + 4 (lane / 32) + e % 4 for e < 8.
-void pack5_split(const FusedBlock& b, uint16_t* o)
+// Returns whether the pieces hold the entries (those of 2^-110 and more, as far as
+// the first is not rounded up to infinity).
+bool pack5_split(const FusedBlock& b, uint16_t* o)
 {
     const int d = 1 << b.k;
+    bool hold = true;
     std::fill(o, o + 6 * 1024, uint16_t(0));
     for (int e = 0; e < 32; e += d)  // the diagonal blocks of M (x) I
         for (int i = 0; i < d; ++i)
@@ -1149,7 +1242,23 @@ void pack5_split(const FusedBlock& b, uint16_t* o)
                         std::memcpy(&f, &w, 4);
                         v -= f;
                     }
+                    hold &= v == 0.f;
                 }
+    return hold;
+}
+
+// The same matrix for FP32 products (kSweepFp32): part, step r, lane: row lane % 32,
+// column 8 (r / 4) + 4 (lane / 32) + r % 4.
+void pack5_fp32(const FusedBlock& b, float* o)
+{
+    const int d = 1 << b.k;
+    for (int part = 0; part < 2; ++part)
+        for (int r = 0; r < 16; ++r)
+            for (int lane = 0; lane < 64; ++lane) {
+                const int row = lane % 32, c = 8 * (r / 4) + 4 * (lane / 32) + r % 4;
+                o[(part * 16 + r) * 64 + lane] =
+                    row / d == c / d ? float(b.m[2 * (size_t(row % d) * d + c % d) + part]) : 0.f;
+            }
 }
 
 }  // namespace
@@ -1200,7 +1309,7 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, Sw
                 used |= 1u << p;
             }
         const int left = choose_lanes(dt, T, used, s.grp, group);
-        if (b.n_couple > 0) s.kind = kSweepCoupled5;
+        if (b.n_couple > 0) s.kind |= kSweepCoupled;
         if (st.coupled) {
             // turns of each target's phase, by the coupled qubit's place: a bit
             // of the group index, or outside the tile
@@ -1226,17 +1335,20 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, Sw
             std::memcpy(mat + sweep_matrix_stride(true), &cp, sizeof cp);
         }
         for (int a = 0; a < k; ++a) s.bit[a] = slot_bytes(dt, 1u << pos[a]);
-        desc[j] = s;
         if (s.kind == kSweepRows5)
             std::memcpy(mat, b.m, 1024 * 2 * sizeof(double));
         else if (k < 5)
             pack_matrix(dt, 12, k, 0, b.m, 0, mat);
-        else if (st.split)
-            pack5_split(b, reinterpret_cast<uint16_t*>(mat));
-        else if (dt == SV_C64)
+        else if (st.split) {
+            if (few_products(b) || !pack5_split(b, reinterpret_cast<uint16_t*>(mat))) {
+                s.kind |= kSweepFp32;
+                pack5_fp32(b, reinterpret_cast<float*>(mat));
+            }
+        } else if (dt == SV_C64)
             pack5(b, n, reinterpret_cast<float*>(mat));
         else
             pack5(b, n, reinterpret_cast<double*>(mat));
+        desc[j] = s;
     }
 }
 

@@ -89,6 +89,7 @@ static void sincospif(float x, float* s, float* c)
 #define __dsub_rn(x, y) ((x) - (y))
 #define __dmul_rn(x, y) ((x) * (y))
 #define __shfl_xor(x, mask, width) no_lanes(x)
+#define __ballot(x) uint64_t(no_lanes(x))
 #define __builtin_amdgcn_readlane(x, l) no_lanes(x)
 #define __builtin_amdgcn_readfirstlane(x) (x)
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
