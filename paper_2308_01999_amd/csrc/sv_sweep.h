@@ -40,13 +40,14 @@ constexpr uint32_t sweep_matrix_stride(bool c64) { return c64 ? 12u << 10 : 16u 
 
 // The phases of a block of coupled fusion, behind each matrix of a coupled sweep.
 // Target a's phase is the sum of the terms of the coupled qubits that are set,
-// as fixed-point turns, whose sum wraps by itself.
+// as fixed-point turns of 2^-64, whose sum wraps by itself.
 struct SweepCouple {
-    uint64_t out[5][36];  // of qubit q outside the tile, 2^-64 turns
-    uint32_t in[5][8];    // of bit j of the group index, 2^-32 turns
-    uint32_t pad[112];
+    uint64_t out[5][36];   // the term of qubit q outside the tile
+    uint64_t wave[5][8];   // the terms of the qubits that a wave's groups share
+    uint64_t lane[5][32];  // and of those that a lane's group adds, lane % 32
+    uint32_t pad[8];
 };
-static_assert(sizeof(SweepCouple) == 2048, "a matrix behind it stays aligned");
+static_assert(sizeof(SweepCouple) == 3072, "a matrix behind it stays aligned");
 
 // Geometry of a sweep (kernel argument).
 constexpr int kSweepMaxHigh = 12;

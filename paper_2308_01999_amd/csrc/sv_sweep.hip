@@ -19,8 +19,8 @@
 // more).  A tile is 32 KiB (64 KiB and 512 threads where plan_sweeps says) and a workgroup 256
 // threads and one tile: the runs of 128 bytes that this leaves for eight free
 // bits stream at 4.6-5.4 TB/s, and four workgroups a CU, at most
-// 128 vector registers a thread, hide each other's loads, stores and
-// barriers.  They do it better than three that load their next tile during a
+// 128 vector registers a thread (the coupled forms spill 11 around a tile's blocks,
+// none inside them), hide each other's loads, stores and barriers.  They do it better than three that load their next tile during a
 // tile's blocks: loads return in order, so a matrix behind a tile waits for
 // HBM (28 qubits, sweeps of 4 blocks: complex64 1.38 -> 1.18 ms, complex128 on
 // 27 qubits 1.91 -> 1.83).
@@ -253,12 +253,13 @@ __device__ __forceinline__ f32x2 cmul(f32x2 a, f32x2 b)
     return f32x2{fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.x, b.y, a.y * b.x)};
 }
 
-// exp(2 pi i u / 2^32) by the Taylor polynomials of sine and cosine on the
+// exp(2 pi i u / 2^64) by the Taylor polynomials of sine and cosine on the
 // quadrant's [-pi/4, pi/4] (the terms left out are below 2e-9).
-__device__ __forceinline__ f32x2 unit(uint32_t u)
+__device__ __forceinline__ f32x2 unit(uint64_t u)
 {
-    const uint32_t q = (u + 0x20000000u) >> 30;
-    const float y = float(int32_t(u - (q << 30))) * 1.46291807926715969e-9f;  // 2 pi / 2^32
+    const uint32_t hi = uint32_t(u >> 32), q = (hi + 0x20000000u) >> 30;
+    const float turn = fmaf(float(uint32_t(u)), 0x1p-32f, float(int32_t(hi - (q << 30))));
+    const float y = turn * 1.46291807926715969e-9f;  // 2 pi / 2^32
     const float z = y * y;
     const float sn = fmaf(y * z, fmaf(z, fmaf(z, fmaf(z, 2.75573192e-6f, -1.98412698e-4f), 8.33333333e-3f), -1.66666667e-1f), y);
     const float cs = fmaf(z, fmaf(z, fmaf(z, fmaf(z, fmaf(z, -2.75573192e-7f, 2.48015873e-5f), -1.38888889e-3f), 4.16666667e-2f), -0.5f), 1.f);
@@ -303,26 +304,24 @@ struct SplitOps {
 // 93.4 ms, error 6.1e-7).  A lane's outputs are its inputs' slots.
 // COUPLED: a block with kSweepCoupled first multiplies each amplitude by its
 // phase, exp of the sum of the phases of the targets set in it; turns: their
-// parts from outside the tile, cp: from the group index.
+// parts from outside the tile and from the wave's part of the group index, cp: from
+// the lane's.
 template <bool COUPLED>
 __device__ __forceinline__ void block5_split(char* lds, const SweepBlock& b, const u32x4* __restrict__ m,
                                              const u32x4* __restrict__ next, SplitOps& o, const LaneBits& lb,
                                              uint32_t wave, int lane, const SweepCouple* __restrict__ cp,
-                                             const uint32_t* turns)
+                                             const uint64_t* turns)
 {
     uint32_t at = lane_part<5>(lb, b.grp) ^ wave_part<3>(wave, b.grp + 5) ^ (lb.m[5] & b.off(4));
     asm volatile("" : "+v"(at));
     const bool coupled = COUPLED && (b.kind & kSweepCoupled);
     // the phase factor of each target
     auto phases = [&](f32x2* w) {
+        uint64_t u[5];
 #pragma unroll
-        for (int a = 0; a < 5; ++a) {
-            uint32_t u = turns[a] + ((wave & 1u) ? cp->in[a][5] : 0u) + ((wave & 2u) ? cp->in[a][6] : 0u) +
-                         ((wave & 4u) ? cp->in[a][7] : 0u);
+        for (int a = 0; a < 5; ++a) u[a] = *lane_address<const uint64_t>(cp->lane[a], uint32_t(lane & 31) * 8);
 #pragma unroll
-            for (int j = 0; j < 5; ++j) u += lb.m[j] & cp->in[a][j];
-            w[a] = unit(u);
-        }
+        for (int a = 0; a < 5; ++a) w[a] = unit(u[a] + turns[a]);
     };
     f32x16 re = {0}, im = {0};
     uint32_t lost = 0;
@@ -682,7 +681,7 @@ template <typename R, int T, int NT, bool SMALL, bool SPLIT = false, bool COUPLE
           bool SUMS = false>
 __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepBlock* __restrict__ blocks,
                                             const char* __restrict__ mats, const SweepArgs& a, uint64_t wg,
-                                            char* lds, const ZSums& zs, [[maybe_unused]] uint32_t* turns)
+                                            char* lds, const ZSums& zs, [[maybe_unused]] uint64_t* turns)
 {
     using A = Amp<R>;
     using W = typename A::W;
@@ -750,15 +749,22 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
         }
         if (FIRST && tid == 0) buf[0][0] = 1;
         if constexpr (COUPLED) {
-            // the phases from outside the tile of every block and target,
+            // the phases of every block, wave and target but the lanes' parts,
             // while the tile is on its way
             const uint64_t origin = uint64_t(base - psi) / A::kBytes;
-            const int bits = 64 - __builtin_clzll(a.amps - 1);
-            for (int j = tid; j < 5 * a.n_blocks; j += NT) {
-                const uint64_t* p = phases(j / 5)->out[j % 5];
-                uint64_t u = 0x80000000u;
-                for (int q = 0; q < bits; ++q) u += ((origin >> q) & 1) ? p[q] : 0;
-                turns[j / 5 * 8 + j % 5] = uint32_t(u >> 32);
+            for (int j = tid; j < 5 * (NT / 64) * a.n_blocks; j += NT) {
+                const SweepCouple* c = phases(j / (5 * (NT / 64)));
+                const uint64_t* p = c->out[j % 5];
+                uint64_t u = c->wave[j % 5][j / 5 % (NT / 64)];
+#pragma nounroll
+                for (int q0 = 0; q0 < 36; q0 += 12) {
+                    uint64_t v[12];
+#pragma unroll
+                    for (int q = 0; q < 12; ++q) v[q] = p[q0 + q];
+#pragma unroll
+                    for (int q = 0; q < 12; ++q) u += ((origin >> (q0 + q)) & 1) ? v[q] : 0;
+                }
+                turns[j] = u;
             }
         }
 #pragma unroll
@@ -778,7 +784,7 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
                 if constexpr (SPLIT) {
                     block5_split<COUPLED>(lds, b, reinterpret_cast<const u32x4*>(matrix(i)),
                                           reinterpret_cast<const u32x4*>(matrix(next)), split, lb, uint32_t(wave), lane,
-                                          phases(i), turns + 8 * i);
+                                          phases(i), turns + 5 * (i * (NT / 64) + wave));
                 } else {
                     Ops<R> o;
                     block5<false, false>(lds, b, matrix(i), o, lb, uint32_t(wave), lane);
@@ -855,7 +861,8 @@ __global__ __launch_bounds__(NT, SMALL ? 1 : 4) void k_sweep(char* __restrict__ 
                                                             const char* __restrict__ mats, SweepArgs a)
 {
     __shared__ __align__(16) char lds[Amp<R>::kBytes << T];
-    __shared__ uint32_t turns[COUPLED ? 8 * kMaxSweepBlocks : 1];
+    // (7.5 KiB: still four workgroups on the CU's 160 KiB, two of the larger tile)
+    __shared__ uint64_t turns[COUPLED ? 5 * (NT / 64) * kMaxSweepBlocks : 1];
     sweep_tiles<R, T, NT, SMALL, SPLIT, COUPLED>(psi, blocks, mats, a, blockIdx.x, lds,
                                                  ZSums{nullptr, -1, nullptr, nullptr}, turns);
 }
@@ -1326,11 +1333,15 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, Sw
                         while (r < st.args.n_hi && st.hi_pos[r] != q) ++r;
                         p = r < st.args.n_hi ? L + r : -1;
                     }
-                    if (p < 0)  // in two steps: 2^64 does not fit
-                        cp.out[a][q] = uint64_t(std::llround(std::ldexp(turn, 62))) << 2;
-                    else
-                        for (int j = 0; j < left; ++j)
-                            if (group[j] == p) cp.in[a][j] = uint32_t(std::llround(std::ldexp(turn, 32)));
+                    const uint64_t u = uint64_t(std::llround(std::ldexp(turn, 62))) << 2;  // (2^64 does not fit)
+                    if (p < 0) cp.out[a][q] = u;
+                    for (int j = 0; j < left; ++j) {
+                        if (group[j] != p) continue;
+                        if (j < 5)
+                            for (int l = 0; l < 32; ++l) cp.lane[a][l] += (l >> j) & 1 ? u : 0;
+                        else
+                            for (int w = 0; w < 8; ++w) cp.wave[a][w] += (w >> (j - 5)) & 1 ? u : 0;
+                    }
                 }
             std::memcpy(mat + sweep_matrix_stride(true), &cp, sizeof cp);
         }
