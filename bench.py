@@ -291,15 +291,13 @@ def run_leg(P, W, torch, H, gates, n, dt, kmax, shots, steps, warmup):
 
 def seeds_leg(P, W, torch, H, n, depth, kmax, seeds):
     """The headline circuit at seeds 0..seeds-1 (the brickwork construction
-    with other angles: the same qubit windows, so the handle's tile choices
-    from the timed legs carry over), fused at kmax, one pass each from
-    |0..0>, timed with HIP events on the handle's stream, complex64 and
-    complex128: GB/s of the fused sweeps per seed."""
+    with other angles: the same qubit windows), fused at kmax, one pass each
+    from |0..0> by one call (blocks share sweeps), timed with HIP events on the
+    handle's stream, complex64 and complex128: time per seed."""
     import numpy as np
     out = {}
-    for dt, s in (("c64", 8), ("c128", 16)):
+    for dt in ("c64", "c128"):
         st = P.State(H, n, dt)
-        sweep = 2 * (1 << n) * s
         vals = []
         for seed in range(seeds):
             f = P.fuse(W.brickwork(n, depth, seed), kmax)
@@ -309,19 +307,19 @@ def seeds_leg(P, W, torch, H, n, depth, kmax, seeds):
             P.sv_apply_fused(st.s, f.f)
             e1.record(H.stream)
             e1.synchronize()
-            vals.append(f.count * sweep / (e0.elapsed_time(e1) * 1e-3) / 1e9)
+            vals.append(e0.elapsed_time(e1))
             f.free()
         st.close()
-        out[dt] = {"seeds": seeds, "mean_GBps": round(float(np.mean(vals)), 1),
-                   "min_GBps": round(float(np.min(vals)), 1), "max_GBps": round(float(np.max(vals)), 1),
-                   "mean_frac_of_8TBps": round(float(np.mean(vals)) / HBM_PEAK_GBS, 4)}
+        out[dt] = {"seeds": seeds, "mean_ms": round(float(np.mean(vals)), 2), "min_ms": round(float(np.min(vals)), 2),
+                   "max_ms": round(float(np.max(vals)), 2)}
         torch.cuda.synchronize()
     return out
 
 
 def kmax_leg(P, W, torch, H, gates, n):
     """The same circuit unfused (one sweep per gate, controlled gates touching
-    only their 2^(n-c) amplitudes) and fused at kmax = 4, 5, 6, complex64 and
+    only their 2^(n-c) amplitudes) and fused at kmax = 4, 5, 6 (blocks share
+    sweeps, so that their number is no number of bytes), complex64 and
     complex128: one warm pass, then one pass timed with HIP events on the
     handle's stream around all its sweeps."""
     out = {}
@@ -332,15 +330,12 @@ def kmax_leg(P, W, torch, H, gates, n):
             if kmax == 0:
                 entries = P.gate_entries(gates)
                 nbytes = sum(2 * (1 << (n - len(e[2]))) * s for e in entries)
-                sweeps = len(entries)
 
                 def go():
                     for t, m, c, cv, adj in entries:
                         st.apply_matrix(m, t, c, cv, adjoint=adj)
             else:
                 f = P.fuse(gates, kmax)
-                sweeps = f.count
-                nbytes = sweeps * 2 * (1 << n) * s
 
                 def go():
                     P.sv_apply_fused(st.s, f.f)
@@ -352,9 +347,11 @@ def kmax_leg(P, W, torch, H, gates, n):
             e1.synchronize()
             ms = e0.elapsed_time(e1)
             if kmax:
+                res[f"kmax{kmax}"] = {"blocks": f.count, "apply_ms": round(ms, 2)}
                 f.free()
-            res["unfused" if kmax == 0 else f"kmax{kmax}"] = {
-                "sweeps": sweeps, "apply_ms": round(ms, 2), "GBps": round(nbytes / (ms * 1e-3) / 1e9, 1)}
+            else:
+                res["unfused"] = {"sweeps": len(entries), "apply_ms": round(ms, 2),
+                                  "GBps": round(nbytes / (ms * 1e-3) / 1e9, 1)}
         base = res["unfused"]["apply_ms"]
         for k in ("kmax4", "kmax5", "kmax6"):
             res[k]["speedup_vs_unfused"] = round(base / res[k]["apply_ms"], 2)
@@ -633,7 +630,7 @@ def diagonal_leg(P, W, torch, H, n, reps=10):
     stream); then the n-qubit QFT fused with dense blocks only (k <= 5)
     against dense plus diagonal blocks (k <= 5, diagonal k <= 10) and against
     coupled fusion (k <= 5, the controlled phases carried as couplings of
-    the dense blocks): sweeps and apply time of one timed pass after one
+    the dense blocks): blocks and apply time of one timed pass after one
     untimed pass."""
     import numpy as np
     out = {}
@@ -668,8 +665,7 @@ def diagonal_leg(P, W, torch, H, n, reps=10):
             e1.record(H.stream)
             e1.synchronize()
             ms = e0.elapsed_time(e1)
-            res[label] = {"sweeps": f.count, "diagonal_sweeps": ndiag, "apply_ms": round(ms, 2),
-                          "GBps": round(f.count * sweep / (ms * 1e-3) / 1e9, 1)}
+            res[label] = {"blocks": f.count, "diagonal_blocks": ndiag, "apply_ms": round(ms, 2)}
             f.free()
         res["qft_speedup"] = round(res["qft_dense_only"]["apply_ms"] / res["qft_dense_and_diagonal"]["apply_ms"], 2)
         res["qft_coupled_speedup"] = round(res["qft_dense_only"]["apply_ms"] / res["qft_coupled"]["apply_ms"], 2)
@@ -802,8 +798,7 @@ def large_leg(P, W, torch, H):
             e1.record(H.stream)
             e1.synchronize()
             ms = e0.elapsed_time(e1)
-            out[dt][label] = {"gates": len(g), "fused_blocks": fc.count, "apply_ms": round(ms, 1),
-                              "GBps": round(fc.count * sweep / (ms * 1e-3) / 1e9, 1)}
+            out[dt][label] = {"gates": len(g), "fused_blocks": fc.count, "apply_ms": round(ms, 1)}
             fc.free()
         # 2^20 samples of the QFT's output state from seeded uniforms, in
         # device memory (one untimed call, then one timed)
@@ -863,8 +858,6 @@ def batched_leg(P, W, torch, H, count, steps, warmup, sample, check_per_n=4):
     tune_s, build_s = b.host_times()
     blocks = b.blocks()
     state_gb = sum((1 << n) * 8 for n in ns) / 1e9
-    # every fused block reads and writes its state once
-    sweep_bytes = sum(int(nb) * 2 * (1 << n) * 8 for nb, n in zip(blocks, ns))
     # errors against the oracle on a sample spread over every qubit count
     check = []
     for n in sorted(set(ns)):
@@ -906,8 +899,6 @@ def batched_leg(P, W, torch, H, count, steps, warmup, sample, check_per_n=4):
         "p99_ms": round(1e3 * float(np.percentile(lat, 99)), 3),
         "latency_clock": "device wall clock, from the run's start to each circuit's state and expectations written",
         "circuits_per_s": round(count / float(np.median(kts)), 1),
-        "sweep_GB": round(sweep_bytes / 1e9, 2),
-        "effective_GBps": round(sweep_bytes / float(np.median(kts)) / 1e9, 1),
         "fusion_widths": widths,
         "plans": plans,
         "fused_blocks_total": int(blocks.sum()),
