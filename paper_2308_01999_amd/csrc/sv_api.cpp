@@ -833,11 +833,14 @@ struct ProgramStep {
     size_t bytes = 0;  // of its device buffer, a multiple of 256
 };
 
-void make_steps(const sv_state_s* s, const sv_fused_s* f, int first, int end, std::vector<ProgramStep>& out)
+void make_steps(const sv_state_s* s, const sv_fused_s* f, int first, int end, bool recorded,
+                std::vector<ProgramStep>& out)
 {
     std::vector<SweepStep> plan;
     if (s->h->tile_mode == SV_TILE_AUTO) {
-        plan = plan_sweeps(s->dt, s->n, s->h->cu_count, f->blocks, first, end);
+        SweepRules rules;
+        rules.few_alone = !recorded;
+        plan = plan_sweeps(s->dt, s->n, s->h->cu_count, f->blocks, first, end, rules);
     } else {
         for (int b = first; b < end; ++b) {
             SweepStep one;
@@ -885,7 +888,7 @@ void apply_fused_blocks(sv_state_s* s, sv_fused_s* f, int first, int count)
     SV_CHECK(first >= 0 && count >= 0 && first <= f->n_blocks && count <= f->n_blocks - first,
              "block range out of bounds");
     std::vector<ProgramStep> steps;
-    make_steps(s, f, first, first + count, steps);
+    make_steps(s, f, first, first + count, false, steps);
     // staged in segment-sized batches: one copy per batch of steps
     const size_t seg = kMatRingBytes / kMatRingSegments;
     size_t i = 0;
@@ -948,7 +951,7 @@ sv_status_t sv_graph_create(sv_state_t s, sv_fused_t f, sv_graph_t* out)
         SV_CHECK(f != nullptr, "fused gates are NULL");
         sv_handle_s* h = s->h;
         std::vector<ProgramStep> steps;
-        make_steps(s, f, 0, f->n_blocks, steps);
+        make_steps(s, f, 0, f->n_blocks, true, steps);
         std::vector<size_t> offs(steps.size());
         size_t bytes = 0;
         for (size_t i = 0; i < steps.size(); ++i) {

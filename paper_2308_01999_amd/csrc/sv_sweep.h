@@ -11,7 +11,7 @@
 namespace sv {
 
 // How a block is swept: 1-4 qubits as they are (states of one tile), five on
-// the matrix cores or on the vector units (block5_rows); added to kSweepMfma5
+// the matrix cores or on the vector units (block_rows); added to kSweepMfma5
 // of a split sweep: the block is coupled, and its products are FP32.
 constexpr int32_t kSweepMfma5 = 5, kSweepRows5 = 6;
 constexpr int32_t kSweepCoupled = 16, kSweepFp32 = 32;
@@ -78,6 +78,7 @@ struct SweepStep {
 };
 
 struct SweepRules {
+    bool few_alone = false;   // calls of few blocks on small states launch each on its own
     bool keep_order = false;  // blocks in program order on states of any size
     bool pad_all = false;     // every block is swept as a five-qubit one
     int spread_lo = 0;        // > 0: tiles with runs of at most 1 KiB, filled up with free bits from here up

@@ -427,17 +427,21 @@ __device__ __forceinline__ void block5_split(char* lds, const SweepBlock& b, con
 }
 
 // complex64, four qubits, on v_mfma_f32_16x16x4_f32 (the chain of
-// k_tile_c64_k4), four column tiles of 16 groups per wave.
+// k_tile_c64_k4), four column tiles of 16 groups per wave of NT / 64, as far as
+// the state of `amps` amplitudes has groups.
+template <int NT>
 __device__ __forceinline__ void block4(char* lds, const SweepBlock& b, const f32x4* __restrict__ m, const LaneBits& lb,
-                                       uint32_t wave, int lane)
+                                       uint32_t wave, int lane, uint64_t amps)
 {
-    constexpr int steps = 4;
+    const uint32_t tiles = amps >> 8 ? uint32_t(amps >> 8) : 1u;
     const int q = lane >> 4;
     const f32x4 ar = m[lane], ai = m[64 + lane], as = m[128 + lane];
     const uint32_t lin = ((q & 1) ? b.off(1) : 0u) ^ ((q & 2) ? b.off(2) : 0u);
     const uint32_t lout = ((q & 1) ? b.off(4) : 0u) ^ ((q & 2) ? b.off(8) : 0u);
-    for (int c = 0; c < steps; ++c) {
-        const uint32_t base = lane_part<4>(lb, b.grp) ^ wave_part<5>(wave * steps + uint32_t(c), b.grp + 4);
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t c = wave + uint32_t(i) * (NT / 64);
+        if (c >= tiles) break;
+        const uint32_t base = lane_part<4>(lb, b.grp) ^ wave_part<5>(c, b.grp + 4);
         f32x2 x[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) x[s] = *reinterpret_cast<const f32x2*>(lds + (base ^ lin ^ b.off(4 * s)));
@@ -491,52 +495,70 @@ __device__ __forceinline__ void block5(char* lds, const SweepBlock& b, const f64
     rows(1, second);
 }
 
-// k <= 3 (complex64) or k <= 4 (complex128) on the vector units, one group
-// per thread and step, in the order of k_apply_dense.
+// k <= 3 on the vector units, in the order of k_apply_dense.  A thread takes all
+// its groups (16 amplitudes of complex64, 8 of complex128) at once, so that the
+// matrix is read once, as far as the state of `amps` amplitudes has groups (16
+// blocks of three qubits on 10 qubits complex64: 79 -> 61 us).
 template <typename R, int K, int T, int NT>
 __device__ __forceinline__ void block_small(char* lds, const SweepBlock& b, const typename Amp<R>::V* __restrict__ m,
-                                            const LaneBits& lb, uint32_t wave)
+                                            const LaneBits& lb, uint32_t wave, uint64_t amps)
 {
     using V = typename Amp<R>::V;
-    constexpr int D = 1 << K;
-    for (uint32_t w = wave; w < (1u << (T - K - 6)); w += NT / 64) {
-        asm volatile("" ::: "memory");  // the matrix stays out of the registers
-        const uint32_t base = lane_part<6>(lb, b.grp) ^ wave_part<T - K - 6>(w, b.grp + 6);
-        V v[D];
+    constexpr int D = 1 << K, kWaves = NT / 64, kAll = 1 << (T - K - 6), G = kAll > kWaves ? kAll / kWaves : 1;
+    const uint32_t groups = amps >> (K + 6) ? uint32_t(amps >> (K + 6)) : 1u;  // in units of a wave's 64
+    if (wave >= groups || wave >= kAll) return;
+    asm volatile("" ::: "memory");  // the matrix stays out of the registers
+    const uint32_t lane = lane_part<6>(lb, b.grp);
+    uint32_t base[G];
+    V v[G][D];
 #pragma unroll
-        for (int c = 0; c < D; ++c) v[c] = *reinterpret_cast<const V*>(lds + (base ^ b.off(c)));
+    for (int g = 0; g < G; ++g) {
+        base[g] = lane ^ wave_part<T - K - 6>(wave + uint32_t(g) * kWaves, b.grp + 6);
+        if (g > 0 && wave + uint32_t(g) * kWaves >= groups) break;
 #pragma unroll
-        for (int r = 0; r < D; ++r) {
+        for (int c = 0; c < D; ++c) v[g][c] = *reinterpret_cast<const V*>(lds + (base[g] ^ b.off(c)));
+    }
+#pragma unroll
+    for (int r = 0; r < D; ++r) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (g > 0 && wave + uint32_t(g) * kWaves >= groups) break;
             R re = 0, im = 0;
 #pragma unroll
             for (int c = 0; c < D; ++c) {
                 const V e = m[r * D + c];
-                re = fma(e.x, v[c].x, re);
-                re = fma(-e.y, v[c].y, re);
-                im = fma(e.x, v[c].y, im);
-                im = fma(e.y, v[c].x, im);
+                re = fma(e.x, v[g][c].x, re);
+                re = fma(-e.y, v[g][c].y, re);
+                im = fma(e.x, v[g][c].y, im);
+                im = fma(e.y, v[g][c].x, im);
             }
-            *reinterpret_cast<V*>(lds + (base ^ b.off(r))) = V{re, im};
+            *reinterpret_cast<V*>(lds + (base[g] ^ b.off(r))) = V{re, im};
         }
     }
 }
 
-// complex128, five qubits, states of fewer than 11 qubits: on the vector units
-// in the order of k_apply_dense, one group per lane and 8 rows per wave (64
-// groups, four waves).  Every wave reads its groups' inputs before any writes.
-__device__ __forceinline__ void block5_rows(char* lds, const SweepBlock& b, const f64x2* __restrict__ m,
-                                            const LaneBits& lb, int wave)
+// complex128, five qubits (states of fewer than 11 qubits) and four: on the vector
+// units in the order of k_apply_dense, one group per lane.  A tile has fewer
+// groups than the workgroup lanes, so each wave takes 8 of its groups' rows (16
+// blocks of four qubits on 10 qubits, all rows by half of the waves: 148 us, now
+// 102).  Every wave reads its groups' inputs before any writes.
+template <int K, int T, int NT>
+__device__ __forceinline__ void block_rows(char* lds, const SweepBlock& b, const f64x2* __restrict__ m,
+                                           const LaneBits& lb, int wave)
 {
-    const uint32_t base = lane_part<6>(lb, b.grp);
-    f64x2 v[32], y[8];
+    constexpr int D = 1 << K, kAll = 1 << (T - K - 6), kRows = D * kAll / (NT / 64);
+    static_assert(kRows == 8, "rows of a thread");
+    const int first = wave / kAll * kRows;
+    const uint32_t base = lane_part<6>(lb, b.grp) ^ wave_part<T - K - 6>(uint32_t(wave % kAll), b.grp + 6);
+    f64x2 v[D], y[kRows];
 #pragma unroll
-    for (int c = 0; c < 32; ++c) v[c] = *reinterpret_cast<const f64x2*>(lds + (base ^ b.off(c)));
+    for (int c = 0; c < D; ++c) v[c] = *reinterpret_cast<const f64x2*>(lds + (base ^ b.off(c)));
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const f64x2* row = m + (wave * 8 + r) * 32;
+    for (int r = 0; r < kRows; ++r) {
+        const f64x2* row = m + (first + r) * D;
         double re = 0, im = 0;
 #pragma unroll
-        for (int c = 0; c < 32; ++c) {
+        for (int c = 0; c < D; ++c) {
             re = fma(row[c].x, v[c].x, re);
             re = fma(-row[c].y, v[c].y, re);
             im = fma(row[c].x, v[c].y, im);
@@ -546,7 +568,7 @@ __device__ __forceinline__ void block5_rows(char* lds, const SweepBlock& b, cons
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) *reinterpret_cast<f64x2*>(lds + (base ^ b.off(wave * 8 + r))) = y[r];
+    for (int r = 0; r < kRows; ++r) *reinterpret_cast<f64x2*>(lds + (base ^ b.off(first + r))) = y[r];
 }
 
 // The first 16 words of a block's descriptor (all that a five-qubit block
@@ -812,15 +834,15 @@ __device__ __forceinline__ void sweep_tiles(char* __restrict__ psi, const SweepB
                 }
                 const auto* mv = reinterpret_cast<const typename A::V*>(matrix(i));
                 if constexpr (sizeof(R) == 8 && NT == 256)
-                    if (b.kind == kSweepRows5) block5_rows(lds, b, mv, lb, wave);
-                if (b.kind == 1) block_small<R, 1, T, NT>(lds, b, mv, lb, uint32_t(wave));
-                if (b.kind == 2) block_small<R, 2, T, NT>(lds, b, mv, lb, uint32_t(wave));
-                if (b.kind == 3) block_small<R, 3, T, NT>(lds, b, mv, lb, uint32_t(wave));
+                    if (b.kind == kSweepRows5) block_rows<5, T, NT>(lds, b, mv, lb, wave);
+                if (b.kind == 1) block_small<R, 1, T, NT>(lds, b, mv, lb, uint32_t(wave), a.amps);
+                if (b.kind == 2) block_small<R, 2, T, NT>(lds, b, mv, lb, uint32_t(wave), a.amps);
+                if (b.kind == 3) block_small<R, 3, T, NT>(lds, b, mv, lb, uint32_t(wave), a.amps);
                 if (b.kind == 4) {
                     if constexpr (sizeof(R) == 8)
-                        block_small<R, 4, T, NT>(lds, b, mv, lb, uint32_t(wave));
+                        block_rows<4, T, NT>(lds, b, mv, lb, wave);
                     else
-                        block4(lds, b, matrix(i), lb, uint32_t(wave), lane);
+                        block4<NT>(lds, b, matrix(i), lb, uint32_t(wave), lane, a.amps);
                 }
             };
             for (int i = 0; i < a.n_blocks; i += 2) {
@@ -923,6 +945,20 @@ constexpr int min_run_bits(sv_dtype_t dt) { return dt == SV_C64 ? 4 : 3; }
 // index bits below the fifth highest one) fits 32 bits.
 constexpr int kMaxSweepQubitsC64 = 34, kMaxSweepQubitsC128 = 33;
 
+// States of one tile and little more: a block's own kernel in launches of the
+// fastest ones (14 us for the first of a call, 2 for each more; the first block of a
+// sweep takes 17-22 us, a second 24).  Calls of up to kFewLaunches take every
+// block on its own: 1, 2, 4 and 6 blocks of two qubits on 10 qubits complex64 14, 17, 22 and 27 us
+// against 17, 24, 27 and 31 as a sweep; from seven launches on a call waits
+// for the device, 65 us against 34.  (A recorded graph has no such cost.)
+constexpr int kFewLaunches = 6;
+int lone_launches(sv_dtype_t dt, int n, const FusedBlock& b)
+{
+    if (b.k <= 3 || b.diagonal) return 1;
+    if (dt == SV_C64) return b.k == 4 ? (n < 12 ? 1 : 2) : (n < 12 ? 2 : 4);
+    return b.k == 4 ? 4 : kFewLaunches + 1;
+}
+
 uint64_t qubit_mask(const FusedBlock& b)
 {
     uint64_t m = 0;
@@ -1014,7 +1050,17 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
                                    const SweepRules& rules)
 {
     std::vector<SweepStep> steps;
-    const bool one_tile = n <= tile_bits(dt) + (rules.pad_all ? 0 : 1);
+    // one qubit more is one tile where most blocks have five qubits: smaller ones are
+    // bound by the vector units of the tile's one CU (32 of three qubits, 12 qubits
+    // complex128, as a recorded graph: 148 us as one tile, 107 as two, 111 a launch each)
+    int fives = 0, launches = 0;
+    for (int i = first; i < end; ++i) {
+        fives += blocks[i].k == 5;
+        launches += lone_launches(dt, n, blocks[i]);
+    }
+    const bool one_tile = n <= tile_bits(dt) + (!rules.pad_all && 2 * fives >= end - first);
+    const bool small = n < kPadQubits && !rules.pad_all;
+    const bool few = small && rules.few_alone && launches <= kFewLaunches;
     // From 22 qubits on a sweep may take a tile of one bit more, if its blocks
     // need it: 24 sweeps become 20 for a 28-qubit CNOT/CP circuit (complex128,
     // 51.3 -> 48.2 ms), 37 become 30 for a 23-qubit coupled program (1.71 -> 1.58
@@ -1044,9 +1090,14 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
         return one_tile || __builtin_popcountll(on >> lo) <= (coupled && !coupled_large ? tile_bits(dt) : T) - lo;
     };
     auto add = [&](std::vector<int>&& take, uint64_t on) {
+        if (few)
+            for (; take.size() > 1; take.erase(take.begin())) {
+                steps.emplace_back();
+                steps.back().blocks = {take[0]};
+            }
         SweepStep st;
         const FusedBlock& b0 = blocks[take[0]];
-        const bool lone = n < kReorderQubits || rules.pad_all || (n <= lone_qubits(dt) && b0.k == 5);
+        const bool lone = !(few || (small && lone_launches(dt, n, b0) < kFewLaunches)) && (n < kReorderQubits || rules.pad_all || (n <= lone_qubits(dt) && b0.k == 5));
         st.multi = take.size() > 1 || (lone && eligible(b0));
         st.blocks = std::move(take);
         st.padded = rules.pad_all || n >= kPadQubits;
@@ -1145,10 +1196,11 @@ namespace {
 uint32_t slot_bytes(sv_dtype_t dt, uint32_t a) { return dt == SV_C64 ? 8u * slot<float>(a) : 16u * slot<double>(a); }
 
 // Byte offsets (grp) and positions (pos) of the group index's bits: the tile
-// bits outside `used`, the lanes' first; returns their number.  The first 4 (complex64; complex128 3) lane bits are to be
+// bits outside `used`, those of the state's n qubits first, the lanes' first of these;
+// returns their number.  The first 4 (complex64; complex128 3) lane bits are to be
 // independent in the 32 banks a write sees, and one more with them in the 64
 // of a read, as far as there are such bits.
-int choose_lanes(sv_dtype_t dt, int T, uint32_t used, uint32_t* grp, int* pos)
+int choose_lanes(sv_dtype_t dt, int T, int n_qubits, uint32_t used, uint32_t* grp, int* pos)
 {
     const int width = dt == SV_C64 ? 5 : 4;
     uint32_t left = ((1u << T) - 1u) & ~used;
@@ -1172,12 +1224,13 @@ int choose_lanes(sv_dtype_t dt, int T, uint32_t used, uint32_t* grp, int* pos)
         grp[n++] = slot_bytes(dt, 1u << p);
     };
     auto bank = [&](int p) { return (dt == SV_C64 ? slot<float>(1u << p) : slot<double>(1u << p)) & ((1u << width) - 1u); };
-    for (int p = 0; p < T && n < width - 1; ++p)
+    const int own = std::min(T, n_qubits);
+    for (int p = 0; p < own && n < width - 1; ++p)
         if (((left >> p) & 1) && add(low, bank(p) & ((1u << (width - 1)) - 1u))) {
             add(full, bank(p));
             take(p);
         }
-    for (int p = 0; p < T && n < width; ++p)
+    for (int p = 0; p < own && n < width; ++p)
         if (((left >> p) & 1) && add(full, bank(p))) take(p);
     for (int p = 0; p < T; ++p)
         if ((left >> p) & 1) take(p);
@@ -1315,7 +1368,7 @@ void pack_sweep(sv_dtype_t dt, const SweepStep& st, const FusedBlock* blocks, Sw
                 pos[a++] = p;
                 used |= 1u << p;
             }
-        const int left = choose_lanes(dt, T, used, s.grp, group);
+        const int left = choose_lanes(dt, T, n, used, s.grp, group);
         if (b.n_couple > 0) s.kind |= kSweepCoupled;
         if (st.coupled) {
             // turns of each target's phase, by the coupled qubit's place: a bit
