@@ -98,19 +98,23 @@ sv_status_t sv_handle_destroy(sv_handle_t h);
 /* Rebinds the handle to another stream (the caller synchronises the switch). */
 sv_status_t sv_handle_set_stream(sv_handle_t h, void* hip_stream);
 
-/* Tile variant of the five-qubit sweeps (the fused-gate hot path, Sec.
- * II-B: gate fusion makes k = 5 the common case), complex64 and complex128.
- * All variants do the same arithmetic on every amplitude group, so results
- * are bitwise the same whichever runs; they differ in tile shape (256-thread
- * workgroups on 32 KiB tiles of 1 KiB runs, or 512-thread workgroups on
- * 64 KiB tiles with twice as long runs), in which index bits besides the
- * targets a tile spans, and in the order workgroups take tiles.  Which one
- * moves HBM fastest depends on the target bits.
- *   SV_TILE_AUTO (default): after the handle's first SV_TILE_WARM_SWEEPS
- *     five-qubit sweeps (untimed, spread), it times each variant three
- *     times, in rotating order, on the sweeps of every (dtype, state size,
- *     target set) it sees, with HIP events on its stream, then keeps the
- *     variant with the lowest mean (no timing while the stream is being
+/* Tile variant of the sweeps of one five-qubit block (the fused-gate hot path,
+ * Sec. II-B: gate fusion makes k = 5 the common case), complex64 and
+ * complex128.  All variants do the same arithmetic on every amplitude group, so
+ * results are bitwise the same whichever runs; they differ in tile shape
+ * (256-thread workgroups on 32 KiB tiles of 1 KiB runs, or 512-thread
+ * workgroups on 64 KiB tiles with twice as long runs), in which index bits
+ * besides the targets a tile spans, and in the order workgroups take tiles.
+ * Which one moves HBM fastest depends on the target bits.
+ *   SV_TILE_AUTO (default): fused programs share sweeps between blocks
+ *     (sv_apply_fused): below 22 qubits with the bits of the forced modes, from
+ *     22 qubits on with other roundings.  For the sweeps that are left (single
+ *     gates; blocks that share none, five-qubit ones only on more than 26
+ *     qubits complex64 / 25 complex128), after the handle's
+ *     first SV_TILE_WARM_SWEEPS five-qubit sweeps (untimed, spread), it times
+ *     each variant three times, in rotating order, on the sweeps of every (dtype,
+ *     state size, target set) it sees, with HIP events on its stream, then keeps
+ *     the variant with the lowest mean (no timing while the stream is being
  *     captured; the spread variant until a target set has timings).
  *     States of fewer than SV_TILE_TUNE_MIN_QUBITS qubits, whose sweeps
  *     are bound by the launch rather than by the tile shape, always take
@@ -314,17 +318,20 @@ sv_status_t sv_fused_free(sv_fused_t f);
 
 /* Applies all blocks of f (async), as if in order: consecutive blocks whose
  * qubits fit one tile share a sweep of the state (Sec. II-B: a sweep is bound
- * by the bandwidth), and on states of 22 qubits and more a block may pass
- * blocks it commutes with on its way into a sweep, and complex64 sweeps multiply
- * exact bf16 parts of matrix and amplitudes, with FP32 sums (less error than the
- * FP32 sweeps').  With a forced tile variant
- * (sv_handle_set_tile_mode) every block is swept on its own, in order.  Block
- * matrices are uploaded in batches of up to 1 MiB, one host-to-device copy per
- * batch. */
+ * by the bandwidth).  Below 22 qubits a state has the bits of one sweep per
+ * block.  From 22 qubits on a block may pass blocks it commutes with on its way
+ * into a sweep, and complex64 sweeps multiply the matrix and the amplitudes in
+ * bf16 parts (all 24 bits of a float; FP32 where the parts do not hold one) with
+ * FP32 sums, whose error against 64 bits is no larger than the FP32 sweeps'.
+ * With a forced tile variant (sv_handle_set_tile_mode) every block is swept on
+ * its own, in order.  Block matrices are uploaded in batches of up to 1 MiB, one
+ * host-to-device copy per batch. */
 sv_status_t sv_apply_fused(sv_state_t s, sv_fused_t f);
 
 /* Applies blocks [first, first + count) of f, as sv_apply_fused does (async), so a caller
  * can interleave its own work (timing events, measurements) between blocks.
+ * Blocks of different calls share no sweep: from 22 qubits on a program applied in
+ * ranges may round differently from the whole.
  * Requires 0 <= first and first + count <= the block count. */
 sv_status_t sv_apply_fused_range(sv_state_t s, sv_fused_t f, int32_t first, int32_t count);
 
@@ -459,8 +466,10 @@ sv_status_t sv_renormalize(sv_state_t s, double* norm_out);
 
 /*
  * Expectation values of Pauli strings (Table I: expectation value with
- * Pauli strings): out[t] = <psi|P_t|psi> / <psi|psi>, FP64 accumulation in a
- * fixed order.  A term may not name a qubit twice.  Blocks.
+ * Pauli strings): out[t] = <psi|P_t|psi> / <psi|psi>, FP64 accumulation in an
+ * order fixed by the state size and, for strings with X or Y, by the strings of
+ * the call (they share read sweeps), so that such a string's last bits may differ
+ * between calls with other strings.  A term may not name a qubit twice.  Blocks.
  */
 sv_status_t sv_expect_pauli(sv_state_t s, const sv_pauli_term_t* terms, int32_t n_terms,
                             double* out);

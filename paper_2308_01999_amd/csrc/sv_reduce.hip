@@ -383,9 +383,12 @@ __global__ __launch_bounds__(kThreads) void k_expect_xy_group(const typename Cx<
 // popcount(i & z) = popcount(c & z) + popcount(x(s) & z): the second part is a
 // bit of the term's `sig`, the same for all cosets.  FP64, per-thread order
 // fixed by n and the sweep's masks.
-// Bound by HBM: 16 random strings on 26 qubits complex64 take four sweeps of
-// four masks, 82 us each (6.5 TB/s), 0.33 ms, where 16 sweeps of one mask took 2.8
-// ms (175 us each: 32 predicated terms an item on the vector units).
+// Bound by HBM up to D = 4: on 26 qubits complex64 and 25 complex128 a sweep alone
+// takes 85-100 us (5.4-6.3 TB/s, 1.000x of the state's bytes, vector units 44% busy at D = 4), four in one
+// launch 330 us (6.5 TB/s).  At D = 5 (173 registers, two waves a SIMD) complex64 takes
+// 124 us, the latency of its loads, complex128 96.  16 random strings on 26 qubits complex64
+// take four sweeps of four masks, 0.33 ms, where 16 sweeps of one mask took 2.8 ms
+// (175 us each: 32 predicated terms an item on the vector units).
 constexpr int kJointMax = 5;         // masks of one sweep
 constexpr int kJointTerms = 2;       // terms of one mask in it
 
@@ -511,7 +514,6 @@ void launch_joint(hipStream_t stream, int d, dim3 grid, const void* psi_v, const
     SV_HIP(hipGetLastError());
 }
 
-// out[t] = sum over blocks of part[t * nb + b], fixed order.  One block per t.
 // A thread's sum of p[tid], p[tid + 256], ... in this order.  One block sums up
 // to 8192 values, so their latency counts: eight loads are in flight at once (8192
 // values of a term 11 -> 6 us, of 17 terms 17 -> 7 us).
@@ -529,6 +531,7 @@ __device__ __forceinline__ double strided_sum(const double* __restrict__ p, uint
     return acc;
 }
 
+// out[t] = sum over blocks of part[t * nb + b], fixed order.  One block per t.
 __global__ __launch_bounds__(kThreads) void k_finish_sums(const double* __restrict__ part, uint64_t nb,
                                                          double* __restrict__ out)
 {

@@ -16,14 +16,14 @@
 // cores for several.  A block costs a wave 48 MFMAs: of v_mfma_f32_32x32x2_f32
 // 3072 cycles (1.7 ms a block at 30 qubits), of v_mfma_f64_16x16x4_f64 the same,
 // of v_mfma_f32_32x32x16_bf16 1536 (block5_split, states of 22 qubits and
-// more).  A tile is 32 KiB (64 KiB and 512 threads where plan_sweeps says) and a workgroup 256
-// threads and one tile: the runs of 128 bytes that this leaves for eight free
-// bits stream at 4.6-5.4 TB/s, and four workgroups a CU, at most
-// 128 vector registers a thread (the coupled forms spill 11 around a tile's blocks,
-// none inside them), hide each other's loads, stores and barriers.  They do it better than three that load their next tile during a
-// tile's blocks: loads return in order, so a matrix behind a tile waits for
-// HBM (28 qubits, sweeps of 4 blocks: complex64 1.38 -> 1.18 ms, complex128 on
-// 27 qubits 1.91 -> 1.83).
+// more).  A tile is 32 KiB (64 KiB and 512 threads where plan_sweeps says) and a
+// workgroup 256 threads and one tile: the runs of 128 bytes that this leaves for
+// eight free bits stream at 4.6-5.4 TB/s, and four workgroups a CU, at most 128
+// vector registers a thread (the coupled forms spill 11 around a tile's blocks,
+// none inside them), hide each other's loads, stores and barriers.  They do it
+// better than three that load their next tile during a tile's blocks: loads
+// return in order, so a matrix behind a tile waits for HBM (28 qubits, sweeps of
+// 4 blocks: complex64 1.38 -> 1.18 ms, complex128 on 27 qubits 1.91 -> 1.83).
 // Measured, before (a sweep per block) and after: 30-qubit brickwork circuit
 // of depth 20, complex64, 52 blocks in 20 sweeps, 156 -> 92 ms; 28-qubit
 // random CNOT/CP circuit, complex128, 71 -> 48 ms; 19-qubit circuit on random
@@ -1097,7 +1097,8 @@ std::vector<SweepStep> plan_sweeps(sv_dtype_t dt, int n, int cu_count, const Fus
             }
         SweepStep st;
         const FusedBlock& b0 = blocks[take[0]];
-        const bool lone = !(few || (small && lone_launches(dt, n, b0) < kFewLaunches)) && (n < kReorderQubits || rules.pad_all || (n <= lone_qubits(dt) && b0.k == 5));
+        const bool own = few || (small && lone_launches(dt, n, b0) < kFewLaunches);
+        const bool lone = !own && (n < kReorderQubits || rules.pad_all || (n <= lone_qubits(dt) && b0.k == 5));
         st.multi = take.size() > 1 || (lone && eligible(b0));
         st.blocks = std::move(take);
         st.padded = rules.pad_all || n >= kPadQubits;
