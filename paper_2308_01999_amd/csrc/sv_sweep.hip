@@ -976,7 +976,6 @@ bool few_products(const FusedBlock& b)
 {
     const int d = 1 << b.k;
     bool re = false, im = false, wide = false;
-    int most = 0;
     for (int i = 0; i < d; ++i) {
         int row = 0;
         for (int c = 0; c < d; ++c) {
@@ -984,15 +983,15 @@ bool few_products(const FusedBlock& b)
             re |= v[0] != 0.f;
             im |= v[1] != 0.f;
             row += v[0] != 0.f || v[1] != 0.f;
+            if (row > 2 || (re && im)) return false;
             for (float f : v) {
                 uint32_t w;
                 std::memcpy(&w, &f, 4);
                 wide |= (w & 0xffffu) != 0;
             }
         }
-        most = std::max(most, row);
     }
-    return most <= 2 && !(re && im) && wide;
+    return wide;
 }
 
 // The qubits that decide which blocks commute with b: its targets and the

@@ -105,3 +105,33 @@ def test_matrix_entries_of_any_size(scale):
     exact = run("c128", P.SV_TILE_AUTO)
     split, fp32 = (np.linalg.norm(run("c64", k) - exact) for k in (P.SV_TILE_AUTO, P.SV_TILE_NARROW))
     assert 0.0 < split <= fp32, (split, fp32)
+
+
+@pytest.mark.parametrize("qubits", [(2,), (0, 1, 2, 3, 4)])
+@pytest.mark.parametrize("exponent", [0, -104])
+def test_coupled_blocks_on_fp32_products(qubits, exponent):
+    # a coupled block that takes FP32 products (one real gate), or whose amplitudes'
+    # parts lose bits, or both: phases from outside the tile and from inside it
+    import torch
+    import paper_2308_01999_amd as P
+    x = (_amplitudes(11, False) * np.float32(2.0) ** np.float32(exponent)).astype(np.complex64)
+    gates = [W.Gate("cp", (a, b), (0.3 + 0.1 * a + 0.01 * b,)) for a in range(5) for b in (5, 6, 9, 14, 17, 20, 21)]
+    gates += CHAIN + [W.Gate("u3", (q,), (0.7 + 0.3 * q, 0.0, 0.0)) for q in qubits]
+    f = P.fuse(gates, 5, coupled=True)
+    assert any(len(t) == 5 and len(c[0]) > 0 for (t, _), c in zip(f.blocks(), f.couplings()))
+
+    def run(dt, mode):
+        h = P.Handle()
+        h.set_tile_mode(mode)
+        t = torch.from_numpy(x.astype(np.complex64 if dt == "c64" else np.complex128)).cuda()
+        st = P.State(h, N, dt, basis=None, tensor=t)
+        P.sv_apply_fused(st.s, f.f)
+        out = st.to_numpy()
+        st.close()
+        h.close()
+        return out
+
+    exact = run("c128", P.SV_TILE_NARROW)
+    swept, alone = (np.linalg.norm((run("c64", m) - exact) * 2.0 ** -exponent) for m in (P.SV_TILE_AUTO, P.SV_TILE_NARROW))
+    f.free()
+    assert 0.0 < swept <= alone, (swept, alone)
